@@ -221,3 +221,27 @@ def tolerance(case):
     if case["op"] == "f32":
         return {"rel": 6e-6, "max": 3e-5}
     return {"rel": 9e-3, "max": 3.7e-2} if case["op"] == "out_bf16" else {"rel": 6.5e-3, "max": 3.7e-2}
+
+
+def exact(case, seed):
+    """What run() returns for these inputs, in float64 from the definition: sum over the active branches of
+    alpha_b * (SiLU(x Wg_b^T) * (x Wu_b^T)) Wd_b^T.  None for the fade, whose outputs are bytes and counts."""
+    if case["op"] == "fade":
+        return None
+    results = []
+    for layer in prepare(case, seed)["layers"]:
+        off, alpha, mask = layer["table"]
+        x = layer["x"].double()
+        Wg, Wu, Wd = layer["W"]
+        out = torch.zeros(x.shape, dtype=torch.float64, device="cuda")
+        for b in range(case["branches"]):
+            lo, hi = int(off[b]), int(off[b + 1])
+            if not mask[b] or hi == lo:
+                continue
+            g = x @ Wg[lo:hi].double().t()
+            h = float(alpha[b]) * (g * torch.sigmoid(g)) * (x @ Wu[lo:hi].double().t())
+            if case["op"] == "routed":
+                h *= (layer["route"][:, b] != 0).double()[:, None]
+            out += h @ Wd[:, lo:hi].double().t()
+        results.append(out)
+    return results
