@@ -63,7 +63,8 @@ enum {
 
 /* Kernel path selection for the *_ws entry points. */
 enum {
-    MLPMOE_PATH_AUTO = 0,    /* library picks: decode for T <= 16, MFMA otherwise, generic if unaligned */
+    MLPMOE_PATH_AUTO = 0,    /* library picks: decode for T <= 16, MFMA otherwise and for odd branch boundaries,
+                              * generic if d_model or d_inter is not a multiple of 8                    */
     MLPMOE_PATH_GENERIC = 1, /* LDS-tiled FMA kernels: any shape and alignment                        */
     MLPMOE_PATH_MFMA = 2,    /* bf16 MFMA prefill kernels (needs d_model%8==0 and offsets%8==0)       */
     MLPMOE_PATH_DECODE = 3,  /* weight-streaming kernels, T <= 16 (same alignment needs as MFMA)      */
@@ -290,10 +291,10 @@ MLPMOE_API int mlpmoe_forward_f32_ws(const float *x, const float *W_gate, const 
  * sums the branches b with active_mask[b] != 0 AND route[t * B + b] != 0,
  *     out[t] = sum over those b of alpha[b] * W_down^(b) [ SiLU(W_gate^(b) x_t) (.) W_up^(b) x_t ].
  * All other arguments, layouts and rounding are those of mlpmoe_forward_bf16 (bf16 storage only).
- * When every branch offset is a multiple of 8 (mlpmoe_slice with pad_to = 8) the kernels skip work
- * per (tile of 256 tokens, branch) pair that no token of the tile is routed to -- for T <= 16 per
- * branch no token takes, whose weights are then never read -- so tokens grouped by route make the
- * call proportionally cheaper; other tables take the generic kernels, which only mask.
+ * When d_model and d_inter are multiples of 8 the kernels skip work per (tile of 256 tokens, branch) pair
+ * that no token of the tile is routed to -- for T <= 16 and branch offsets that are all multiples of 8
+ * (mlpmoe_slice with pad_to = 8) per branch no token takes, whose weights are then never read -- so tokens
+ * grouped by route make the call proportionally cheaper; other tables take the generic kernels, which only mask.
  * The _ws form takes a caller-owned workspace of mlpmoe_workspace_bytes() bytes and never allocates.
  */
 MLPMOE_API int mlpmoe_forward_routed_bf16(const void *x, const void *W_gate, const void *W_up,

@@ -81,9 +81,9 @@ size_t mfma_partial_bytes(int T, int d_model, int d_inter);
 hipError_t launch_fill_zero(float *out, size_t n, hipStream_t s);
 hipError_t launch_fill_zero16(uint16_t *out, size_t n, hipStream_t s);
 hipError_t launch_generic(const FwdArgs &a, const BranchTable &bt, bool is_bf16);
-hipError_t launch_mfma_bf16(const FwdArgs &a, const BranchTable &bt);
+hipError_t launch_mfma_bf16(const FwdArgs &a, const BranchTable &bt, bool uneven);
 size_t route_scratch_bytes(int T, int d_inter);
-hipError_t launch_mfma_routed_bf16(const FwdArgs &a, const BranchTable &bt);
+hipError_t launch_mfma_routed_bf16(const FwdArgs &a, const BranchTable &bt, bool uneven);
 hipError_t launch_decode_bf16(const FwdArgs &a, const BranchTable &bt);
 hipError_t launch_decode_routed_bf16(const FwdArgs &a, const BranchTable &bt);
 hipError_t launch_compact(const void *Wg, const void *Wu, const void *Wd, const int32_t *gather,

@@ -18,6 +18,7 @@
 // 16x16x32 shape is used rather than 32x32x16 because the chip is power limited on this work: with
 // random operands a pure stream of 16x16x32 MFMAs sustains 2.0 PFLOP/s, one of 32x32x16 1.7.
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -33,7 +34,13 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 constexpr int BM = 256;          // tokens per tile of the large-tile kernels (and of the routed path's tables)
 constexpr int BM_SMALL = 128;    // tokens per tile of the small-tile kernels
 constexpr int BNH_MAX = 128;     // rows of each of the two B blocks: 32 * NB, NB = 4 (128) or 2 (64)
-constexpr int BK = 64;           // K elements per tile: one tile row is 128 bytes = one cache line
+// A K tile is 128 bytes (one cache line) of every row: 64 bf16 values or 32 floats; a 16-byte chunk is the unit of
+// the loads and the alignment unit of K ranges and neuron tiles.
+template <typename E>
+struct Elem {
+    static constexpr int BK = 128 / sizeof(E), CHUNK = 16 / sizeof(E);
+};
+constexpr int BK = Elem<uint16_t>::BK;
 // The LDS is a ring that keeps the K tile in use and the D tiles requested ahead of it.  Two layouts:
 //   alternating (the 256-token tiles): 2 D + 1 parts of equal size, A0 B0 A1 B1 A2 | B2 A3 ...; with D = 2 the
 //       ring fills the LDS of a CU (five parts of 32 KiB), half a K tile less than whole stages would need;
@@ -43,8 +50,8 @@ __host__ __device__ constexpr int n_parts(int depth) { return 2 * depth + 1; }
 // A part of the alternating ring holds the A rows (BMT tokens), or the B rows (2 blocks of 32 NB), of one K tile.
 // 256-token tiles: 32 KiB parts, the ring is the whole LDS of a CU (one workgroup of 8 waves per CU).
 // 128-token tiles with NB = 2: 16 KiB parts, 80 KiB per workgroup of 4 waves, two workgroups per CU.
-__host__ __device__ constexpr int part_bytes(int bmt, int nb) { return (bmt > 64 * nb ? bmt : 64 * nb) * BK * 2; }
-__host__ __device__ constexpr int stage_bytes(int bmt, int nb) { return (bmt + 64 * nb) * BK * 2; }
+__host__ __device__ constexpr int part_bytes(int bmt, int nb) { return (bmt > 64 * nb ? bmt : 64 * nb) * 128; }
+__host__ __device__ constexpr int stage_bytes(int bmt, int nb) { return (bmt + 64 * nb) * 128; }
 __host__ __device__ constexpr int lds_bytes(int bmt, int nb, int depth = 2, bool staged = false)
 {
     return staged ? (depth + 1) * stage_bytes(bmt, nb) : n_parts(depth) * part_bytes(bmt, nb);
@@ -66,6 +73,29 @@ typedef __attribute__((address_space(3))) void *lptr_t;
 __device__ __forceinline__ void dma16(const void *src, void *lds_dst)
 {
     __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)lds_dst, 16, 0, 0);
+}
+
+// A fragment piece: one 16-byte chunk per lane.  Lane group lane >> 4 holds a chunk of its own, so a bf16 piece is
+// the 32 K values of one 16x16x32 MFMA; a float piece is four 16x16x4 steps, step e taking element e of every chunk.
+template <typename E>
+struct FragOf {
+    typedef bf16x8 type;
+};
+template <>
+struct FragOf<float> {
+    typedef f32x4 type;
+};
+template <typename E>
+using Frag = typename FragOf<E>::type;
+template <typename E>
+constexpr int MFMAS_PER_CHUNK = sizeof(E) == 4 ? 4 : 1;
+__device__ __forceinline__ f32x4 mfma_step(bf16x8 r, bf16x8 c, f32x4 acc, int)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(r, c, acc, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4 mfma_step(f32x4 r, f32x4 c, f32x4 acc, int e)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(r[e], c[e], acc, 0, 0, 0);
 }
 
 // Workgroup barrier that waits until at most N of this wave's direct-to-LDS loads (they return
@@ -131,15 +161,15 @@ __device__ __forceinline__ KRunsLanes routed_runs(const BranchTable &bt, const u
     return kr;
 }
 
-template <typename KR>
+template <int BKE, typename KR>
 __device__ __forceinline__ KCursor k_seek(const KR &kr, int tile)
 {
     KCursor c{0, 0};
     for (int r = 0; r < kr.n_runs(); ++r) {
-        const int n = (kr.end(r) - kr.start(r) + BK - 1) / BK;
+        const int n = (kr.end(r) - kr.start(r) + BKE - 1) / BKE;
         if (tile < n) {
             c.run = r;
-            c.k = kr.start(r) + tile * BK;
+            c.k = kr.start(r) + tile * BKE;
             return c;
         }
         tile -= n;
@@ -175,13 +205,17 @@ __device__ __forceinline__ KCursor k_seek(const KR &kr, int tile)
 // NB = 16-row MFMA pieces per B block per wave: 4 (B blocks of 128 rows, a 256 x 256 tile) or 2 (B
 // blocks of 64 rows, a 256 x 128 tile, for shapes that would otherwise leave most CUs without a
 // tile in the last round).  A B part of 64 + 64 rows fills half of its ring slot.
-template <int BMT, int WM, int NB, int D, bool kStaged, bool kRowsAreB, typename KR>
-__device__ __forceinline__ void mainloop(const uint16_t *__restrict__ A_tile, int lda, int a_valid,
-                                         const uint16_t *__restrict__ B0_tile,
-                                         const uint16_t *__restrict__ B1_tile, int ldb, int b0_valid,
+// Float storage (E = float) differs only in what a 16-byte chunk holds: 4 K elements, fed to four
+// v_mfma_f32_16x16x4_f32 one after the other instead of one 16x16x32.
+template <int BMT, int WM, int NB, int D, bool kStaged, bool kRowsAreB, typename E, typename KR>
+__device__ __forceinline__ void mainloop(const E *__restrict__ A_tile, int lda, int a_valid,
+                                         const E *__restrict__ B0_tile,
+                                         const E *__restrict__ B1_tile, int ldb, int b0_valid,
                                          int b1_valid, const KR &kr, int kt_begin, int kt_end, char *lds,
                                          f32x4 (&acc0)[BMT / 16 / WM][NB], f32x4 (&acc1)[BMT / 16 / WM][NB])
 {
+    constexpr int BKE = Elem<E>::BK, CHUNK = Elem<E>::CHUNK;
+    constexpr unsigned ES = sizeof(E);
     constexpr int MI = BMT / 16 / WM;             // 16-row MFMA tiles per wave along M
     constexpr int NWAVES = WM * 2;
     constexpr int BNH = 32 * NB;                  // rows of each B block
@@ -221,7 +255,7 @@ __device__ __forceinline__ void mainloop(const uint16_t *__restrict__ A_tile, in
         const int cl = cl0 ^ (n & 1);             // PL is even, so slab parity is n parity
         int ra = slab * 8 + lr;
         ra = ra < a_valid ? ra : a_valid - 1;
-        a_off[n] = (unsigned)ra * (unsigned)lda * 2u + (unsigned)cl * 16u;
+        a_off[n] = (unsigned)ra * (unsigned)lda * ES + (unsigned)cl * 16u;
     }
 #pragma unroll
     for (int n = 0; n < PLB; ++n) {
@@ -229,7 +263,7 @@ __device__ __forceinline__ void mainloop(const uint16_t *__restrict__ A_tile, in
         const int cl = cl0 ^ (n & 1);
         int rb = (slab % (4 * NB)) * 8 + lr;
         rb = rb < b_valid ? rb : b_valid - 1;
-        b_off[n] = (unsigned)rb * (unsigned)ldb * 2u + (unsigned)cl * 16u;
+        b_off[n] = (unsigned)rb * (unsigned)ldb * ES + (unsigned)cl * 16u;
     }
     const char *a_base = reinterpret_cast<const char *>(A_tile);
     const char *b_base = reinterpret_cast<const char *>(second ? B1_tile : B0_tile);
@@ -245,7 +279,7 @@ __device__ __forceinline__ void mainloop(const uint16_t *__restrict__ A_tile, in
         int run, k, kend, left, off;              // off: byte offset in the ring of the part to be filled next
     };
     auto advance = [&](Issue &q) {                // stays on the last range once the list is exhausted
-        q.k += BK;
+        q.k += BKE;
         if (q.k >= q.kend && q.run + 1 < kr.n_runs()) {
             ++q.run;
             q.k = kr.start(q.run);
@@ -264,10 +298,10 @@ __device__ __forceinline__ void mainloop(const uint16_t *__restrict__ A_tile, in
     auto part_of = [&](const Issue &q, const char *base, char *w_dst) {
         Part pt;
         const int kend = q.left > 0 ? q.kend : -(1 << 30);
-        pt.src = base + (size_t)q.k * 2;
+        pt.src = base + (size_t)q.k * ES;
         pt.dst = w_dst + q.off;
-        pt.ok[0] = q.k + cl0 * 8 < kend;
-        pt.ok[1] = q.k + (cl0 ^ 1) * 8 < kend;
+        pt.ok[0] = q.k + cl0 * CHUNK < kend;
+        pt.ok[1] = q.k + (cl0 ^ 1) * CHUNK < kend;
         return pt;
     };
     auto dma_part = [&](int n, const Part &pt, const unsigned *off) {
@@ -295,26 +329,26 @@ __device__ __forceinline__ void mainloop(const uint16_t *__restrict__ A_tile, in
     // first / second B block each), then the A pieces.  MFMA m uses A piece m / (2 NB) and B piece
     // m % (2 NB).
     struct Frags {
-        bf16x8 v[N_PIECES];
+        Frag<E> v[N_PIECES];
     };
     auto read_piece = [&](Frags &f, int g, int a_at, int ks) {
         // the B part of a tile follows its A part (alternating ring: in the next part, which may be the first)
         const int b_at = kStaged ? a_at + B_FIRST : (a_at + B_FIRST < RING_BYTES ? a_at + B_FIRST : 0);
         if (g < 2 * NB)
-            f.v[g] = *reinterpret_cast<const bf16x8 *>(lds + b_at + b_rd[ks] + (g / NB) * (BNH * 128) +
+            f.v[g] = *reinterpret_cast<const Frag<E> *>(lds + b_at + b_rd[ks] + (g / NB) * (BNH * 128) +
                                                        (g % NB) * (16 * 128));
         else
-            f.v[g] = *reinterpret_cast<const bf16x8 *>(lds + a_at + a_rd[ks] + (g - 2 * NB) * (16 * 128));
+            f.v[g] = *reinterpret_cast<const Frag<E> *>(lds + a_at + a_rd[ks] + (g - 2 * NB) * (16 * 128));
     };
     // kRowsAreB: the B rows (weights) are the MFMA's row operand and the A rows (tokens) its column
     // operand.  In the 16x16 result lane l then holds column l & 15 = one token and rows
     // 4 * (l >> 4) + 0..3 = four consecutive B rows, which the epilogues store as one 8- or 16-byte
     // piece of the token's output row.  Otherwise tokens are the rows.
-    auto mfma_n = [&](const Frags &f, int m) {
+    auto mfma_n = [&](const Frags &f, int m, int e) {
         const int i = m / (2 * NB), b = m % (2 * NB);
-        const bf16x8 r = kRowsAreB ? f.v[b] : f.v[2 * NB + i], c = kRowsAreB ? f.v[2 * NB + i] : f.v[b];
-        if (b < NB) acc0[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(r, c, acc0[i][b], 0, 0, 0);
-        else acc1[i][b - NB] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(r, c, acc1[i][b - NB], 0, 0, 0);
+        const Frag<E> r = kRowsAreB ? f.v[b] : f.v[2 * NB + i], c = kRowsAreB ? f.v[2 * NB + i] : f.v[b];
+        if (b < NB) acc0[i][b] = mfma_step(r, c, acc0[i][b], e);
+        else acc1[i][b - NB] = mfma_step(r, c, acc1[i][b - NB], e);
     };
     // One K step, written in the instruction order wanted: slots of {4 MFMAs, then LDS reads of
     // the next step's fragments, then (in evenly spaced slots) one direct load}; nothing may be
@@ -330,10 +364,14 @@ __device__ __forceinline__ void mainloop(const uint16_t *__restrict__ A_tile, in
             // asking at 1, cannot cut in, which the older wave otherwise always does) and drops
             // to 0 for its loads and address arithmetic, which then run under the other's turn.
             __builtin_amdgcn_s_setprio(1);
-            mfma_n(cur_f, 4 * g);
+            mfma_n(cur_f, 4 * g, 0);
             __builtin_amdgcn_s_setprio(3);
 #pragma unroll
-            for (int q = 1; q < 4; ++q) mfma_n(cur_f, 4 * g + q);
+            for (int q = 1; q < 4; ++q) mfma_n(cur_f, 4 * g + q, 0);
+#pragma unroll
+            for (int e = 1; e < MFMAS_PER_CHUNK<E>; ++e)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) mfma_n(cur_f, 4 * g + q, e);
             __builtin_amdgcn_s_setprio(0);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -354,7 +392,7 @@ __device__ __forceinline__ void mainloop(const uint16_t *__restrict__ A_tile, in
     // prologue: the parts of tiles 0 .. D-1 in flight, tile 0 landed
     Issue qa, qb;
     {
-        const KCursor c = k_seek(kr, kt_begin);
+        const KCursor c = k_seek<BKE>(kr, kt_begin);
         qa.run = c.run;
         qa.k = c.k;
         qa.kend = kr.end(c.run);
@@ -393,6 +431,96 @@ __device__ __forceinline__ void mainloop(const uint16_t *__restrict__ A_tile, in
     pipeline_barrier<0>();                        // LDS may be reused by the caller
 }
 
+// Tables whose run boundaries are not multiples of a 16-byte chunk (kEdges).  The neuron tiles of the gate+up
+// projection walk the runs rounded OUTWARDS to whole chunks (H is stored for active neurons only); the K ranges of
+// the down projection are the runs rounded INWARDS, and the chunks that lie across a boundary, at most two per run,
+// are added by edge_steps below: they go from global memory straight into MFMA operand registers, inactive K
+// elements masked to 0 in BOTH operands (nothing of a pruned branch reaches the sum, non-finite values included).
+// What bounds it: one global load latency per four chunks at the end of a tile.  896 x 4864 in 12 branches of 406 / 405
+// neurons, first 9 kept, T = 333: 34 us against 701 us for the general FMA kernels.
+constexpr int kMaxEdges = 2 * kMaxRuns;
+struct EdgeList {
+    int n;
+    int col[kMaxEdges];                           // first K element of the chunk
+    uint8_t mask[kMaxEdges];                      // bit i: element i of the chunk is active
+};
+struct NoEdges {};
+// Edges of run [s, e): its first chunk (side 0) and its last (side 1), as far as they are partial.  A run inside one
+// chunk has its elements in side 0, or in side 1 if it starts at the chunk.  mask 0: no such edge.
+template <int CHUNK>
+__host__ __device__ inline void run_edge(int s, int e, int side, int &col, unsigned &mask)
+{
+    const int cs = s / CHUNK * CHUNK, ce = e / CHUNK * CHUNK;
+    const unsigned all = (1u << CHUNK) - 1;
+    col = side == 0 ? cs : ce;
+    if (side == 0) mask = s == cs ? 0u : (all << (s - cs)) & (e - cs < CHUNK ? (1u << (e - cs)) - 1 : all);
+    else mask = (e == ce || (ce == cs && s != cs)) ? 0u : (1u << (e - ce)) - 1;
+}
+// The runs of `raw` rounded inwards, empty ones dropped (lane r holds range r).
+template <int CHUNK>
+__device__ __forceinline__ KRunsLanes inner_runs(const KRunsLanes &raw)
+{
+    KRunsLanes in{0, 0, 0};
+    const int lane = threadIdx.x & 63;
+    for (int r = 0; r < raw.n; ++r) {
+        const int s = (raw.start(r) + CHUNK - 1) / CHUNK * CHUNK, e = raw.end(r) / CHUNK * CHUNK;
+        if (e <= s) continue;
+        in.v_start = lane == in.n ? s : in.v_start;
+        in.v_end = lane == in.n ? e : in.v_end;
+        ++in.n;
+    }
+    return in;
+}
+// chunk & mask, element by element
+template <typename E>
+__device__ __forceinline__ Frag<E> masked_chunk(const E *p, unsigned mask)
+{
+    u32x4 v = *reinterpret_cast<const u32x4 *>(p);
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const uint32_t m = sizeof(E) == 4 ? ((mask >> w) & 1u ? 0xffffffffu : 0u)
+                                          : ((mask >> (2 * w)) & 1u ? 0x0000ffffu : 0u) | ((mask >> (2 * w + 1)) & 1u ? 0xffff0000u : 0u);
+        v[w] &= m;
+    }
+    return __builtin_bit_cast(Frag<E>, v);
+}
+// Adds `n` edge chunks to the accumulators of a down tile: four chunks (one per lane group) per step.
+// at(i, col, mask) gives chunk i and may be asked with another i in every lane; all lanes of a wave ask together.
+template <int MI, int NB, typename E, typename At>
+__device__ __forceinline__ void edge_steps(int n, const At &at, const E *__restrict__ A_tile, int lda, int a_valid,
+                                           const E *__restrict__ B0_tile, const E *__restrict__ B1_tile, int ldb,
+                                           int b0_valid, int b1_valid, f32x4 (&acc0)[MI][NB], f32x4 (&acc1)[MI][NB])
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wm = wave >> 1, wn = wave & 1, lrow = lane & 15;
+    for (int i0 = 0; i0 < n; i0 += 4) {
+        int col = 0;
+        unsigned mask = 0;
+        const int i = i0 + (lane >> 4);
+        at(i < n ? i : n - 1, col, mask);
+        if (i >= n) mask = 0;
+        if (mask == 0) col = 0;                   // nothing to add: any chunk that exists
+        Frag<E> a[MI];
+#pragma unroll
+        for (int m = 0; m < MI; ++m) {
+            const int r = wm * (MI * 16) + m * 16 + lrow;
+            a[m] = masked_chunk(A_tile + (size_t)(r < a_valid ? r : a_valid - 1) * lda + col, mask);
+        }
+#pragma unroll
+        for (int b = 0; b < 2 * NB; ++b) {
+            const int r = wn * (16 * NB) + (b % NB) * 16 + lrow, valid = b < NB ? b0_valid : b1_valid;
+            const Frag<E> w = masked_chunk((b < NB ? B0_tile : B1_tile) + (size_t)(r < valid ? r : valid - 1) * ldb + col, mask);
+#pragma unroll
+            for (int e = 0; e < MFMAS_PER_CHUNK<E>; ++e)
+#pragma unroll
+                for (int m = 0; m < MI; ++m) {
+                    f32x4 &acc = b < NB ? acc0[m][b] : acc1[m][b - NB];
+                    acc = mfma_step(w, a[m], acc, e);
+                }
+        }
+    }
+}
+
 __device__ __forceinline__ int branch_of(const BranchTable &bt, int j)
 {
     int b = 0;
@@ -412,6 +540,24 @@ __device__ __forceinline__ uint16_t to_bf16(float v)
     const __bf16 b = (__bf16)v;          // v_cvt_pk_bf16_f32: round to nearest even
     return __builtin_bit_cast(uint16_t, b);
 }
+
+// alpha_b * SiLU(g) * u, as the storage type's kernels form it: with expf and a division for float storage
+__device__ __forceinline__ float gated(float alpha, float g, float u, uint16_t) { return alpha * silu_mul(g, u); }
+__device__ __forceinline__ float gated(float alpha, float g, float u, float)
+{
+    const float s = g / (1.0f + expf(-g));
+    return alpha * (s * u);
+}
+__device__ __forceinline__ void store1(uint16_t *p, float v) { *p = to_bf16(v); }
+__device__ __forceinline__ void store1(float *p, float v) { *p = v; }
+__device__ __forceinline__ void store4(uint16_t *p, f32x4 v)
+{
+    u32x2 pk;
+    pk.x = (uint32_t)to_bf16(v[0]) | ((uint32_t)to_bf16(v[1]) << 16);
+    pk.y = (uint32_t)to_bf16(v[2]) | ((uint32_t)to_bf16(v[3]) << 16);
+    *reinterpret_cast<u32x2 *>(p) = pk;
+}
+__device__ __forceinline__ void store4(float *p, f32x4 v) { *reinterpret_cast<f32x4 *>(p) = v; }
 
 // Workgroup id -> output tile.  The hardware deals consecutive workgroup ids round-robin to the
 // 8 XCDs, each with its own L2.  Every XCD therefore takes one contiguous eighth of a "grouped"
@@ -476,9 +622,9 @@ __device__ __forceinline__ bool neuron_tile(const BranchTable &bt, int tn, int b
 
 // One tile of the gate+up projection: tokens tm * BMT .., neurons n0 .. min(n0 + 32 NB, n_end) of a run that
 // ends at n_end.  lds: lds_bytes(BMT, NB, D) bytes.
-template <int BMT, int WM, int NB, int D, bool kStaged, bool kRouted>
-__device__ __forceinline__ void gate_up_tile(const uint16_t *__restrict__ X, const uint16_t *__restrict__ Wg,
-                                             const uint16_t *__restrict__ Wu, uint16_t *__restrict__ H, int T,
+template <int BMT, int WM, int NB, int D, bool kStaged, bool kRouted, bool kEdges = false, typename E>
+__device__ __forceinline__ void gate_up_tile(const E *__restrict__ X, const E *__restrict__ Wg,
+                                             const E *__restrict__ Wu, E *__restrict__ H, int T,
                                              int d_model, int ldh, const uint8_t *__restrict__ route,
                                              const BranchTable &bt, char *lds, int tm, int n0, int n_end)
 {
@@ -495,7 +641,7 @@ __device__ __forceinline__ void gate_up_tile(const uint16_t *__restrict__ X, con
             accu[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
 
-    const int nk = (d_model + BK - 1) / BK;
+    const int nk = (d_model + Elem<E>::BK - 1) / Elem<E>::BK;
     mainloop<BMT, WM, NB, D, kStaged, true>(X + (size_t)t0 * d_model, d_model, T - t0, Wg + (size_t)n0 * d_model,
                        Wu + (size_t)n0 * d_model, d_model, n_end - n0, n_end - n0, KSingle{d_model}, 0, nk,
                        lds, accg, accu);
@@ -503,11 +649,13 @@ __device__ __forceinline__ void gate_up_tile(const uint16_t *__restrict__ X, con
     // alpha of the tile's neurons -> LDS (the main loop is done with it)
     float *al = reinterpret_cast<float *>(lds);
     int *bl = reinterpret_cast<int *>(lds + BNH_MAX * sizeof(float));      // branch of each neuron (routing)
+    int *on = reinterpret_cast<int *>(lds + 2 * BNH_MAX * sizeof(float));  // neuron in an active branch (kEdges)
     if (threadIdx.x < BNH) {
         const int n = n0 + threadIdx.x;
         const int b = branch_of(bt, n < n_end ? n : n_end - 1);
         al[threadIdx.x] = n < n_end ? bt.alpha[b] : 0.f;
         if (kRouted) bl[threadIdx.x] = b;
+        if (kEdges) on[threadIdx.x] = n < n_end && ((bt.active >> b) & 1ULL) ? 1 : 0;
     }
     __syncthreads();
 
@@ -520,20 +668,24 @@ __device__ __forceinline__ void gate_up_tile(const uint16_t *__restrict__ X, con
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
             const int nl = wn * (16 * NB) + j * 16 + 4 * q4;   // first of 4 neurons, tile relative
-            // run ends are multiples of 8: the four neurons are all inside the run or all outside
+            // run ends are multiples of a chunk (rounded outwards with kEdges): the four are all inside or all outside
             if (t < T && n0 + nl < n_end) {
                 const f32x4 a4 = *reinterpret_cast<const f32x4 *>(al + nl);
-                uint16_t h[4];
+                f32x4 h;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    float v = a4[q] * silu_mul(accg[i][j][q], accu[i][j][q]);
-                    if (kRouted) v = route[(size_t)t * bt.B + bl[nl + q]] ? v : 0.f;
-                    h[q] = to_bf16(v);
+                    h[q] = gated(a4[q], accg[i][j][q], accu[i][j][q], E{});
+                    if (kRouted) h[q] = route[(size_t)t * bt.B + bl[nl + q]] ? h[q] : 0.f;
                 }
-                u32x2 pk;
-                pk.x = (uint32_t)h[0] | ((uint32_t)h[1] << 16);
-                pk.y = (uint32_t)h[2] | ((uint32_t)h[3] << 16);
-                *reinterpret_cast<u32x2 *>(H + (size_t)t * ldh + n0 + nl) = pk;
+                E *dst = H + (size_t)t * ldh + n0 + nl;
+                if (kEdges && !(on[nl] & on[nl + 1] & on[nl + 2] & on[nl + 3])) {
+                    // the columns of inactive branches are never written
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (on[nl + q]) store1(dst + q, h[q]);
+                } else {
+                    store4(dst, h);
+                }
             }
         }
     }
@@ -545,10 +697,10 @@ __device__ __forceinline__ void gate_up_tile(const uint16_t *__restrict__ X, con
 // over the full grid (one contiguous stretch of the list per XCD), the ids left over exit.  The
 // down projection skips the same (token tile, branch) pairs, and H is multiplied by the token's
 // route bit, so that it is exactly 0 where a token does not take a branch.
-template <int BMT, int WM, int NB, int D, bool kStaged, bool kRouted>
+template <int BMT, int WM, int NB, int D, bool kStaged, bool kRouted, bool kEdges, typename E>
 __global__ void __launch_bounds__(WM * 128)
-gate_up_mfma(const uint16_t *__restrict__ X, const uint16_t *__restrict__ Wg,
-             const uint16_t *__restrict__ Wu, uint16_t *__restrict__ H, int T, int d_model, int d_inter,
+gate_up_mfma(const E *__restrict__ X, const E *__restrict__ Wg,
+             const E *__restrict__ Wu, E *__restrict__ H, int T, int d_model, int d_inter,
              int ldh, int tiles_m, int tiles_n, const uint8_t *__restrict__ route, RouteTiles rt,
              BranchTable bt)
 {
@@ -580,7 +732,7 @@ gate_up_mfma(const uint16_t *__restrict__ X, const uint16_t *__restrict__ Wg,
     }
     int n0, n_end;
     if (!neuron_tile(bt, tn, BNH, n0, n_end)) return;
-    gate_up_tile<BMT, WM, NB, D, kStaged, kRouted>(X, Wg, Wu, H, T, d_model, ldh, route, bt, lds, tm, n0, n_end);
+    gate_up_tile<BMT, WM, NB, D, kStaged, kRouted, kEdges>(X, Wg, Wu, H, T, d_model, ldh, route, bt, lds, tm, n0, n_end);
 }
 
 // The gate+up projection with WIDE tiles for the full rounds of 256 workgroups and smaller tiles for what
@@ -638,12 +790,15 @@ gate_up_mfma_mixed(const uint16_t *__restrict__ X, const uint16_t *__restrict__ 
 // rounded once (RNE).
 // kRouted: the K loop of token tile tm walks only the branches some token of the tile is routed
 // to (tile_need); H is 0 for the tokens of the tile that do not take a branch.
-template <int BMT, int WM, int NB, int D, bool kStaged, bool kRouted>
+// kEdges: bt holds the runs rounded inwards (kRouted: the table's own runs; the ranges of a tile are rounded here)
+// and `edges` (static tables) the partial chunks, which the last K split adds.
+template <int BMT, int WM, int NB, int D, bool kStaged, bool kRouted, bool kEdges, typename E>
 __global__ void __launch_bounds__(WM * 128)
-down_mfma(const uint16_t *__restrict__ H, const uint16_t *__restrict__ Wd, float *__restrict__ dst, int T,
+down_mfma(const E *__restrict__ H, const E *__restrict__ Wd, float *__restrict__ dst, int T,
           int d_model, int d_inter, int ldh, int tiles_m, int tiles_n, int splits, int kt_total, int dst_mode,
-          const uint8_t *__restrict__ tile_need, BranchTable bt)
+          const uint8_t *__restrict__ tile_need, BranchTable bt, std::conditional_t<kEdges && !kRouted, EdgeList, NoEdges> edges)
 {
+    constexpr int BKE = Elem<E>::BK, CHUNK = Elem<E>::CHUNK;
     static_assert(!kRouted || BMT == BM, "the routed path's tables are per 256 tokens");
     __shared__ __attribute__((aligned(1024))) char lds[lds_bytes(BMT, NB, D, kStaged)];
     // Work items are (split, tile in the grouped order), split slowest, and every XCD takes one contiguous
@@ -659,11 +814,12 @@ down_mfma(const uint16_t *__restrict__ H, const uint16_t *__restrict__ Wd, float
     tile_from_logical((int)(item % tiles), tiles_m, tiles_n, tm, tn);
     constexpr int BNH = 32 * NB;                  // output features per B block; a tile has two
     const int t0 = tm * BMT, n0 = tn * (2 * BNH);
-    KRunsLanes dyn{0, 0, 0};
+    KRunsLanes dyn{0, 0, 0}, raw{0, 0, 0};
     if (kRouted) {
-        dyn = routed_runs(bt, tile_need + (size_t)tm * bt.B);
+        raw = dyn = routed_runs(bt, tile_need + (size_t)tm * bt.B);
+        if (kEdges) dyn = inner_runs<CHUNK>(raw);
         kt_total = 0;
-        for (int r = 0; r < dyn.n; ++r) kt_total += (dyn.end(r) - dyn.start(r) + BK - 1) / BK;
+        for (int r = 0; r < dyn.n; ++r) kt_total += (dyn.end(r) - dyn.start(r) + BKE - 1) / BKE;
     }
     const int kt_begin = (int)((long long)kt_total * z / splits);
     const int kt_end = (int)((long long)kt_total * (z + 1) / splits);
@@ -688,6 +844,22 @@ down_mfma(const uint16_t *__restrict__ H, const uint16_t *__restrict__ Wd, float
         mainloop<BMT, WM, NB, D, kStaged, true>(H + (size_t)t0 * ldh, ldh, T - t0, Wd + (size_t)n0 * d_inter,
                                     Wd + (size_t)n1 * d_inter, d_inter, d_model - n0, d_model - n1, KRuns{bt},
                                     kt_begin, kt_end, lds, acc0, acc1);
+    if constexpr (kEdges) {
+        const auto edge_at = [&](int i, int &col, unsigned &mask) {
+            if constexpr (kRouted) {
+                run_edge<CHUNK>(__shfl(raw.v_start, i >> 1), __shfl(raw.v_end, i >> 1), i & 1, col, mask);
+            } else {
+                col = edges.col[i];
+                mask = edges.mask[i];
+            }
+        };
+        int n_edges;
+        if constexpr (kRouted) n_edges = 2 * raw.n;
+        else n_edges = edges.n;
+        if (z == splits - 1)
+            edge_steps<MI, NB>(n_edges, edge_at, H + (size_t)t0 * ldh, ldh, T - t0, Wd + (size_t)n0 * d_inter,
+                               Wd + (size_t)n1 * d_inter, d_inter, d_model - n0, d_model - n1, acc0, acc1);
+    }
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave >> 1, wn = wave & 1;
@@ -701,17 +873,13 @@ down_mfma(const uint16_t *__restrict__ H, const uint16_t *__restrict__ Wd, float
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
                 const int m = n0 + half * BNH + wn * (16 * NB) + j * 16 + 4 * q4;
-                // d_model is a multiple of 8: the four features are all inside or all outside
+                // d_model is a multiple of a chunk (4 or 8): the four features are all inside or all outside
                 if (t < T && m < d_model) {
                     const f32x4 v = half ? acc1[i][j] : acc0[i][j];
-                    if (dst_mode == DST_BF16) {
-                        u32x2 pk;
-                        pk.x = (uint32_t)to_bf16(v[0]) | ((uint32_t)to_bf16(v[1]) << 16);
-                        pk.y = (uint32_t)to_bf16(v[2]) | ((uint32_t)to_bf16(v[3]) << 16);
-                        *reinterpret_cast<u32x2 *>(reinterpret_cast<uint16_t *>(dst) + (size_t)t * d_model + m) = pk;
-                    } else {
-                        *reinterpret_cast<f32x4 *>(o + (size_t)t * d_model + m) = v;
-                    }
+                    if (dst_mode == DST_BF16)
+                        store4(reinterpret_cast<uint16_t *>(dst) + (size_t)t * d_model + m, v);
+                    else
+                        store4(o + (size_t)t * d_model + m, v);
                 }
             }
     }
@@ -850,7 +1018,7 @@ route_tile_list(const uint8_t *__restrict__ route, uint8_t *__restrict__ tile_ne
 }
 
 // out[i] = sum_z partial[z][i], summed in z order: deterministic.  out_bf16: out holds bf16 values.
-// n4 = pieces of four values (T * d_model is a multiple of 8 on this path; partial is 256-byte, out 16-byte
+// n4 = pieces of four values (T * d_model is a multiple of 4 on this path; partial is 256-byte, out 16-byte
 // aligned).  Two pieces per thread and trip, so that 2 * splits loads are in flight per thread.
 __global__ void __launch_bounds__(256)
 reduce_partials(const float *__restrict__ partial, float *__restrict__ out, size_t n4, int splits, int out_bf16)
@@ -886,11 +1054,49 @@ reduce_partials(const float *__restrict__ partial, float *__restrict__ out, size
     }
 }
 
-int k_tiles(const BranchTable &bt)
+int k_tiles(const BranchTable &bt, int bk = BK)
 {
     int n = 0;
-    for (int r = 0; r < bt.n_runs; ++r) n += ceil_div(bt.run_end[r] - bt.run_start[r], BK);
+    for (int r = 0; r < bt.n_runs; ++r) n += ceil_div(bt.run_end[r] - bt.run_start[r], bk);
     return n;
+}
+
+// The run lists of a table whose boundaries are not multiples of `chunk`: rounded outwards without overlap (gate+up),
+// rounded inwards without empty ones (down), and the partial chunks.  outer / inner keep everything else of bt.
+struct UnevenRuns {
+    BranchTable outer, inner;
+    EdgeList edges;
+};
+template <int CHUNK>
+void uneven_runs(const BranchTable &bt, UnevenRuns &u)
+{
+    u.outer = u.inner = bt;
+    u.outer.n_runs = u.inner.n_runs = u.edges.n = 0;
+    for (int r = 0; r < bt.n_runs; ++r) {
+        const int s = bt.run_start[r], e = bt.run_end[r];
+        const int os = s / CHUNK * CHUNK;
+        const int oe = (e + CHUNK - 1) / CHUNK * CHUNK;
+        BranchTable &o = u.outer;
+        if (o.n_runs > 0 && os <= o.run_end[o.n_runs - 1]) {
+            o.run_end[o.n_runs - 1] = oe;             // shares a chunk with the run before it, or touches it
+        } else {
+            o.run_start[o.n_runs] = os;
+            o.run_end[o.n_runs++] = oe;
+        }
+        const int is = (s + CHUNK - 1) / CHUNK * CHUNK, ie = e / CHUNK * CHUNK;
+        if (ie > is) {
+            u.inner.run_start[u.inner.n_runs] = is;
+            u.inner.run_end[u.inner.n_runs++] = ie;
+        }
+        for (int side = 0; side < 2; ++side) {
+            int col;
+            unsigned mask;
+            run_edge<CHUNK>(s, e, side, col, mask);
+            if (!mask) continue;
+            u.edges.col[u.edges.n] = col;
+            u.edges.mask[u.edges.n++] = (uint8_t)mask;
+        }
+    }
 }
 
 // Tile shapes.  WIDE: 256 tokens x (128 + 128) rows of B, the shape with the most reuse per byte moved
@@ -1071,7 +1277,7 @@ size_t mfma_partial_bytes(int T, int d_model, int d_inter)
     return s > 1 ? align_up((size_t)s * T * d_model * sizeof(float), 256) : 0;
 }
 
-template <typename S, bool kRouted = false>
+template <typename S, bool kRouted = false, bool kEdges = false, typename E = uint16_t>
 static hipError_t launch_gate_up(const FwdArgs &a, const BranchTable &bt)
 {
     constexpr int BMT = S::BMT, WM = S::WM, NB = S::NB;
@@ -1099,9 +1305,8 @@ static hipError_t launch_gate_up(const FwdArgs &a, const BranchTable &bt)
         rt = RouteTiles{need, counts, list, stride};
     }
     ProfileScope ps(MLPMOE_KERNEL_GATE_UP_MFMA, a.stream);
-    gate_up_mfma<BMT, WM, NB, S::D, S::kStaged, kRouted><<<(unsigned)grid, WM * 128, 0, a.stream>>>(
-        static_cast<const uint16_t *>(a.x), static_cast<const uint16_t *>(a.Wg),
-        static_cast<const uint16_t *>(a.Wu), static_cast<uint16_t *>(a.H), a.T, a.d_model, a.d_inter,
+    gate_up_mfma<BMT, WM, NB, S::D, S::kStaged, kRouted, kEdges><<<(unsigned)grid, WM * 128, 0, a.stream>>>(
+        static_cast<const E *>(a.x), static_cast<const E *>(a.Wg), static_cast<const E *>(a.Wu), static_cast<E *>(a.H), a.T, a.d_model, a.d_inter,
         a.ldh, tiles_m, (int)tiles_n, a.route, rt, bt);
     return launch_status("gate_up_mfma launch");
 }
@@ -1125,72 +1330,106 @@ static hipError_t launch_gate_up_mixed(const FwdArgs &a, const BranchTable &bt)
     return launch_status("gate_up_mfma_mixed launch");
 }
 
-template <typename S, bool kRouted = false>
-static hipError_t launch_down(const FwdArgs &a, const BranchTable &bt, int splits)
+// bt: the K ranges (kEdges without routing: the inner runs, with their edges)
+template <typename S, bool kRouted = false, bool kEdges = false, typename E = uint16_t>
+static hipError_t launch_down(const FwdArgs &a, const BranchTable &bt, int splits,
+                              const std::conditional_t<kEdges && !kRouted, EdgeList, NoEdges> &edges)
 {
     constexpr int BMT = S::BMT, WM = S::WM, NB = S::NB;
     const int tiles_m = ceil_div(a.T, BMT);
     const int tiles_n = ceil_div(a.d_model, 64 * NB);
-    const int kt_total = k_tiles(bt);
+    const int kt_total = k_tiles(bt, Elem<E>::BK);
     const long long grid = (long long)XCDS * ids_per_xcd((long long)tiles_m * tiles_n * splits);
     if (grid > 0x7fffffffLL) return note_hip_error("down_mfma grid", hipErrorInvalidValue);
     ProfileScope ps(MLPMOE_KERNEL_DOWN_MFMA, a.stream);
-    down_mfma<BMT, WM, NB, S::D, S::kStaged, kRouted><<<(unsigned)grid, WM * 128, 0, a.stream>>>(
-        static_cast<const uint16_t *>(a.H), static_cast<const uint16_t *>(a.Wd),
+    down_mfma<BMT, WM, NB, S::D, S::kStaged, kRouted, kEdges><<<(unsigned)grid, WM * 128, 0, a.stream>>>(
+        static_cast<const E *>(a.H), static_cast<const E *>(a.Wd),
         splits > 1 ? a.partial : a.out, a.T, a.d_model, a.d_inter, a.ldh, tiles_m, tiles_n, splits, kt_total,
-        (a.out_bf16 && splits == 1) ? DST_BF16 : DST_F32, a.route_scratch, bt);
+        (a.out_bf16 && splits == 1) ? DST_BF16 : DST_F32, a.route_scratch, bt, edges);
     return launch_status("down_mfma launch");
 }
 
-// The down projection as planned, then the sum of the partial results if K was split through the workspace.
-template <bool kRouted>
-static hipError_t down_and_reduce(const FwdArgs &a, const BranchTable &bt, const DownPlan &pl)
+// Adds up the partial results of a K split.
+static hipError_t reduce_splits(const FwdArgs &a, int splits)
 {
-    hipError_t e;
-    if (pl.shape == TILE_WIDE) e = launch_down<ShapeWide, kRouted>(a, bt, pl.splits);
-    else if (pl.shape == TILE_NARROW) e = launch_down<ShapeNarrow, kRouted>(a, bt, pl.splits);
-    else if (kRouted) e = hipErrorInvalidValue;
-    else if (pl.shape == TILE_SMALL) e = launch_down<ShapeSmall>(a, bt, pl.splits);
-    else if (pl.shape == TILE_DEEP) e = launch_down<ShapeDeep>(a, bt, pl.splits);
-    else e = launch_down<ShapeSlim>(a, bt, pl.splits);
-    if (e != hipSuccess) return hipErrorLaunchFailure;
-    if (pl.splits > 1) {
-        ProfileScope ps(MLPMOE_KERNEL_SPLITK_REDUCE, a.stream);
-        const size_t n4 = (size_t)a.T * a.d_model / 4;
-        size_t blocks = (n4 + 511) / 512;
-        if (blocks > 4096) blocks = 4096;
-        reduce_partials<<<(unsigned)blocks, 256, 0, a.stream>>>(a.partial, a.out, n4, pl.splits, a.out_bf16 ? 1 : 0);
-    }
+    if (splits < 2) return hipSuccess;
+    ProfileScope ps(MLPMOE_KERNEL_SPLITK_REDUCE, a.stream);
+    const size_t n4 = (size_t)a.T * a.d_model / 4;
+    size_t blocks = (n4 + 511) / 512;
+    if (blocks > 4096) blocks = 4096;
+    reduce_partials<<<(unsigned)blocks, 256, 0, a.stream>>>(a.partial, a.out, n4, splits, a.out_bf16 ? 1 : 0);
     return launch_status("reduce_partials launch");
+}
+
+// The down projection as planned, then the sum of the partial results if K was split through the workspace.
+template <bool kRouted, bool kEdges, typename Ed>
+static hipError_t down_and_reduce(const FwdArgs &a, const BranchTable &bt, const DownPlan &pl, const Ed &edges)
+{
+    hipError_t e = hipErrorInvalidValue;
+    if (pl.shape == TILE_WIDE) e = launch_down<ShapeWide, kRouted, kEdges>(a, bt, pl.splits, edges);
+    else if (pl.shape == TILE_NARROW) e = launch_down<ShapeNarrow, kRouted, kEdges>(a, bt, pl.splits, edges);
+    if constexpr (!kRouted) {
+        if (pl.shape == TILE_SMALL) e = launch_down<ShapeSmall, false, kEdges>(a, bt, pl.splits, edges);
+        else if (pl.shape == TILE_DEEP) e = launch_down<ShapeDeep, false, kEdges>(a, bt, pl.splits, edges);
+        else if (pl.shape == TILE_SLIM) e = launch_down<ShapeSlim, false, kEdges>(a, bt, pl.splits, edges);
+    }
+    if (e != hipSuccess) return hipErrorLaunchFailure;
+    return reduce_splits(a, pl.splits);
 }
 
 // Per-token routing on the MFMA kernels (wide tiles: how many tiles are live is known only on the
 // device).  a.route_scratch is route_scratch_bytes(T, d_inter) bytes, 256-byte aligned.
-hipError_t launch_mfma_routed_bf16(const FwdArgs &a, const BranchTable &bt)
+// uneven: a branch boundary is not a multiple of 8; d_model and d_inter are.
+hipError_t launch_mfma_routed_bf16(const FwdArgs &a, const BranchTable &bt, bool uneven)
 {
-    hipError_t e = launch_gate_up<ShapeWide, true>(a, bt);
+    hipError_t e;
+    if (uneven) {
+        UnevenRuns u;
+        uneven_runs<Elem<uint16_t>::CHUNK>(bt, u);
+        e = launch_gate_up<ShapeWide, true, true>(a, u.outer);
+    } else {
+        e = launch_gate_up<ShapeWide, true>(a, bt);
+    }
     if (e != hipSuccess) return hipErrorLaunchFailure;
     // 256-token tiles (the routing tables are per 256 tokens); narrow when K is split: half the partial sums
     int splits = down_splits(a.T, a.d_model, bt.d_eff, TILE_WIDE);
     const TileShape sh = splits > 1 ? TILE_NARROW : TILE_WIDE;
     splits = std::min(down_splits(a.T, a.d_model, bt.d_eff, sh), std::max(1, k_tiles(bt)));
     if (splits > 1 && (size_t)splits * a.T * a.d_model * sizeof(float) > a.partial_bytes) splits = 1;
-    return down_and_reduce<true>(a, bt, DownPlan{sh, splits});
+    return uneven ? down_and_reduce<true, true>(a, bt, DownPlan{sh, splits}, NoEdges{})
+                  : down_and_reduce<true, false>(a, bt, DownPlan{sh, splits}, NoEdges{});
 }
 
-hipError_t launch_mfma_bf16(const FwdArgs &a, const BranchTable &bt)
+template <bool kEdges>
+static hipError_t launch_gate_up_shape(const FwdArgs &a, const BranchTable &bt, TileShape sh)
 {
-    const DownPlan pl = plan_down(a, bt, false);
+    switch (sh) {
+    case TILE_WIDE: return launch_gate_up<ShapeWide, false, kEdges>(a, bt);
+    case TILE_NARROW: return launch_gate_up<ShapeNarrow, false, kEdges>(a, bt);
+    case TILE_SMALL: return launch_gate_up<ShapeSmall, false, kEdges>(a, bt);
+    case TILE_DEEP: return launch_gate_up<ShapeDeep, false, kEdges>(a, bt);
+    case TILE_SLIM: return launch_gate_up<ShapeSlim, false, kEdges>(a, bt);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+// uneven: a run boundary is not a multiple of 8 (first-K pruning or branches switched off where B does not divide
+// the width); d_model and d_inter are.
+hipError_t launch_mfma_bf16(const FwdArgs &a, const BranchTable &bt, bool uneven)
+{
+    if (uneven) {
+        UnevenRuns u;
+        uneven_runs<Elem<uint16_t>::CHUNK>(bt, u);
+        TileShape gu = pick_gate_up_tile(u.outer, a.T, a.d_model);
+        if (gu == TILE_MIXED) gu = TILE_WIDE;
+        if (launch_gate_up_shape<true>(a, u.outer, gu) != hipSuccess) return hipErrorLaunchFailure;
+        return down_and_reduce<false, true>(a, u.inner, plan_down(a, u.inner, false), u.edges);
+    }
     TileShape gu = a.tile_shape >= 0 ? (TileShape)a.tile_shape : pick_gate_up_tile(bt, a.T, a.d_model);
     if (gu == TILE_MIXED && mixed_wide_per_xcd(gate_up_tiles(bt, a.T, TILE_WIDE)) < 0) gu = TILE_WIDE;   // forced where it does not apply
-    hipError_t e = gu == TILE_WIDE     ? launch_gate_up<ShapeWide>(a, bt)
-                   : gu == TILE_NARROW ? launch_gate_up<ShapeNarrow>(a, bt)
-                   : gu == TILE_SMALL  ? launch_gate_up<ShapeSmall>(a, bt)
-                   : gu == TILE_DEEP   ? launch_gate_up<ShapeDeep>(a, bt)
-                   : gu == TILE_SLIM   ? launch_gate_up<ShapeSlim>(a, bt)
-                                       : launch_gate_up_mixed(a, bt);
+    const hipError_t e = gu == TILE_MIXED ? launch_gate_up_mixed(a, bt) : launch_gate_up_shape<false>(a, bt, gu);
     if (e != hipSuccess) return hipErrorLaunchFailure;
-    return down_and_reduce<false>(a, bt, pl);
+    return down_and_reduce<false, false>(a, bt, plan_down(a, bt, false), NoEdges{});
 }
 
 }  // namespace mlpmoe
