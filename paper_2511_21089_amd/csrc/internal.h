@@ -77,11 +77,13 @@ inline int h_ld(int d_inter) { return (int)align_up((size_t)(d_inter > 0 ? d_int
 // Split-K factor of the MFMA down projection for an output of T x d_model and kt K-tiles.
 int mfma_down_splits(int T, int d_model, int k_elems);
 size_t mfma_partial_bytes(int T, int d_model, int d_inter);
+size_t mfma_partial_bytes_f32(int T, int d_model, int d_inter);
 
 hipError_t launch_fill_zero(float *out, size_t n, hipStream_t s);
 hipError_t launch_fill_zero16(uint16_t *out, size_t n, hipStream_t s);
 hipError_t launch_generic(const FwdArgs &a, const BranchTable &bt, bool is_bf16);
 hipError_t launch_mfma_bf16(const FwdArgs &a, const BranchTable &bt, bool uneven);
+hipError_t launch_mfma_f32(const FwdArgs &a, const BranchTable &bt);
 size_t route_scratch_bytes(int T, int d_inter);
 hipError_t launch_mfma_routed_bf16(const FwdArgs &a, const BranchTable &bt, bool uneven);
 hipError_t launch_decode_bf16(const FwdArgs &a, const BranchTable &bt);

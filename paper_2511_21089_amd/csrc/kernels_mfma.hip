@@ -1128,6 +1128,13 @@ using ShapeNarrow = ShapeT<BM, MFMA_WM, 2, 2, false>;
 using ShapeSmall = ShapeT<BM_SMALL, SMALL_WM, 2, 2, false>;
 using ShapeDeep = ShapeT<BM_SMALL, SMALL_WM, 2, DEEP_D, false>;
 using ShapeSlim = ShapeT<BM_SLIM, SLIM_WM, 2, SLIM_D, true>;
+// Float storage: 64 tokens x (32 + 32), 4 waves of 32 x (16 + 16) outputs, 40 KiB, four workgroups per CU.  Bound: the
+// float MFMA rate (v_mfma_f32_16x16x4_f32, 256 flop per clock and CU, a sixteenth of bf16's), which this small a tile
+// already reaches: it asks the L2 for 16 bytes per clock and CU while the matrix pipe is busy, of about 40 available,
+// and small tiles fill the chip at the sizes float storage is used for (4864 neurons and 256 tokens are 608 tiles; the
+// 128 x (64 + 64) tile would make 152).  The layer at T = 256: 87 us against 1008 us on the general FMA kernels, error
+// against float64 1.0e-6 against 1.5e-6 (rel.).
+using ShapeF32 = ShapeT<64, 2, 1, 2, false>;
 struct TileDims {
     int bm, bn;       // tokens, B rows per block (a tile has two blocks)
     int per_cu;       // workgroups resident per CU
@@ -1398,6 +1405,54 @@ hipError_t launch_mfma_routed_bf16(const FwdArgs &a, const BranchTable &bt, bool
     if (splits > 1 && (size_t)splits * a.T * a.d_model * sizeof(float) > a.partial_bytes) splits = 1;
     return uneven ? down_and_reduce<true, true>(a, bt, DownPlan{sh, splits}, NoEdges{})
                   : down_and_reduce<true, false>(a, bt, DownPlan{sh, splits}, NoEdges{});
+}
+
+// Float storage.  K split of the down projection: the factor with the shortest estimate, a K tile of 32 floats taking a
+// workgroup 0.43 us of matrix pipe (workgroups that share a CU take turns), about 2 us for its first loads and its
+// stores, and the separate sum about 4 us plus its traffic.  Depends on T through whole token tiles only.
+static int f32_down_splits(int T, int d_model, int kt)
+{
+    const long long tiles_m = ceil_div(T, ShapeF32::BMT), tiles = tiles_m * ceil_div(d_model, 64 * ShapeF32::NB);
+    int best = 1;
+    double best_us = 1e30;
+    for (int s = 1; s <= 16 && s <= std::max(1, kt / 4); ++s) {
+        double us = (double)((tiles * s + kCUs - 1) / kCUs) * (ceil_div(kt, s) * 0.43 + 2.0);
+        if (s > 1) us += 4.0 + (s + 1.0) * (double)(tiles_m * ShapeF32::BMT) * d_model * 4.0 / 5e6;
+        if (us < best_us) {
+            best = s;
+            best_us = us;
+        }
+    }
+    return best;
+}
+
+size_t mfma_partial_bytes_f32(int T, int d_model, int d_inter)
+{
+    const int s = f32_down_splits(T, d_model, ceil_div(d_inter, Elem<float>::BK));
+    return s > 1 ? align_up((size_t)s * T * d_model * sizeof(float), 256) : 0;
+}
+
+template <bool kEdges, typename Ed>
+static hipError_t launch_mfma_f32_runs(const FwdArgs &a, const BranchTable &outer, const BranchTable &inner, const Ed &edges)
+{
+    if (launch_gate_up<ShapeF32, false, kEdges, float>(a, outer) != hipSuccess) return hipErrorLaunchFailure;
+    // a workspace without room for all partial sums gets as many as fit
+    const long long fit = (long long)(a.partial_bytes / ((size_t)a.T * a.d_model * sizeof(float)));
+    int splits = f32_down_splits(a.T, a.d_model, k_tiles(inner, Elem<float>::BK));
+    if (splits > fit) splits = fit < 1 ? 1 : (int)fit;
+    if (launch_down<ShapeF32, false, kEdges, float>(a, inner, splits, edges) != hipSuccess) return hipErrorLaunchFailure;
+    return reduce_splits(a, splits);
+}
+
+// d_model and d_inter are multiples of 4.
+hipError_t launch_mfma_f32(const FwdArgs &a, const BranchTable &bt)
+{
+    UnevenRuns u;
+    uneven_runs<Elem<float>::CHUNK>(bt, u);
+    bool even = true;
+    for (int r = 0; r < bt.n_runs; ++r)
+        even = even && bt.run_start[r] % Elem<float>::CHUNK == 0 && bt.run_end[r] % Elem<float>::CHUNK == 0;
+    return even ? launch_mfma_f32_runs<false>(a, bt, bt, NoEdges{}) : launch_mfma_f32_runs<true>(a, u.outer, u.inner, u.edges);
 }
 
 template <bool kEdges>

@@ -105,6 +105,14 @@ size_t h_bytes(int T, int d_inter, int elem_bytes)
     return align_up((size_t)T * (size_t)h_ld(d_inter) * (size_t)elem_bytes, 256);
 }
 
+// The least workspace a call runs in.  Float storage only gains speed from the partial sums of a K split: a block
+// without room for them is accepted.
+size_t min_workspace_bytes(int T, int d_model, int d_inter, int B, int elem)
+{
+    const size_t full = mlpmoe_workspace_bytes(T, d_model, d_inter, B, elem);
+    return elem == 4 && full > 0 && T > 0 ? full - mfma_partial_bytes_f32(T, d_model, d_inter) : full;
+}
+
 // Dispatch with a ready branch table: path choice, workspace carving, launch.  No loops over
 // branches, no allocation, no synchronisation.
 // route: per-token routing [T, B] on the device, or nullptr.  Routed calls use the kernels that skip
@@ -148,7 +156,8 @@ int forward_table(const BranchTable &bt, bool aligned, const void *x, const void
     if (path == MLPMOE_PATH_DECODE && T > 16) return MLPMOE_ERR_UNSUPPORTED;
 
     const int elem = is_bf16 ? 2 : 4;
-    const size_t need = mlpmoe_workspace_bytes(T, d_model, d_inter, bt.B, elem);
+    size_t need = mlpmoe_workspace_bytes(T, d_model, d_inter, bt.B, elem);
+    if (workspace_bytes < need) need = min_workspace_bytes(T, d_model, d_inter, bt.B, elem);
     if (!workspace || workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 255u))
         return MLPMOE_ERR_WORKSPACE;
 
@@ -168,7 +177,12 @@ int forward_table(const BranchTable &bt, bool aligned, const void *x, const void
     a.route_scratch = reinterpret_cast<uint8_t *>(static_cast<char *>(workspace) + need - route_scratch_bytes(T, d_inter));
 
     hipError_t e;
-    if (path == MLPMOE_PATH_GENERIC) {
+    // Float storage takes the float MFMA kernels where rows are whole 16-byte pieces (256 tokens on 896 x 4864: 87 us
+    // against 1008 us on the generic kernels); routed calls, other row lengths and more token rows than the generic
+    // kernels' grid holds (an error there) stay where they were.
+    if (!is_bf16 && !route && d_model % 4 == 0 && d_inter % 4 == 0 && T <= 65535 * 64) {
+        e = launch_mfma_f32(a, bt);
+    } else if (path == MLPMOE_PATH_GENERIC) {
         e = launch_generic(a, bt, is_bf16);
     } else if (route) {
         e = path == MLPMOE_PATH_MFMA ? launch_mfma_routed_bf16(a, bt, uneven) : launch_decode_routed_bf16(a, bt);
@@ -199,7 +213,8 @@ int forward_impl(const void *x, const void *Wg, const void *Wu, const void *Wd, 
 
 // Workspace of the current device for the entry points that take none: the caller's block if one
 // was set, else the library-owned one, grown on demand.  g_ws_mutex must be held by the caller.
-int owned_workspace(size_t need, hipStream_t stream, void **ptr, size_t *bytes)
+// need: what the call asks for; a block that cannot grow (the caller's, or during a capture) only has to hold least.
+int owned_workspace(size_t need, size_t least, hipStream_t stream, void **ptr, size_t *bytes)
 {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -209,7 +224,7 @@ int owned_workspace(size_t need, hipStream_t stream, void **ptr, size_t *bytes)
     }
     DeviceWorkspace &w = g_ws[dev];
     if (w.user_ptr) {                        // caller-owned: use it or refuse, never allocate
-        if (w.user_bytes < need) return MLPMOE_ERR_WORKSPACE;
+        if (w.user_bytes < least) return MLPMOE_ERR_WORKSPACE;
         *ptr = w.user_ptr;
         *bytes = w.user_bytes;
         return MLPMOE_OK;
@@ -218,7 +233,12 @@ int owned_workspace(size_t need, hipStream_t stream, void **ptr, size_t *bytes)
         // growing synchronises the device and allocates: neither is allowed while the stream records a graph
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(stream, &cap) != hipSuccess) (void)hipGetLastError();
-        if (cap != hipStreamCaptureStatusNone) return MLPMOE_ERR_WORKSPACE;
+        if (cap != hipStreamCaptureStatusNone) {
+            if (!w.ptr || w.bytes < least) return MLPMOE_ERR_WORKSPACE;
+            *ptr = w.ptr;
+            *bytes = w.bytes;
+            return MLPMOE_OK;
+        }
         if (w.ptr) {
             e = hipDeviceSynchronize();      // earlier launches may still be using the old block
             if (e != hipSuccess) {
@@ -253,7 +273,7 @@ int forward_owned(const void *x, const void *Wg, const void *Wu, const void *Wd,
     void *ws = nullptr;
     size_t ws_bytes = 0;
     std::lock_guard<std::mutex> lock(g_ws_mutex);      // held until the kernels are enqueued
-    rc = owned_workspace(need, stream, &ws, &ws_bytes);
+    rc = owned_workspace(need, min_workspace_bytes(T, d_model, d_inter, B, is_bf16 ? 2 : 4), stream, &ws, &ws_bytes);
     if (rc != MLPMOE_OK) return rc;
     return forward_impl(x, Wg, Wu, Wd, off, alpha, mask, T, d_model, d_inter, B, out, ws, ws_bytes,
                         MLPMOE_PATH_AUTO, is_bf16, stream, out_bf16);
@@ -578,7 +598,7 @@ size_t mlpmoe_workspace_bytes(int T, int d_model, int d_inter, int B, int elem_b
         return 0;
     if (T == 0) return 256;
     size_t bytes = h_bytes(T, d_inter, elem_bytes);
-    if (elem_bytes == 2) bytes += mfma_partial_bytes(T, d_model, d_inter);
+    bytes += elem_bytes == 2 ? mfma_partial_bytes(T, d_model, d_inter) : mfma_partial_bytes_f32(T, d_model, d_inter);
     return bytes + 256 + route_scratch_bytes(T, d_inter);     // slack, then the routed path's tile tables
 }
 
@@ -696,8 +716,9 @@ static int forward_routed(const void *x, const void *Wg, const void *Wu, const v
     std::unique_lock<std::mutex> lock(g_ws_mutex, std::defer_lock);
     if (own) {
         lock.lock();                                   // held until the kernels are enqueued
-        rc = owned_workspace(mlpmoe_workspace_bytes(T, d_model, d_inter, B, is_bf16 ? 2 : 4), stream, &workspace,
-                             &workspace_bytes);
+        const int elem = is_bf16 ? 2 : 4;
+        rc = owned_workspace(mlpmoe_workspace_bytes(T, d_model, d_inter, B, elem),
+                             min_workspace_bytes(T, d_model, d_inter, B, elem), stream, &workspace, &workspace_bytes);
         if (rc != MLPMOE_OK) return rc;
     }
     BranchTable bt;

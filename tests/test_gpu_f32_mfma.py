@@ -1,0 +1,94 @@
+"""Float storage on the float MFMA kernels (d_model and d_inter multiples of 4): token and feature tails, K tails, runs
+that start and end inside a 16-byte chunk, the K split with and without room for its partial sums.  Against float64,
+with the error fp32 sums may have and non-finite weights in every pruned branch."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import C_SUM, U24, run_gpu
+from paper_2511_21089_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mm():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2511_21089_amd import binding
+    return binding
+
+
+TABLES = {
+    "even": ([64, 128, 36, 132], [1, 0, 1, 1]),
+    "all_on": ([101, 101, 101, 101], [1, 1, 1, 1]),
+    "first_k": ([101, 101, 101, 100, 101], [1, 1, 1, 0, 0]),
+    "first_off": ([101, 101, 101, 100, 101], [0, 1, 0, 1, 1]),
+    "one_chunk": ([1, 1, 1, 1, 9, 130, 5], [0, 1, 0, 1, 0, 1, 0]),
+    "no_interior": ([1, 3, 5, 3, 4, 1, 2, 1], [1, 0, 1, 0, 0, 0, 1, 1]),
+    "thin": ([1] * 64, [1, 0, 0] * 21 + [1]),
+    "tile_edges": ([31, 1, 33, 63, 65, 31], [1, 0, 1, 1, 0, 1]),
+}
+
+
+def make(widths, mask, T, d_model, seed):
+    off = np.concatenate([[0], np.cumsum(widths)]).astype(np.int32)
+    assert off[-1] % 4 == 0
+    rng = np.random.default_rng(seed)
+    x, Wg, Wu, Wd = synth.random_layer(rng, T, d_model, int(off[-1]), dtype="f32", w_scale=0.05)
+    alpha = rng.uniform(0.8, 1.25, size=len(widths)).astype(np.float32)
+    return x, Wg, Wu, Wd, off, alpha, np.array(mask, np.uint8)
+
+
+def poison_pruned(args):
+    x, Wg, Wu, Wd, off, alpha, mask = args
+    Wg, Wu, Wd = Wg.copy(), Wu.copy(), Wd.copy()
+    for b in np.flatnonzero(mask == 0):
+        Wg[off[b]:off[b + 1]] = np.nan
+        Wu[off[b]:off[b + 1]] = np.inf
+        Wd[:, off[b]:off[b + 1]] = -np.inf
+    return x, Wg, Wu, Wd, off, alpha, mask
+
+
+def check(got, x, Wg, Wu, Wd, off, alpha, mask):
+    h, g, u, ag, au = oracle.mlpmoe_hidden(x, Wg, Wu, off, alpha, mask, "exact", details=True)
+    a = np.repeat(alpha.astype(np.float64) * (mask != 0), np.diff(off))
+    sig = 1.0 / (1.0 + np.exp(-g))
+    # first-order error of h under the errors of its two fp32 sums, and a few fp32 roundings of h itself
+    eg, eu = C_SUM * U24 * ag, C_SUM * U24 * au
+    dh = np.abs(a) * (np.abs(sig * (1.0 + g * (1.0 - sig)) * u) * eg + np.abs(g * sig) * eu + eg * eu) + C_SUM * U24 * np.abs(h)
+    h = np.where(a != 0, h, 0.0)
+    dh = np.where(a != 0, dh, 0.0)
+    aWd = np.abs(Wd.astype(np.float64))
+    allow = dh @ aWd.T + C_SUM * U24 * (np.abs(h) @ aWd.T)
+    assert np.all(np.isfinite(got))
+    assert np.all(np.abs(got - h @ Wd.astype(np.float64).T) <= allow + 1e-30)
+
+
+@pytest.mark.parametrize("T,d_model", [(1, 68), (17, 4), (64, 96), (65, 132), (300, 64)])
+@pytest.mark.parametrize("name", sorted(TABLES))
+def test_f32_table(mm, name, T, d_model):
+    args = make(*TABLES[name], T, d_model, seed=T)
+    got = run_gpu(*poison_pruned(args))
+    check(got, *args)
+
+
+@pytest.mark.parametrize("T", [3, 130])
+def test_f32_split_k_and_small_workspace(mm, T):
+    import torch
+    args = make([1003, 1003, 1003, 1003], [1, 1, 0, 1], T, 64, seed=9)
+    bad = poison_pruned(args)
+    x, Wg, Wu, Wd, off, alpha, mask = bad
+    dev = [torch.from_numpy(a).cuda() for a in (x, Wg, Wu, Wd)]
+    full = mm.mlpmoe_workspace_bytes(T, 64, int(off[-1]), 4, 4)
+    hidden = (T * mm.mlpmoe_hidden_ld(int(off[-1])) * 4 + 255) // 256 * 256     # float, rows of mlpmoe_hidden_ld
+    # a byte short of the room for all partial sums: none are used
+    for n in (full, full - 1):
+        ws = torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda")
+        out = torch.full((T, 64), float("nan"), dtype=torch.float32, device="cuda")
+        mm.mlpmoe_forward_f32_ws(*dev, off, alpha, mask, ws, out=out)
+        torch.cuda.synchronize()
+        check(out.cpu().numpy(), *args)
+    with pytest.raises(mm.MlpMoeError) as ei:
+        mm.mlpmoe_forward_f32_ws(*dev, off, alpha, mask, ws[:hidden], out=out)
+    assert ei.value.status == mm.ERR_WORKSPACE
