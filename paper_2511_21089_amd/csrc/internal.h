@@ -43,11 +43,11 @@ struct FwdArgs {
 
 extern thread_local char g_err_detail[192];
 
-// Fractal Fade of one bf16 projection matrix (see kernels_fade.hip); synchronises the stream.
-hipError_t launch_fade_bf16(void *W, const int32_t *off, const double *sparsity, int B, int d_model,
-                            uint32_t *scratch, uint32_t *host_result, int *job_of_branch, hipStream_t s);
+// Fractal Fade of one or two bf16 projection matrices (see kernels_fade.hip); synchronises the stream.
+hipError_t launch_fade_bf16(void *const *W, int mats, const int32_t *off, const double *sparsity, int B, int d_model,
+                            uint32_t *scratch, uint32_t *host_result, int *job_of_branch, int *n_jobs, hipStream_t s);
 size_t fade_scratch_words(int B);
-// The same for a float matrix; thresholds / kept are per job (job_of_branch maps branches to jobs).
+// One float matrix; thresholds / kept are per job (job_of_branch maps branches to jobs).
 hipError_t launch_fade_f32(void *W, const int32_t *off, const double *sparsity, int B, int d_model,
                            uint32_t *scratch, double *thresholds, long long *kept, int *job_of_branch, hipStream_t s);
 size_t fade_scratch_words_f32(int B);

@@ -491,9 +491,9 @@ int mlpmoe_fade(void *W_gate, void *W_up, const int32_t *branch_offsets, const d
     }
     int rc = MLPMOE_OK;
     void *mats[2] = {W_gate, W_up};
-    for (int m = 0; m < 2 && rc == MLPMOE_OK; ++m) {
-        int job[MLPMOE_MAX_BRANCHES];
-        if (elem_bytes == 4) {
+    int job[MLPMOE_MAX_BRANCHES];
+    if (elem_bytes == 4) {
+        for (int m = 0; m < 2 && rc == MLPMOE_OK; ++m) {
             double thr[MLPMOE_MAX_BRANCHES];
             long long cnt[MLPMOE_MAX_BRANCHES];
             e = launch_fade_f32(mats[m], branch_offsets, sched, B, d_model, scratch, thr, cnt, job,
@@ -507,27 +507,36 @@ int mlpmoe_fade(void *W_gate, void *W_up, const int32_t *branch_offsets, const d
                 if (thresholds) thresholds[2 * b + m] = (float)thr[job[b]];
                 if (kept) kept[2 * b + m] = cnt[job[b]];
             }
-            continue;
         }
-        uint32_t res[4 * MLPMOE_MAX_BRANCHES];
-        e = launch_fade_bf16(mats[m], branch_offsets, sched, B, d_model, scratch, res, job,
-                             static_cast<hipStream_t>(stream));
-        if (e != hipSuccess) {
-            rc = MLPMOE_ERR_HIP;
-            break;
-        }
-        for (int b = 0; b < B; ++b) {
-            const int j = job[b];
-            if (j < 0) continue;
-            const long long n = (long long)(branch_offsets[b + 1] - branch_offsets[b]) * d_model;
-            const double p = sched[b] * (double)(n - 1);
-            const double frac = p - (double)(long long)p;
-            const uint32_t lo_bits = res[4 * j] << 16, hi_bits = res[4 * j + 1] << 16;
-            float lo, hi;
-            memcpy(&lo, &lo_bits, 4);
-            memcpy(&hi, &hi_bits, 4);
-            if (thresholds) thresholds[2 * b + m] = (float)((double)lo + frac * ((double)hi - (double)lo));
-            if (kept) kept[2 * b + m] = (long long)(((unsigned long long)res[4 * j + 3] << 32) | res[4 * j + 2]);
+    } else {
+        // both matrices at once, one after the other if they overlap in memory
+        const uintptr_t g0 = reinterpret_cast<uintptr_t>(W_gate), u0 = reinterpret_cast<uintptr_t>(W_up);
+        const size_t size = (size_t)d_inter * d_model * 2;
+        const int at_once = g0 < u0 + size && u0 < g0 + size ? 1 : 2;
+        uint32_t res[2 * 4 * MLPMOE_MAX_BRANCHES];
+        int n_jobs = 0;
+        for (int m = 0; m < 2 && rc == MLPMOE_OK; ++m) {
+            if (m % at_once == 0) {
+                e = launch_fade_bf16(mats + m, at_once, branch_offsets, sched, B, d_model, scratch, res, job, &n_jobs,
+                                     static_cast<hipStream_t>(stream));
+                if (e != hipSuccess) {
+                    rc = MLPMOE_ERR_HIP;
+                    break;
+                }
+            }
+            for (int b = 0; b < B; ++b) {
+                if (job[b] < 0) continue;
+                const uint32_t *r = res + 4 * ((m % at_once) * n_jobs + job[b]);
+                const long long n = (long long)(branch_offsets[b + 1] - branch_offsets[b]) * d_model;
+                const double p = sched[b] * (double)(n - 1);
+                const double frac = p - (double)(long long)p;
+                const uint32_t lo_bits = r[0] << 16, hi_bits = r[1] << 16;
+                float lo, hi;
+                memcpy(&lo, &lo_bits, 4);
+                memcpy(&hi, &hi_bits, 4);
+                if (thresholds) thresholds[2 * b + m] = (float)((double)lo + frac * ((double)hi - (double)lo));
+                if (kept) kept[2 * b + m] = (long long)(((unsigned long long)r[3] << 32) | r[2]);
+            }
         }
     }
     (void)hipFree(scratch);
