@@ -565,6 +565,7 @@ __device__ __forceinline__ void store4(float *p, f32x4 v) { *reinterpret_cast<f3
 // on an XCD form an 8 x 4 block of tiles and share their A and B tiles through that L2.
 // The grid holds 8 * ceil(tiles / 8) ids; ids past the end get no tile.
 constexpr int XCDS = 8;
+constexpr int kCUs = 256;
 constexpr int GROUP_M = 8;
 __host__ __device__ inline int ids_per_xcd(long long tiles) { return (int)((tiles + XCDS - 1) / XCDS); }
 // position in the grouped tile order -> tile
@@ -692,47 +693,19 @@ __device__ __forceinline__ void gate_up_tile(const E *__restrict__ X, const E *_
 }
 
 // grid.x = 8 * ids_per_xcd(tilesM * sum over runs of N tiles).
-// kRouted: per-token routing.  route[t * B + b] != 0 says token t takes branch b.  Only the live
-// tiles are computed: workgroup ids are dealt over the compacted tile list as tile_of() deals them
-// over the full grid (one contiguous stretch of the list per XCD), the ids left over exit.  The
-// down projection skips the same (token tile, branch) pairs, and H is multiplied by the token's
-// route bit, so that it is exactly 0 where a token does not take a branch.
-template <int BMT, int WM, int NB, int D, bool kStaged, bool kRouted, bool kEdges, typename E>
+template <int BMT, int WM, int NB, int D, bool kStaged, bool kEdges, typename E>
 __global__ void __launch_bounds__(WM * 128)
 gate_up_mfma(const E *__restrict__ X, const E *__restrict__ Wg,
              const E *__restrict__ Wu, E *__restrict__ H, int T, int d_model, int d_inter,
-             int ldh, int tiles_m, int tiles_n, const uint8_t *__restrict__ route, RouteTiles rt,
-             BranchTable bt)
+             int ldh, int tiles_m, int tiles_n, BranchTable bt)
 {
-    static_assert(!kRouted || BMT == BM, "the routed path's tables are per 256 tokens");
     __shared__ __attribute__((aligned(1024))) char lds[lds_bytes(BMT, NB, D, kStaged)];
     constexpr int BNH = 32 * NB;                  // neurons per tile
     int tm, tn;
-    if (kRouted) {
-        const int groups = (tiles_m + GROUP_M - 1) / GROUP_M;
-        int total = 0;
-        for (int g = 0; g < groups; ++g) total += (int)rt.counts[g];
-        const int per_xcd = ids_per_xcd(total);
-        const int k = blockIdx.x / XCDS;
-        const int logical = (blockIdx.x % XCDS) * per_xcd + k;
-        if (k >= per_xcd || logical >= total) return;
-        int g = 0, before = 0;
-        for (; g < groups - 1; ++g) {
-            const int c = (int)rt.counts[g];
-            if (logical < before + c) break;
-            before += c;
-        }
-        const int e = (int)rt.list[(size_t)g * rt.stride + (logical - before)];
-        const int m0 = g * GROUP_M;
-        const int gsz = tiles_m - m0 < GROUP_M ? tiles_m - m0 : GROUP_M;
-        tm = m0 + e % gsz;
-        tn = e / gsz;
-    } else if (!tile_of(blockIdx.x, tiles_m, tiles_n, tm, tn)) {
-        return;
-    }
+    if (!tile_of(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
     int n0, n_end;
     if (!neuron_tile(bt, tn, BNH, n0, n_end)) return;
-    gate_up_tile<BMT, WM, NB, D, kStaged, kRouted, kEdges>(X, Wg, Wu, H, T, d_model, ldh, route, bt, lds, tm, n0, n_end);
+    gate_up_tile<BMT, WM, NB, D, kStaged, false, kEdges>(X, Wg, Wu, H, T, d_model, ldh, nullptr, bt, lds, tm, n0, n_end);
 }
 
 // The gate+up projection with WIDE tiles for the full rounds of 256 workgroups and smaller tiles for what
@@ -782,6 +755,69 @@ gate_up_mfma_mixed(const uint16_t *__restrict__ X, const uint16_t *__restrict__ 
             gate_up_tile<BM / 2, WM, 2, QUARTER_D, false, false>(X, Wg, Wu, H, T, d_model, ldh, nullptr, bt, lds, tq,
                                                                  n0, n_end);
         }
+    }
+}
+
+// The gate+up projection with per-token routing.  route[t * B + b] != 0 says token t takes branch b.  Only the live
+// tiles are computed: workgroup ids are dealt over the compacted tile list as tile_of() deals them over the full grid
+// (one contiguous stretch of the list per XCD), the ids left over exit.  The down projection skips the same (token
+// tile, branch) pairs, and H is multiplied by the token's route bit, so that it is exactly 0 where a token does not
+// take a branch.
+// How many tiles are live is known on the device only, so the split of the last round into halves or quarters (see
+// gate_up_mfma_mixed, same rule, also when there is no full round) is decided here by every workgroup.
+// 4096 x 14336, 16 branches, T = 1900, 7 sequences of 4 branches each (about 336 live tiles): 186 us against 205 us with a
+// second round of whole tiles (the whole call 292 against 312 us).  Workgroups past the last item cost nothing that
+// shows: a loop over the items in two rounds of workgroups instead took 194 us, in one round 185 us, and spills.
+// grid.x = 8 * (ids_per_xcd(all tiles) + kCUs / XCDS): the most workgroups any number of live tiles asks for.
+template <int WM, bool kEdges>
+__global__ void __launch_bounds__(WM * 128)
+gate_up_mfma_routed(const uint16_t *__restrict__ X, const uint16_t *__restrict__ Wg,
+                    const uint16_t *__restrict__ Wu, uint16_t *__restrict__ H, int T, int d_model, int ldh,
+                    int tiles_m, const uint8_t *__restrict__ route, RouteTiles rt, BranchTable bt)
+{
+    __shared__ __attribute__((aligned(1024))) char lds[lds_bytes(BM, 4)];
+    const int groups = (tiles_m + GROUP_M - 1) / GROUP_M;
+    int total = 0;
+    for (int g = 0; g < groups; ++g) total += (int)rt.counts[g];
+    const int P = ids_per_xcd(total);
+    const int rest = total % kCUs;
+    const int parts = rest == 0 || rest > kCUs / 2 ? 1 : (rest <= kCUs / 4 ? 4 : 2);     // pieces of a left-over tile
+    const int whole_per_xcd = parts == 1 ? P : total / kCUs * (kCUs / XCDS);
+    const int xcd = blockIdx.x % XCDS;
+    const int xcd_end = (xcd + 1) * P < total ? (xcd + 1) * P : total;
+    int k = blockIdx.x / XCDS, piece = -1;
+    if (k >= whole_per_xcd) {
+        if (parts == 1) return;
+        piece = (k - whole_per_xcd) % parts;
+        k = whole_per_xcd + (k - whole_per_xcd) / parts;
+    }
+    const int logical = xcd * P + k;
+    if (logical >= xcd_end) return;
+    int g = 0, before = 0;
+    for (; g < groups - 1; ++g) {
+        const int c = (int)rt.counts[g];
+        if (logical < before + c) break;
+        before += c;
+    }
+    const int e = (int)rt.list[(size_t)g * rt.stride + (logical - before)];
+    const int m0 = g * GROUP_M;
+    const int gsz = tiles_m - m0 < GROUP_M ? tiles_m - m0 : GROUP_M;
+    const int tm = m0 + e % gsz, tn = e / gsz;
+    int n0, n_end;
+    if (!neuron_tile(bt, tn, 128, n0, n_end)) return;
+    if (piece < 0) {
+        gate_up_tile<BM, WM, 4, 2, false, true, kEdges>(X, Wg, Wu, H, T, d_model, ldh, route, bt, lds, tm, n0, n_end);
+        return;
+    }
+    n0 += (piece % 2) * 64;
+    if (n0 >= n_end) return;                                       // the run ends in the first half
+    if (parts == 2) {
+        gate_up_tile<BM, WM, 2, 2, false, true, kEdges>(X, Wg, Wu, H, T, d_model, ldh, route, bt, lds, tm, n0, n_end);
+    } else {
+        const int tq = 2 * tm + piece / 2;                         // token tile of 128
+        if (tq * (BM / 2) >= T) return;                            // the last token tile ends in its first half
+        gate_up_tile<BM / 2, WM, 2, QUARTER_D, false, true, kEdges>(X, Wg, Wu, H, T, d_model, ldh, route, bt, lds, tq,
+                                                                    n0, n_end);
     }
 }
 
@@ -1141,7 +1177,6 @@ struct TileDims {
 };
 constexpr TileDims kTileDims[N_TILE_SHAPES] = {{BM, 128, 1}, {BM, 64, 1}, {BM_SMALL, 64, 2}, {BM, 128, 1}, {BM_SMALL, 64, 1},
                                                {BM_SLIM, 64, 1}};
-constexpr int kCUs = 256;
 
 long long gate_up_tiles(const BranchTable &bt, int T, TileShape sh)
 {
@@ -1284,7 +1319,7 @@ size_t mfma_partial_bytes(int T, int d_model, int d_inter)
     return s > 1 ? align_up((size_t)s * T * d_model * sizeof(float), 256) : 0;
 }
 
-template <typename S, bool kRouted = false, bool kEdges = false, typename E = uint16_t>
+template <typename S, bool kEdges = false, typename E = uint16_t>
 static hipError_t launch_gate_up(const FwdArgs &a, const BranchTable &bt)
 {
     constexpr int BMT = S::BMT, WM = S::WM, NB = S::NB;
@@ -1293,29 +1328,39 @@ static hipError_t launch_gate_up(const FwdArgs &a, const BranchTable &bt)
     for (int r = 0; r < bt.n_runs; ++r) tiles_n += ceil_div(bt.run_end[r] - bt.run_start[r], 32 * NB);
     const long long grid = (long long)XCDS * ids_per_xcd(tiles_m * tiles_n);
     if (grid > 0x7fffffffLL) return note_hip_error("gate_up_mfma grid", hipErrorInvalidValue);
-    RouteTiles rt{nullptr, nullptr, nullptr, 0};
-    if (kRouted) {
-        // one launch builds the tile list (and tile_need, which the down projection reads as well)
-        static_assert(!kRouted || 32 * NB == BNH_MAX, "the list's row stride is sized for wide tiles");
-        uint8_t *need = a.route_scratch;
-        uint32_t *counts = reinterpret_cast<uint32_t *>(a.route_scratch + route_need_bytes(a.T));
-        uint32_t *list = reinterpret_cast<uint32_t *>(a.route_scratch + route_need_bytes(a.T) + route_counts_bytes(a.T));
-        const int stride = route_list_stride(a.d_inter);
-        if ((long long)GROUP_M * tiles_n > stride || tiles_n > ROUTE_MAX_TILES_N)
-            return note_hip_error("route tile list size", hipErrorInvalidValue);
-        {
-            ProfileScope ps(MLPMOE_KERNEL_ROUTE_TILES, a.stream);
-            route_tile_list<32 * NB><<<ceil_div(tiles_m, GROUP_M), 1024, 0, a.stream>>>(
-                a.route, need, counts, list, stride, a.T, tiles_m, (int)tiles_n, bt);
-        }
-        if (launch_status("route_tile_list launch") != hipSuccess) return hipErrorLaunchFailure;
-        rt = RouteTiles{need, counts, list, stride};
-    }
     ProfileScope ps(MLPMOE_KERNEL_GATE_UP_MFMA, a.stream);
-    gate_up_mfma<BMT, WM, NB, S::D, S::kStaged, kRouted, kEdges><<<(unsigned)grid, WM * 128, 0, a.stream>>>(
-        static_cast<const E *>(a.x), static_cast<const E *>(a.Wg), static_cast<const E *>(a.Wu), static_cast<E *>(a.H), a.T, a.d_model, a.d_inter,
-        a.ldh, tiles_m, (int)tiles_n, a.route, rt, bt);
+    gate_up_mfma<BMT, WM, NB, S::D, S::kStaged, kEdges><<<(unsigned)grid, WM * 128, 0, a.stream>>>(
+        static_cast<const E *>(a.x), static_cast<const E *>(a.Wg), static_cast<const E *>(a.Wu), static_cast<E *>(a.H), a.T,
+        a.d_model, a.d_inter, a.ldh, tiles_m, (int)tiles_n, bt);
     return launch_status("gate_up_mfma launch");
+}
+
+// One launch builds the list of live tiles (and tile_need, which the down projection reads as well), one walks it.
+template <bool kEdges>
+static hipError_t launch_gate_up_routed(const FwdArgs &a, const BranchTable &bt)
+{
+    const int tiles_m = ceil_div(a.T, BM);
+    long long tiles_n = 0;
+    for (int r = 0; r < bt.n_runs; ++r) tiles_n += ceil_div(bt.run_end[r] - bt.run_start[r], BNH_MAX);
+    const long long grid = (long long)XCDS * (ids_per_xcd(tiles_m * tiles_n) + kCUs / XCDS);
+    if (grid > 0x7fffffffLL) return note_hip_error("gate_up_mfma_routed grid", hipErrorInvalidValue);
+    uint8_t *need = a.route_scratch;
+    uint32_t *counts = reinterpret_cast<uint32_t *>(a.route_scratch + route_need_bytes(a.T));
+    uint32_t *list = reinterpret_cast<uint32_t *>(a.route_scratch + route_need_bytes(a.T) + route_counts_bytes(a.T));
+    const int stride = route_list_stride(a.d_inter);
+    if ((long long)GROUP_M * tiles_n > stride || tiles_n > ROUTE_MAX_TILES_N)
+        return note_hip_error("route tile list size", hipErrorInvalidValue);
+    {
+        ProfileScope ps(MLPMOE_KERNEL_ROUTE_TILES, a.stream);
+        route_tile_list<BNH_MAX><<<ceil_div(tiles_m, GROUP_M), 1024, 0, a.stream>>>(
+            a.route, need, counts, list, stride, a.T, tiles_m, (int)tiles_n, bt);
+    }
+    if (launch_status("route_tile_list launch") != hipSuccess) return hipErrorLaunchFailure;
+    ProfileScope ps(MLPMOE_KERNEL_GATE_UP_MFMA, a.stream);
+    gate_up_mfma_routed<MFMA_WM, kEdges><<<(unsigned)grid, MFMA_WM * 128, 0, a.stream>>>(
+        static_cast<const uint16_t *>(a.x), static_cast<const uint16_t *>(a.Wg), static_cast<const uint16_t *>(a.Wu),
+        static_cast<uint16_t *>(a.H), a.T, a.d_model, a.ldh, tiles_m, a.route, RouteTiles{need, counts, list, stride}, bt);
+    return launch_status("gate_up_mfma_routed launch");
 }
 
 static hipError_t launch_gate_up_mixed(const FwdArgs &a, const BranchTable &bt)
@@ -1393,9 +1438,9 @@ hipError_t launch_mfma_routed_bf16(const FwdArgs &a, const BranchTable &bt, bool
     if (uneven) {
         UnevenRuns u;
         uneven_runs<Elem<uint16_t>::CHUNK>(bt, u);
-        e = launch_gate_up<ShapeWide, true, true>(a, u.outer);
+        e = launch_gate_up_routed<true>(a, u.outer);
     } else {
-        e = launch_gate_up<ShapeWide, true>(a, bt);
+        e = launch_gate_up_routed<false>(a, bt);
     }
     if (e != hipSuccess) return hipErrorLaunchFailure;
     // 256-token tiles (the routing tables are per 256 tokens); narrow when K is split: half the partial sums
@@ -1435,7 +1480,7 @@ size_t mfma_partial_bytes_f32(int T, int d_model, int d_inter)
 template <bool kEdges, typename Ed>
 static hipError_t launch_mfma_f32_runs(const FwdArgs &a, const BranchTable &outer, const BranchTable &inner, const Ed &edges)
 {
-    if (launch_gate_up<ShapeF32, false, kEdges, float>(a, outer) != hipSuccess) return hipErrorLaunchFailure;
+    if (launch_gate_up<ShapeF32, kEdges, float>(a, outer) != hipSuccess) return hipErrorLaunchFailure;
     // a workspace without room for all partial sums gets as many as fit
     const long long fit = (long long)(a.partial_bytes / ((size_t)a.T * a.d_model * sizeof(float)));
     int splits = f32_down_splits(a.T, a.d_model, k_tiles(inner, Elem<float>::BK));
@@ -1459,11 +1504,11 @@ template <bool kEdges>
 static hipError_t launch_gate_up_shape(const FwdArgs &a, const BranchTable &bt, TileShape sh)
 {
     switch (sh) {
-    case TILE_WIDE: return launch_gate_up<ShapeWide, false, kEdges>(a, bt);
-    case TILE_NARROW: return launch_gate_up<ShapeNarrow, false, kEdges>(a, bt);
-    case TILE_SMALL: return launch_gate_up<ShapeSmall, false, kEdges>(a, bt);
-    case TILE_DEEP: return launch_gate_up<ShapeDeep, false, kEdges>(a, bt);
-    case TILE_SLIM: return launch_gate_up<ShapeSlim, false, kEdges>(a, bt);
+    case TILE_WIDE: return launch_gate_up<ShapeWide, kEdges>(a, bt);
+    case TILE_NARROW: return launch_gate_up<ShapeNarrow, kEdges>(a, bt);
+    case TILE_SMALL: return launch_gate_up<ShapeSmall, kEdges>(a, bt);
+    case TILE_DEEP: return launch_gate_up<ShapeDeep, kEdges>(a, bt);
+    case TILE_SLIM: return launch_gate_up<ShapeSlim, kEdges>(a, bt);
     default: return hipErrorInvalidValue;
     }
 }
