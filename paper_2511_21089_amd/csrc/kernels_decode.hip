@@ -55,12 +55,36 @@ __device__ __forceinline__ uint16_t to_bf16(float v)
     return __builtin_bit_cast(uint16_t, b);
 }
 
-__device__ __forceinline__ int branch_of(const BranchTable &bt, int j)
+// Uses two registers that were just loaded, so that their loads are waited for here, once, and not at every lane read
+// in a loop that has weights in flight.
+template <typename A, typename B>
+__device__ __forceinline__ void arrived(A &a, B &b)
 {
-    int b = 0;
-    while (b + 1 < bt.B && j >= bt.off[b + 1]) ++b;
-    return b;
+    asm volatile("" : "+v"(a), "+v"(b));
 }
+
+// Branch of a neuron and its alpha, from registers: lane b of every wave holds alpha_b and the first neuron past
+// branch b, loaded once as the kernel starts.  An epilogue that looked the branch up in the kernel arguments waited
+// for a chain of loads per tile, and its vector loads waited, in order, for the whole ring of weights in flight.
+// With the stretches' bounds in lanes, the clear behind the first requests and the grid size among the arguments: 896 x 4864,
+// T = 1: 15.8 -> 14.1 us; 6 of its 8 branches, T = 8, 24 layers: 399 -> 367 us; 4096 x 14336, T = 1, 2 layers: 134.7 -> 130.0 us.
+struct BranchLanes {
+    int v_next;
+    float v_alpha;
+    __device__ __forceinline__ explicit BranchLanes(const BranchTable &bt)
+    {
+        const int lane = threadIdx.x & 63;
+        const int next = bt.off[lane + 1];
+        v_next = lane + 1 < bt.B ? next : 0x7fffffff;
+        v_alpha = bt.alpha[lane];
+    }
+    // n and b uniform over the wave, every lane active
+    __device__ __forceinline__ int branch(int n) const { return __popcll(__ballot(v_next <= n)); }
+    __device__ __forceinline__ float alpha(int b) const
+    {
+        return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v_alpha), b));
+    }
+};
 
 // Lane layout of v_mfma_f32_16x16x32_bf16: operand lane l holds row/col (l & 15) and the 8
 // K values of group q = l >> 4.  A lane here loads 16 contiguous K values k0+16q .. k0+16q+15
@@ -86,17 +110,29 @@ __device__ __forceinline__ unsigned long long live_branches(const BranchTable &b
 // The stretches of the intermediate dimension a launch works on.  Without routing they are the
 // table's runs of active branches; with routing, one stretch per branch, empty unless the branch is
 // live (all branch offsets are then multiples of 8).
+// Lane r of every wave holds the bounds of stretch r, so that the cursors read lanes and not memory: one round of
+// loads as the kernel starts, in place of a chain of dependent ones before the first weights are asked for.
 template <bool kRouted>
 struct Stretches {
-    const BranchTable &bt;
-    unsigned long long live;
-    __device__ __forceinline__ int count() const { return kRouted ? bt.B : bt.n_runs; }
-    __device__ __forceinline__ int beg(int r) const { return kRouted ? bt.off[r] : bt.run_start[r]; }
-    __device__ __forceinline__ int end(int r) const
+    int n, v_beg, v_end;
+    __device__ __forceinline__ Stretches(const BranchTable &bt, const uint8_t *route, int T)
     {
-        if (!kRouted) return bt.run_end[r];
-        return ((live >> r) & 1ULL) ? bt.off[r + 1] : bt.off[r];
+        const int lane = threadIdx.x & 63;
+        if (kRouted) {
+            n = bt.B;
+            v_beg = bt.off[lane];
+            const int next = bt.off[lane + 1];
+            v_end = ((live_branches(bt, route, T) >> lane) & 1ULL) ? next : v_beg;
+        } else {
+            n = bt.n_runs;
+            const int r = lane < kMaxRuns ? lane : kMaxRuns - 1;
+            v_beg = bt.run_start[r];
+            v_end = bt.run_end[r];
+        }
     }
+    __device__ __forceinline__ int count() const { return n; }
+    __device__ __forceinline__ int beg(int r) const { return __builtin_amdgcn_readlane(v_beg, r); }
+    __device__ __forceinline__ int end(int r) const { return __builtin_amdgcn_readlane(v_end, r); }
 };
 
 // Walks the groups of 8 rows ("tiles") of the stretches in steps: (stretch, tile inside it).
@@ -134,7 +170,10 @@ decode_kernel(const uint16_t *__restrict__ Xin, int ldx, int T,
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r16 = lane & 15, q = lane >> 4;
-    const Stretches<kRouted> st{bt, kRouted ? live_branches(bt, route, T) : 0ULL};
+    BranchLanes br(bt);
+    Stretches<kRouted> st(bt, route, T);
+    arrived(br.v_next, br.v_alpha);
+    arrived(st.v_beg, st.v_end);
 
     // tile -> this lane's weight row
     int row0 = 0;
@@ -212,9 +251,17 @@ decode_kernel(const uint16_t *__restrict__ Xin, int ldx, int T,
     __syncthreads();
     if (threadIdx.x >= 256) return;
     // accumulator layout: register v of lane l is D[row 4*(l>>4)+v][col l&15]
-    const int v = threadIdx.x >> 6;
+    const int v = wave;
     const int row = 4 * q + v;
     const int t = r16;
+    int b = 0;
+    float alpha = 0.f;
+    if (kGateUp) {
+        const int b0 = br.branch(row0 + v), b1 = br.branch(row0 + 4 + v);
+        const float alpha0 = br.alpha(b0), alpha1 = br.alpha(b1);
+        b = q ? b1 : b0;                                 // rows 0-7: q is 0 or 1
+        alpha = q ? alpha1 : alpha0;
+    }
     if (t >= T) return;
     if (kGateUp) {
         if (row >= 8) return;                            // rows 8-15 hold the up projection of rows 0-7
@@ -225,8 +272,7 @@ decode_kernel(const uint16_t *__restrict__ Xin, int ldx, int T,
             up += red[w][threadIdx.x + 32];              // row + 8: two lane groups further
         }
         const int n = row0 + row;
-        const int b = branch_of(bt, n);
-        float v = bt.alpha[b] * silu_mul(g, up);
+        float v = alpha * silu_mul(g, up);
         if (kRouted) v = route[(size_t)t * bt.B + b] ? v : 0.f;
         Hout[(size_t)t * ldh + n] = to_bf16(v);
     } else {
@@ -265,7 +311,8 @@ decode_down_split(const uint16_t *__restrict__ Hin, int ldx, int T, const uint16
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r16 = lane & 15, q = lane >> 4;
-    const Stretches<kRouted> st{bt, kRouted ? live_branches(bt, route, T) : 0ULL};
+    Stretches<kRouted> st(bt, route, T);
+    arrived(st.v_beg, st.v_end);
     const int row0 = blockIdx.x * (16 * RT);
     const uint16_t *wrow[RT];
 #pragma unroll
@@ -357,7 +404,17 @@ decode_down_split(const uint16_t *__restrict__ Hin, int ldx, int T, const uint16
     }
 }
 
+// Sets n floats to 0 for the kernel that follows (decode_down_split); p may be null.  Called once the first weights are
+// requested: loads wait for the stores before them.
+__device__ __forceinline__ void clear_floats(float *__restrict__ p, int n, int threads, int grid)
+{
+    if (p)
+        for (int i = blockIdx.x * threads + threadIdx.x; i < n; i += grid * threads) p[i] = 0.f;
+}
+
 // Persistent gate+up kernel for layers whose x fits in LDS (T * (d_model*2 + 16) bytes).
+// grid is gridDim.x, handed over beside the other arguments: the hidden argument is a cold line of its own that the
+// first weight request would wait for.
 // One workgroup per CU copies x into LDS once and then walks its tiles (tile t belongs to
 // workgroup t % grid, so every CU gets the same number).  The NW waves of the workgroup share each
 // tile with interleaved 64-element K blocks, which makes the workgroup read NW*128 contiguous
@@ -371,11 +428,8 @@ template <int NW, int U, bool kRouted = false>
 __global__ void __launch_bounds__(NW * 64)
 decode_gate_up_persist(const uint16_t *__restrict__ X, int T, const uint16_t *__restrict__ Wg,
                        const uint16_t *__restrict__ Wu, int d_model, uint16_t *__restrict__ Hout, int ldh,
-                       const uint8_t *__restrict__ route, float *__restrict__ clear, int clear_n, BranchTable bt)
+                       const uint8_t *__restrict__ route, float *__restrict__ clear, int clear_n, int grid, BranchTable bt)
 {
-    // clear (may be null): clear_n floats to set to 0 for the kernel that follows (decode_down_split)
-    if (clear)
-        for (int i = blockIdx.x * (NW * 64) + threadIdx.x; i < clear_n; i += gridDim.x * (NW * 64)) clear[i] = 0.f;
     static_assert(NW >= 4, "the reduction uses 256 threads");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     float *red = reinterpret_cast<float *>(smem);                 // [2][NW][256]
@@ -394,7 +448,10 @@ decode_gate_up_persist(const uint16_t *__restrict__ X, int T, const uint16_t *__
     const uint16_t *wsel = r16 < 8 ? Wg : Wu;
 
     // with routing the workgroups share out the tiles of the live branches only
-    const Stretches<kRouted> st{bt, kRouted ? live_branches(bt, route, T) : 0ULL};
+    BranchLanes br(bt);
+    Stretches<kRouted> st(bt, route, T);
+    arrived(br.v_next, br.v_alpha);
+    arrived(st.v_beg, st.v_end);
 
     // load cursor: U blocks ahead of the block being consumed
     TileCursor<kRouted> l_cur(st, blockIdx.x);
@@ -410,7 +467,7 @@ decode_gate_up_persist(const uint16_t *__restrict__ X, int T, const uint16_t *__
         wa[u][1] = ld16((more && kl + KH < d_model) ? l_wrow + b * KB + KH : zero);
         if (++l_j == nb_pad) {
             l_j = 0;
-            l_cur.advance(st, gridDim.x);
+            l_cur.advance(st, grid);
             l_row0 = l_cur.row0(st);
             if (l_row0 >= 0) l_wrow = wsel + (size_t)l_row0 * d_model + lane_row_off;
         }
@@ -441,9 +498,11 @@ decode_gate_up_persist(const uint16_t *__restrict__ X, int T, const uint16_t *__
     if (threadIdx.x == 0) *reinterpret_cast<u32x4 *>(xs + zero_off) = u32x4{0, 0, 0, 0};
     __syncthreads();
 
+    clear_floats(clear, clear_n, NW * 64, grid);
+
     int it = 0;
     TileCursor<kRouted> cur(st, blockIdx.x);
-    for (int row0 = cur.row0(st); row0 >= 0; cur.advance(st, gridDim.x), row0 = cur.row0(st), ++it) {
+    for (int row0 = cur.row0(st); row0 >= 0; cur.advance(st, grid), row0 = cur.row0(st), ++it) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
         for (int j0 = 0; j0 < nb_pad; j0 += U) {
 #pragma unroll
@@ -466,8 +525,12 @@ decode_gate_up_persist(const uint16_t *__restrict__ X, int T, const uint16_t *__
         for (int v = 0; v < 4; ++v) rb[wave * 256 + v * 64 + lane] = acc[v];
         __syncthreads();
         if (threadIdx.x < 256) {
-            const int v = threadIdx.x >> 6;
+            const int v = wave;
             const int row = 4 * q + v;                   // register v of lane l is D[row 4*(l>>4)+v][col l&15]
+            const int b0 = br.branch(row0 + v), b1 = br.branch(row0 + 4 + v);
+            const int b = q ? b1 : b0;                   // rows 0-7: q is 0 or 1
+            const float alpha0 = br.alpha(b0), alpha1 = br.alpha(b1);
+            const float alpha = q ? alpha1 : alpha0;
             if (row < 8 && tok) {
                 float g = 0.f, up = 0.f;
 #pragma unroll
@@ -476,8 +539,7 @@ decode_gate_up_persist(const uint16_t *__restrict__ X, int T, const uint16_t *__
                     up += rb[w * 256 + threadIdx.x + 32];
                 }
                 const int n = row0 + row;
-                const int b = branch_of(bt, n);
-                float v = bt.alpha[b] * silu_mul(g, up);
+                float v = alpha * silu_mul(g, up);
                 if (kRouted) v = route[(size_t)r16 * bt.B + b] ? v : 0.f;
                 Hout[(size_t)r16 * ldh + n] = to_bf16(v);
             }
@@ -497,10 +559,8 @@ template <int NW, int U, int XB, bool kRouted = false>
 __global__ void __launch_bounds__(NW * 64)
 decode_gate_up_xreg(const uint16_t *__restrict__ X, int T, const uint16_t *__restrict__ Wg,
                     const uint16_t *__restrict__ Wu, int d_model, uint16_t *__restrict__ Hout, int ldh,
-                    const uint8_t *__restrict__ route, float *__restrict__ clear, int clear_n, BranchTable bt)
+                    const uint8_t *__restrict__ route, float *__restrict__ clear, int clear_n, int grid, BranchTable bt)
 {
-    if (clear)
-        for (int i = blockIdx.x * (NW * 64) + threadIdx.x; i < clear_n; i += gridDim.x * (NW * 64)) clear[i] = 0.f;
     static_assert(NW >= 4 && (XB % U == 0 || U % XB == 0), "the reduction uses 256 threads; ring slots are compile-time");
     constexpr int TPR = XB >= U ? 1 : U / XB;     // tiles per revolution of the ring
     __shared__ float red[2][NW][256];
@@ -511,7 +571,10 @@ decode_gate_up_xreg(const uint16_t *__restrict__ X, int T, const uint16_t *__res
     const uint16_t *zero = reinterpret_cast<const uint16_t *>(g_zero16);
     const size_t lane_row_off = (size_t)(r16 & 7) * d_model + q * KQ;
     const uint16_t *wsel = r16 < 8 ? Wg : Wu;
-    const Stretches<kRouted> st{bt, kRouted ? live_branches(bt, route, T) : 0ULL};
+    BranchLanes br(bt);
+    Stretches<kRouted> st(bt, route, T);
+    arrived(br.v_next, br.v_alpha);
+    arrived(st.v_beg, st.v_end);
 
     TileCursor<kRouted> l_cur(st, blockIdx.x);
     int l_j = 0;
@@ -526,7 +589,7 @@ decode_gate_up_xreg(const uint16_t *__restrict__ X, int T, const uint16_t *__res
         wa[u][1] = ld16((more && kl + KH < d_model) ? l_wrow + b * KB + KH : zero);
         if (++l_j == XB) {
             l_j = 0;
-            l_cur.advance(st, gridDim.x);
+            l_cur.advance(st, grid);
             l_row0 = l_cur.row0(st);
             if (l_row0 >= 0) l_wrow = wsel + (size_t)l_row0 * d_model + lane_row_off;
         }
@@ -546,6 +609,8 @@ decode_gate_up_xreg(const uint16_t *__restrict__ X, int T, const uint16_t *__res
             xr[j][1] = ld16((tok && kl + KH < d_model) ? xp + b * KB + KH : zero);
         }
     }
+
+    clear_floats(clear, clear_n, NW * 64, grid);
 
     int it = 0;
     TileCursor<kRouted> cur(st, blockIdx.x);
@@ -571,8 +636,12 @@ decode_gate_up_xreg(const uint16_t *__restrict__ X, int T, const uint16_t *__res
             for (int v = 0; v < 4; ++v) rb[wave * 256 + v * 64 + lane] = acc[v];
             __syncthreads();
             if (threadIdx.x < 256) {
-                const int v = threadIdx.x >> 6;
-                const int row = 4 * q + v;
+                const int v = wave;
+                const int row = 4 * q + v;                   // register v of lane l is D[row 4*(l>>4)+v][col l&15]
+                const int b0 = br.branch(row0 + v), b1 = br.branch(row0 + 4 + v);
+                const int b = q ? b1 : b0;                   // rows 0-7: q is 0 or 1
+                const float alpha0 = br.alpha(b0), alpha1 = br.alpha(b1);
+                const float alpha = q ? alpha1 : alpha0;
                 if (row < 8 && tok) {
                     float g = 0.f, up = 0.f;
 #pragma unroll
@@ -581,14 +650,13 @@ decode_gate_up_xreg(const uint16_t *__restrict__ X, int T, const uint16_t *__res
                         up += rb[w * 256 + threadIdx.x + 32];
                     }
                     const int n = row0 + row;
-                    const int b = branch_of(bt, n);
-                    float v = bt.alpha[b] * silu_mul(g, up);
+                    float v = alpha * silu_mul(g, up);
                     if (kRouted) v = route[(size_t)r16 * bt.B + b] ? v : 0.f;
                     Hout[(size_t)r16 * ldh + n] = to_bf16(v);
                 }
             }
             ++it;
-            cur.advance(st, gridDim.x);
+            cur.advance(st, grid);
             row0 = cur.row0(st);
         }
     }
@@ -647,19 +715,19 @@ static hipError_t launch_decode_impl(const FwdArgs &a, const BranchTable &bt)
         const int nb_wave = ceil_div(ceil_div(a.d_model, KB), DEC_SNW);      // K blocks per wave and tile
         if (nb_wave <= 2)
             decode_gate_up_xreg<DEC_SNW, DEC_SU, 2, kRouted><<<grid, DEC_SNW * 64, 0, a.stream>>>(
-                X, a.T, Wg, Wu, a.d_model, H, a.ldh, a.route, clear, clear_n, bt);
+                X, a.T, Wg, Wu, a.d_model, H, a.ldh, a.route, clear, clear_n, grid, bt);
         else if (nb_wave <= 4)
             decode_gate_up_xreg<DEC_SNW, DEC_SU, 4, kRouted><<<grid, DEC_SNW * 64, 0, a.stream>>>(
-                X, a.T, Wg, Wu, a.d_model, H, a.ldh, a.route, clear, clear_n, bt);
+                X, a.T, Wg, Wu, a.d_model, H, a.ldh, a.route, clear, clear_n, grid, bt);
         else if (nb_pad <= 8)
             decode_gate_up_xreg<DEC_SNW, DEC_SU, 8, kRouted><<<grid, DEC_SNW * 64, 0, a.stream>>>(
-                X, a.T, Wg, Wu, a.d_model, H, a.ldh, a.route, clear, clear_n, bt);
+                X, a.T, Wg, Wu, a.d_model, H, a.ldh, a.route, clear, clear_n, grid, bt);
         else if (nb_pad <= 16)
             decode_gate_up_xreg<DEC_SNW, DEC_SU, 16, kRouted><<<grid, DEC_SNW * 64, 0, a.stream>>>(
-                X, a.T, Wg, Wu, a.d_model, H, a.ldh, a.route, clear, clear_n, bt);
+                X, a.T, Wg, Wu, a.d_model, H, a.ldh, a.route, clear, clear_n, grid, bt);
         else
             decode_gate_up_persist<DEC_SNW, DEC_SU, kRouted><<<grid, DEC_SNW * 64, xs_bytes, a.stream>>>(
-                X, a.T, Wg, Wu, a.d_model, H, a.ldh, a.route, clear, clear_n, bt);
+                X, a.T, Wg, Wu, a.d_model, H, a.ldh, a.route, clear, clear_n, grid, bt);
         if (launch_status("decode gate+up (persistent) launch") != hipSuccess) return hipErrorLaunchFailure;
     } else {
         ProfileScope ps(MLPMOE_KERNEL_DECODE_GATE_UP, a.stream);
