@@ -63,29 +63,6 @@ __device__ __forceinline__ void arrived(A &a, B &b)
     asm volatile("" : "+v"(a), "+v"(b));
 }
 
-// Branch of a neuron and its alpha, from registers: lane b of every wave holds alpha_b and the first neuron past
-// branch b, loaded once as the kernel starts.  An epilogue that looked the branch up in the kernel arguments waited
-// for a chain of loads per tile, and its vector loads waited, in order, for the whole ring of weights in flight.
-// With the stretches' bounds in lanes, the clear behind the first requests and the grid size among the arguments: 896 x 4864,
-// T = 1: 15.8 -> 14.1 us; 6 of its 8 branches, T = 8, 24 layers: 399 -> 367 us; 4096 x 14336, T = 1, 2 layers: 134.7 -> 130.0 us.
-struct BranchLanes {
-    int v_next;
-    float v_alpha;
-    __device__ __forceinline__ explicit BranchLanes(const BranchTable &bt)
-    {
-        const int lane = threadIdx.x & 63;
-        const int next = bt.off[lane + 1];
-        v_next = lane + 1 < bt.B ? next : 0x7fffffff;
-        v_alpha = bt.alpha[lane];
-    }
-    // n and b uniform over the wave, every lane active
-    __device__ __forceinline__ int branch(int n) const { return __popcll(__ballot(v_next <= n)); }
-    __device__ __forceinline__ float alpha(int b) const
-    {
-        return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v_alpha), b));
-    }
-};
-
 // Lane layout of v_mfma_f32_16x16x32_bf16: operand lane l holds row/col (l & 15) and the 8
 // K values of group q = l >> 4.  A lane here loads 16 contiguous K values k0+16q .. k0+16q+15
 // and feeds the low 8 to one MFMA and the high 8 to the next (KQ, KH); x is loaded with the same

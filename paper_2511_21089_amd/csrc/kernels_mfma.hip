@@ -521,13 +521,6 @@ __device__ __forceinline__ void edge_steps(int n, const At &at, const E *__restr
     }
 }
 
-__device__ __forceinline__ int branch_of(const BranchTable &bt, int j)
-{
-    int b = 0;
-    while (b + 1 < bt.B && j >= bt.off[b + 1]) ++b;
-    return b;
-}
-
 __device__ __forceinline__ float silu_mul(float g, float u)
 {
     // SiLU(g) * u with hardware exp2 / rcp (about 1 ulp each)
@@ -642,19 +635,25 @@ __device__ __forceinline__ void gate_up_tile(const E *__restrict__ X, const E *_
             accu[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
 
+    const BranchLanes br(bt);
     const int nk = (d_model + Elem<E>::BK - 1) / Elem<E>::BK;
     mainloop<BMT, WM, NB, D, kStaged, true>(X + (size_t)t0 * d_model, d_model, T - t0, Wg + (size_t)n0 * d_model,
                        Wu + (size_t)n0 * d_model, d_model, n_end - n0, n_end - n0, KSingle{d_model}, 0, nk,
                        lds, accg, accu);
 
-    // alpha of the tile's neurons -> LDS (the main loop is done with it)
+    // alpha of the tile's neurons -> LDS (the main loop is done with it), from the table in the lanes: a search through
+    // the kernel arguments at this point was a chain of loads with nothing to hide it (4096 x 14336, T = 100: the call 91.3 ->
+    // 85.8 us; 896 x 4864, 9 of 12 branches, T = 333: 34.0 -> 30.4 us; in float, T = 256: 86.4 -> 84.6 us)
     float *al = reinterpret_cast<float *>(lds);
     int *bl = reinterpret_cast<int *>(lds + BNH_MAX * sizeof(float));      // branch of each neuron (routing)
     int *on = reinterpret_cast<int *>(lds + 2 * BNH_MAX * sizeof(float));  // neuron in an active branch (kEdges)
+    const int n = n0 + threadIdx.x, n_last = (n0 + BNH < n_end ? n0 + BNH : n_end) - 1;
+    int b = br.branch(n0);
+    // n_last < d_inter: this ends at the entry that holds d_inter; threads past n_last are not used
+    for (int i = b, next; (next = br.next(i)) <= n_last; ++i) b += next <= n ? 1 : 0;
+    const float alpha = __shfl(br.v_alpha, b);
     if (threadIdx.x < BNH) {
-        const int n = n0 + threadIdx.x;
-        const int b = branch_of(bt, n < n_end ? n : n_end - 1);
-        al[threadIdx.x] = n < n_end ? bt.alpha[b] : 0.f;
+        al[threadIdx.x] = n < n_end ? alpha : 0.f;
         if (kRouted) bl[threadIdx.x] = b;
         if (kEdges) on[threadIdx.x] = n < n_end && ((bt.active >> b) & 1ULL) ? 1 : 0;
     }

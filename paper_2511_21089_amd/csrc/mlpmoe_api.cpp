@@ -73,7 +73,7 @@ void build_table(const int32_t *off, const float *alpha, const uint8_t *mask, in
 {
     memset(&bt, 0, sizeof(bt));
     bt.B = B;
-    for (int b = 0; b <= B; ++b) bt.off[b] = off[b];
+    for (int b = 0; b <= MLPMOE_MAX_BRANCHES; ++b) bt.off[b] = b <= B ? off[b] : kOffEnd;
     int runs = 0;
     for (int b = 0; b < B; ++b) {
         bt.alpha[b] = alpha[b];
