@@ -1,0 +1,26 @@
+"""The down projection with K split: the sum of 2 to 32 partial results, around one batch of partial sums and around the
+size from which a thread adds two pieces, and the split planned for short K loops.  Against a float64 product of the
+stored intermediate; the bf16 result is the float one rounded once."""
+import numpy as np
+import pytest
+
+from gpu_util import C_SUM, U24, run_gpu_with_hidden, widen
+from paper_2511_21089_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,d_model,d_inter", [
+    (17, 64, 8 * 64), (33, 72, 32 * 64), (100, 136, 36 * 64), (50, 64, 40 * 64), (20, 128, 130 * 64),   # 2 .. 32 splits
+    (128, 896, 4864), (333, 896, 3656), (600, 896, 4864), (150, 2048, 2048),                             # short K loops
+    (2047, 512, 1024), (2048, 512, 1024), (2049, 512, 1024)])                                            # around 2^18 pieces
+def test_split_sum(T, d_model, d_inter):
+    rng = np.random.default_rng(T + d_inter)
+    x, Wg, Wu, Wd = synth.random_layer(rng, T, d_model, d_inter, dtype="bf16", w_scale=0.05)
+    args = (x, Wg, Wu, Wd, np.array([0, d_inter], np.int32), np.ones(1, np.float32), np.ones(1, np.uint8))
+    got, H = run_gpu_with_hidden(*args)
+    W = widen(Wd).astype(np.float64)
+    bound = C_SUM * U24 * (np.abs(H) @ np.abs(W).T) + 1e-30
+    assert np.all(np.abs(got - H @ W.T) <= bound)
+    low, _ = run_gpu_with_hidden(*args, out_bf16=True)
+    assert np.all(np.abs(low - got) <= 2.0 ** -8 * np.abs(got) + 1e-30)
