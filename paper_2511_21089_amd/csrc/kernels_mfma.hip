@@ -1265,6 +1265,24 @@ int down_splits(int T, int d_model, int k_elems, TileShape sh)
     return s < 1 ? 1 : (int)s;
 }
 
+// Estimate for a launch of the down projection.  K loops of at most 16 tiles (what a K split of a narrow layer leaves) have
+// their operands in the caches: a K tile takes SLIM 0.44 and DEEP 0.6 us there, the first loads and the stores of a SLIM
+// workgroup 2.5 us and of a pair of SMALL ones 2.2 us each (896 x 4864 at T = 128 .. 600).
+constexpr int SHORT_K_TILES = 16;
+double down_cost_us(long long tiles, int nk, TileShape sh, double bytes)
+{
+    double c = launch_cost_us(tiles, nk, sh, bytes);
+    const double rounds = (double)((tiles + kCUs - 1) / kCUs);
+    if (nk > SHORT_K_TILES) return c;
+    if (sh == TILE_SLIM) c = std::max(rounds * (nk * 0.44 + 2.5), bytes / kDeepStreamBytesPerUs + 2.5);
+    if (sh == TILE_DEEP) c = std::max(rounds * (nk * 0.6 + 4.4), bytes / kDeepStreamBytesPerUs + 4.4);
+    if (sh == TILE_SMALL && rounds >= 2) c += 0.7 * 2 * (int)(rounds / 2);
+    return c;
+}
+
+// The sum of sp partial results of n floats: about 5 us for small ones, and 3.3 us plus its traffic at 6.5 TB/s.
+double reduce_cost_us(int sp, double n) { return sp > 1 ? std::max(5.0, 3.3 + (sp + 1.0) * n * 4.0 / 6.5e6) : 0.0; }
+
 // How the down projection of one call is launched: tile shape and K split (the partial results of a split
 // go through the workspace and a second kernel adds them up in a fixed order; adding two halves into
 // the result with float atomics instead was measured 2.4 times slower on the 0.5B-shaped layer).
@@ -1283,15 +1301,19 @@ DownPlan plan_down(const FwdArgs &a, const BranchTable &bt, bool routed)
         if (routed && kTileDims[sh].bm != BM) continue;
         const TileDims &d = kTileDims[sh];
         const long long tiles = (long long)ceil_div(a.T, d.bm) * ceil_div(a.d_model, 2 * d.bn);
-        int sp = std::min(down_splits(a.T, a.d_model, bt.d_eff, sh), kt);
-        if (sp > 1 && (size_t)sp * a.T * a.d_model * sizeof(float) > a.partial_bytes) sp = 1;
-        // split as far as it fills the chip; the second kernel that adds the sp partial sums up costs about
-        // 6 us plus (sp + 1) * T * d_model floats at 8 TB/s
-        double c = launch_cost_us(tiles * sp, ceil_div(kt, sp), sh, 2.0 * bt.d_eff * (a.d_model + a.T));
-        if (sp > 1) c += 6.0 + (sp + 1.0) * (double)a.T * a.d_model * 4.0 / 8e6;
-        if (c < best_cost) {
-            best = DownPlan{sh, sp};
-            best_cost = c;
+        const int fill = std::min(down_splits(a.T, a.d_model, bt.d_eff, sh), kt);
+        // Split as far as it fills the chip or, with SMALL and a short K, as far as gives every CU one workgroup: half the
+        // partial sums, and no pair that shares a CU.  896 x 4864 in one run: T = 333 31.3 -> 28.6, T = 600 37.4 -> 34.4,
+        // T = 128 (SLIM instead of SMALL) 26.4 -> 25.4 us.
+        for (int sp : {fill, fill / 2}) {
+            if (sp < 1 || (sp != fill && (sh != TILE_SMALL || ceil_div(kt, sp) > SHORT_K_TILES))) continue;
+            if (sp > 1 && (size_t)sp * a.T * a.d_model * sizeof(float) > a.partial_bytes) sp = 1;
+            const double c = down_cost_us(tiles * sp, ceil_div(kt, sp), sh, 2.0 * bt.d_eff * (a.d_model + a.T)) +
+                             reduce_cost_us(sp, (double)a.T * a.d_model);
+            if (c < best_cost) {
+                best = DownPlan{sh, sp};
+                best_cost = c;
+            }
         }
     }
     return best;
