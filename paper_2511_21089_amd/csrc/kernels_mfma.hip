@@ -827,7 +827,9 @@ gate_up_mfma_routed(const uint16_t *__restrict__ X, const uint16_t *__restrict__
 // to (tile_need); H is 0 for the tokens of the tile that do not take a branch.
 // kEdges: bt holds the runs rounded inwards (kRouted: the table's own runs; the ranges of a tile are rounded here)
 // and `edges` (static tables) the partial chunks, which the last K split adds.
-template <int BMT, int WM, int NB, int D, bool kStaged, bool kRouted, bool kEdges, typename E>
+// kSerial (no room for partial results): a workgroup goes through all splits of its tile and adds their sums up in the
+// order of reduce_partials, so that the result has the same bits; grid.x = 8 * ids_per_xcd(tilesM * tilesN), dst = out.
+template <int BMT, int WM, int NB, int D, bool kStaged, bool kRouted, bool kEdges, bool kSerial, typename E>
 __global__ void __launch_bounds__(WM * 128)
 down_mfma(const E *__restrict__ H, const E *__restrict__ Wd, float *__restrict__ dst, int T,
           int d_model, int d_inter, int ldh, int tiles_m, int tiles_n, int splits, int kt_total, int dst_mode,
@@ -840,7 +842,7 @@ down_mfma(const E *__restrict__ H, const E *__restrict__ Wd, float *__restrict__
     // eighth of that list: with K split, an XCD then works on few splits, whose slices of H and W_down are
     // what its L2 has to hold (the 0.5B-shaped layer at T = 2048: 4.7 MB per XCD instead of 12.5 MB).
     const int tiles = tiles_m * tiles_n;
-    const long long items = (long long)tiles * splits;
+    const long long items = (long long)tiles * (kSerial ? 1 : splits);
     const int per_xcd = ids_per_xcd(items);
     const long long item = (long long)(blockIdx.x % XCDS) * per_xcd + blockIdx.x / XCDS;
     if (item >= items) return;
@@ -856,44 +858,65 @@ down_mfma(const E *__restrict__ H, const E *__restrict__ Wd, float *__restrict__
         kt_total = 0;
         for (int r = 0; r < dyn.n; ++r) kt_total += (dyn.end(r) - dyn.start(r) + BKE - 1) / BKE;
     }
-    const int kt_begin = (int)((long long)kt_total * z / splits);
-    const int kt_end = (int)((long long)kt_total * (z + 1) / splits);
-
     constexpr int MI = BMT / 16 / WM;
     f32x4 acc0[MI][NB], acc1[MI][NB];
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j) {
-            acc0[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-            acc1[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-
     // the second block of output features may start past d_model: point it at the last row
     const int n1 = n0 + BNH < d_model ? n0 + BNH : d_model - 1;
-    if (kRouted)
-        mainloop<BMT, WM, NB, D, kStaged, true>(H + (size_t)t0 * ldh, ldh, T - t0, Wd + (size_t)n0 * d_inter,
-                                    Wd + (size_t)n1 * d_inter, d_inter, d_model - n0, d_model - n1, dyn, kt_begin,
-                                    kt_end, lds, acc0, acc1);
-    else
-        mainloop<BMT, WM, NB, D, kStaged, true>(H + (size_t)t0 * ldh, ldh, T - t0, Wd + (size_t)n0 * d_inter,
-                                    Wd + (size_t)n1 * d_inter, d_inter, d_model - n0, d_model - n1, KRuns{bt},
-                                    kt_begin, kt_end, lds, acc0, acc1);
-    if constexpr (kEdges) {
-        const auto edge_at = [&](int i, int &col, unsigned &mask) {
-            if constexpr (kRouted) {
-                run_edge<CHUNK>(__shfl(raw.v_start, i >> 1), __shfl(raw.v_end, i >> 1), i & 1, col, mask);
-            } else {
-                col = edges.col[i];
-                mask = edges.mask[i];
+    const auto sum_split = [&](int part) {         // acc0, acc1 = the sums over K split `part`
+        const int kt_begin = (int)((long long)kt_total * part / splits);
+        const int kt_end = (int)((long long)kt_total * (part + 1) / splits);
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                acc0[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                acc1[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
             }
-        };
-        int n_edges;
-        if constexpr (kRouted) n_edges = 2 * raw.n;
-        else n_edges = edges.n;
-        if (z == splits - 1)
-            edge_steps<MI, NB>(n_edges, edge_at, H + (size_t)t0 * ldh, ldh, T - t0, Wd + (size_t)n0 * d_inter,
-                               Wd + (size_t)n1 * d_inter, d_inter, d_model - n0, d_model - n1, acc0, acc1);
+        if (kRouted)
+            mainloop<BMT, WM, NB, D, kStaged, true>(H + (size_t)t0 * ldh, ldh, T - t0, Wd + (size_t)n0 * d_inter,
+                                        Wd + (size_t)n1 * d_inter, d_inter, d_model - n0, d_model - n1, dyn, kt_begin,
+                                        kt_end, lds, acc0, acc1);
+        else
+            mainloop<BMT, WM, NB, D, kStaged, true>(H + (size_t)t0 * ldh, ldh, T - t0, Wd + (size_t)n0 * d_inter,
+                                        Wd + (size_t)n1 * d_inter, d_inter, d_model - n0, d_model - n1, KRuns{bt},
+                                        kt_begin, kt_end, lds, acc0, acc1);
+        if constexpr (kEdges) {
+            const auto edge_at = [&](int i, int &col, unsigned &mask) {
+                if constexpr (kRouted) {
+                    run_edge<CHUNK>(__shfl(raw.v_start, i >> 1), __shfl(raw.v_end, i >> 1), i & 1, col, mask);
+                } else {
+                    col = edges.col[i];
+                    mask = edges.mask[i];
+                }
+            };
+            int n_edges;
+            if constexpr (kRouted) n_edges = 2 * raw.n;
+            else n_edges = edges.n;
+            if (part == splits - 1)
+                edge_steps<MI, NB>(n_edges, edge_at, H + (size_t)t0 * ldh, ldh, T - t0, Wd + (size_t)n0 * d_inter,
+                                   Wd + (size_t)n1 * d_inter, d_inter, d_model - n0, d_model - n1, acc0, acc1);
+        }
+    };
+    sum_split(z);
+    if constexpr (kSerial) {
+        f32x4 sum0[MI][NB], sum1[MI][NB];
+        for (int part = 1; part < splits; ++part) {
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    sum0[i][j] = acc0[i][j];
+                    sum1[i][j] = acc1[i][j];
+                }
+            sum_split(part);
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    acc0[i][j] = sum0[i][j] + acc0[i][j];
+                    acc1[i][j] = sum1[i][j] + acc1[i][j];
+                }
+        }
     }
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1412,8 +1435,8 @@ static hipError_t launch_gate_up_mixed(const FwdArgs &a, const BranchTable &bt)
     return launch_status("gate_up_mfma_mixed launch");
 }
 
-// bt: the K ranges (kEdges without routing: the inner runs, with their edges)
-template <typename S, bool kRouted = false, bool kEdges = false, typename E = uint16_t>
+// bt: the K ranges (kEdges without routing: the inner runs, with their edges).  kSerial: all splits in one workgroup.
+template <typename S, bool kRouted = false, bool kEdges = false, bool kSerial = false, typename E = uint16_t>
 static hipError_t launch_down(const FwdArgs &a, const BranchTable &bt, int splits,
                               const std::conditional_t<kEdges && !kRouted, EdgeList, NoEdges> &edges)
 {
@@ -1421,12 +1444,12 @@ static hipError_t launch_down(const FwdArgs &a, const BranchTable &bt, int split
     const int tiles_m = ceil_div(a.T, BMT);
     const int tiles_n = ceil_div(a.d_model, 64 * NB);
     const int kt_total = k_tiles(bt, Elem<E>::BK);
-    const long long grid = (long long)XCDS * ids_per_xcd((long long)tiles_m * tiles_n * splits);
+    const long long grid = (long long)XCDS * ids_per_xcd((long long)tiles_m * tiles_n * (kSerial ? 1 : splits));
     if (grid > 0x7fffffffLL) return note_hip_error("down_mfma grid", hipErrorInvalidValue);
     ProfileScope ps(MLPMOE_KERNEL_DOWN_MFMA, a.stream);
-    down_mfma<BMT, WM, NB, S::D, S::kStaged, kRouted, kEdges><<<(unsigned)grid, WM * 128, 0, a.stream>>>(
+    down_mfma<BMT, WM, NB, S::D, S::kStaged, kRouted, kEdges, kSerial><<<(unsigned)grid, WM * 128, 0, a.stream>>>(
         static_cast<const E *>(a.H), static_cast<const E *>(a.Wd),
-        splits > 1 ? a.partial : a.out, a.T, a.d_model, a.d_inter, a.ldh, tiles_m, tiles_n, splits, kt_total,
+        splits > 1 && !kSerial ? a.partial : a.out, a.T, a.d_model, a.d_inter, a.ldh, tiles_m, tiles_n, splits, kt_total,
         (a.out_bf16 && splits == 1) ? DST_BF16 : DST_F32, a.route_scratch, bt, edges);
     return launch_status("down_mfma launch");
 }
@@ -1514,11 +1537,14 @@ template <bool kEdges, typename Ed>
 static hipError_t launch_mfma_f32_runs(const FwdArgs &a, const BranchTable &outer, const BranchTable &inner, const Ed &edges)
 {
     if (launch_gate_up<ShapeF32, kEdges, float>(a, outer) != hipSuccess) return hipErrorLaunchFailure;
-    // a workspace without room for all partial sums gets as many as fit
-    const long long fit = (long long)(a.partial_bytes / ((size_t)a.T * a.d_model * sizeof(float)));
-    int splits = f32_down_splits(a.T, a.d_model, k_tiles(inner, Elem<float>::BK));
-    if (splits > fit) splits = fit < 1 ? 1 : (int)fit;
-    if (launch_down<ShapeF32, false, kEdges, float>(a, inner, splits, edges) != hipSuccess) return hipErrorLaunchFailure;
+    // The order of the sums depends on the sizes and the table alone: at most the splits that the workspace is sized for
+    // (short runs have more K tiles than the width they add up to), and a workspace without room for the partial sums
+    // changes who adds them up, not the result (896 x 4864, T = 256: 161 us in the least block, 86 us in a full one).
+    const int splits = std::min(f32_down_splits(a.T, a.d_model, k_tiles(inner, Elem<float>::BK)),
+                                f32_down_splits(a.T, a.d_model, ceil_div(a.d_inter, Elem<float>::BK)));
+    if (splits > 1 && (size_t)splits * a.T * a.d_model * sizeof(float) > a.partial_bytes)
+        return launch_down<ShapeF32, false, kEdges, true, float>(a, inner, splits, edges);
+    if (launch_down<ShapeF32, false, kEdges, false, float>(a, inner, splits, edges) != hipSuccess) return hipErrorLaunchFailure;
     return reduce_splits(a, splits);
 }
 

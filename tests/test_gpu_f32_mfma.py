@@ -92,3 +92,37 @@ def test_f32_split_k_and_small_workspace(mm, T):
     with pytest.raises(mm.MlpMoeError) as ei:
         mm.mlpmoe_forward_f32_ws(*dev, off, alpha, mask, ws[:hidden], out=out)
     assert ei.value.status == mm.ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("widths,mask,T,d_model", [
+    ([2048, 2048], [1, 1], 3, 64),                       # even runs
+    ([1003, 1003, 1003, 1003], [1, 1, 0, 1], 130, 68),   # edge chunks, added by the last split
+    ([36, 4] * 32, [1, 0] * 32, 17, 64),                 # short runs: more K tiles than the width adds up to
+])
+def test_f32_same_bits_in_any_block(mm, widths, mask, T, d_model):
+    """Where the partial sums of a K split are kept, or that there is no room for them, does not show in the result."""
+    import torch
+    args = make(widths, mask, T, d_model, seed=T)
+    x, Wg, Wu, Wd, off, alpha, mask = poison_pruned(args)
+    dev = [torch.from_numpy(a).cuda() for a in (x, Wg, Wu, Wd)]
+    full = mm.mlpmoe_workspace_bytes(T, d_model, int(off[-1]), len(alpha), 4)
+    # bf16 with so many output tiles that nothing is split: the same block but for H
+    hidden = [(T * mm.mlpmoe_hidden_ld(int(off[-1])) * e + 255) // 256 * 256 for e in (2, 4)]
+    least = mm.mlpmoe_workspace_bytes(T, 1 << 22, int(off[-1]), len(alpha), 2) - hidden[0] + hidden[1]
+    assert least < full                                  # K is split
+    results = []
+    for n in (full, full + 4096, full - 1, (least + full) // 2, least):
+        ws = torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda")
+        out = torch.full((T, d_model), float("nan"), dtype=torch.float32, device="cuda")
+        mm.mlpmoe_forward_f32_ws(*dev, off, alpha, mask, ws, out=out)
+        torch.cuda.synchronize()
+        results.append(out.cpu().numpy())
+    check(results[0], *args)
+    for r in results[1:]:
+        assert np.array_equal(r, results[0])
+    status = None
+    try:
+        mm.mlpmoe_forward_f32_ws(*dev, off, alpha, mask, ws[:least - 1], out=out)
+    except mm.MlpMoeError as e:
+        status = e.status
+    assert status == mm.ERR_WORKSPACE
