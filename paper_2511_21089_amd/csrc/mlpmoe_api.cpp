@@ -213,7 +213,8 @@ int forward_impl(const void *x, const void *Wg, const void *Wu, const void *Wd, 
 
 // Workspace of the current device for the entry points that take none: the caller's block if one
 // was set, else the library-owned one, grown on demand.  g_ws_mutex must be held by the caller.
-// need: what the call asks for; a block that cannot grow (the caller's, or during a capture) only has to hold least.
+// need: what a new block is made for.  A block that holds least, which the call can run in, is not replaced: a graph may
+// have been recorded with it.
 int owned_workspace(size_t need, size_t least, hipStream_t stream, void **ptr, size_t *bytes)
 {
     int dev = 0;
@@ -229,16 +230,11 @@ int owned_workspace(size_t need, size_t least, hipStream_t stream, void **ptr, s
         *bytes = w.user_bytes;
         return MLPMOE_OK;
     }
-    if (w.bytes < need) {
+    if (w.bytes < least) {
         // growing synchronises the device and allocates: neither is allowed while the stream records a graph
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(stream, &cap) != hipSuccess) (void)hipGetLastError();
-        if (cap != hipStreamCaptureStatusNone) {
-            if (!w.ptr || w.bytes < least) return MLPMOE_ERR_WORKSPACE;
-            *ptr = w.ptr;
-            *bytes = w.bytes;
-            return MLPMOE_OK;
-        }
+        if (cap != hipStreamCaptureStatusNone) return MLPMOE_ERR_WORKSPACE;
         if (w.ptr) {
             e = hipDeviceSynchronize();      // earlier launches may still be using the old block
             if (e != hipSuccess) {

@@ -1,0 +1,83 @@
+"""One scenario a process: libmlpmoe.so on the recorded runtime of fake_hip.cpp.  argv: scenario, fake library, library."""
+import ctypes
+import sys
+
+fake = ctypes.CDLL(sys.argv[2], ctypes.RTLD_GLOBAL)
+lib = ctypes.CDLL(sys.argv[3])
+fake.fake_record.restype = ctypes.c_char_p
+fake.fake_largest_allocation.argtypes = [ctypes.c_size_t]
+lib.mlpmoe_workspace_bytes.restype = ctypes.c_size_t
+lib.mlpmoe_last_error_detail.restype = ctypes.c_char_p
+OK, ERR_WORKSPACE, ERR_HIP = 0, -5, -6
+P = ctypes.c_void_p(0x10000)                       # any aligned device address: no kernel runs
+
+
+def record():
+    """What the runtime was asked since the last look: [verb, words ...] per call."""
+    lines = [l.split() for l in fake.fake_record().decode().splitlines()]
+    fake.fake_clear()
+    return lines
+
+
+def verbs(lines):
+    return [l[0] for l in lines]
+
+
+def kernels(lines):
+    return [l[1] for l in lines if l[0] == "launch"]
+
+
+def table(widths, mask=None):
+    n = len(widths)
+    off = (ctypes.c_int32 * (n + 1))()
+    for b, w in enumerate(widths):
+        off[b + 1] = off[b] + w
+    return off, (ctypes.c_float * n)(*[1.0] * n), (ctypes.c_uint8 * n)(*(mask or [1] * n)), off[n], n
+
+
+def forward(f, T, d_model, widths, mask=None, route=False):
+    off, alpha, on, d_inter, B = table(widths, mask)
+    args = [P, P, P, P, off, alpha, on] + ([P] if route else []) + [T, d_model, d_inter, B, P, None]
+    return f(*args)
+
+
+def least_and_full(T, d_model, d_inter, B):
+    """Float storage: the workspace without the partial sums of a K split (H, the tile tables, the slack: what the bf16
+    call of a size that never splits has, with H twice as large) and with them."""
+    full = lib.mlpmoe_workspace_bytes(T, d_model, d_inter, B, 4)
+    ld = lib.mlpmoe_hidden_ld(d_inter)
+    hidden2, hidden4 = ((T * ld * e + 255) // 256 * 256 for e in (2, 4))
+    wide = lib.mlpmoe_workspace_bytes(T, 1 << 22, d_inter, B, 2)     # so many output tiles that K is never split
+    return wide - hidden2 + hidden4, full
+
+
+def graph_block_stays():
+    """A block that a recorded graph may point into is replaced only by a call that cannot run in it."""
+    T, d_model, widths = 64, 256, [1024] * 4
+    least, full = least_and_full(T, d_model, 4096, 4)
+    assert least < full, (least, full)
+    # a bf16 call leaves a block between the two
+    rows = next(t for t in range(T, 4096) if least <= lib.mlpmoe_workspace_bytes(t, d_model, 4096, 4, 2) < full)
+    assert forward(lib.mlpmoe_forward_bf16, rows, d_model, widths) == OK
+    assert verbs(record()).count("malloc") == 1
+    fake.fake_capturing(1)
+    assert forward(lib.mlpmoe_forward_f32, T, d_model, widths) == OK           # recorded: runs in what is there
+    captured = record()
+    fake.fake_capturing(0)
+    assert forward(lib.mlpmoe_forward_f32, T, d_model, widths) == OK           # the same call, eager
+    eager = record()
+    assert "free" not in verbs(captured) + verbs(eager), eager
+    assert kernels(captured) == kernels(eager), (captured, eager)
+    # a larger call does replace it, and a fresh block has room for the partial sums
+    fake.fake_capturing(1)
+    assert forward(lib.mlpmoe_forward_f32, 40 * T, d_model, widths) == ERR_WORKSPACE
+    assert not record()
+    fake.fake_capturing(0)
+    lib.mlpmoe_release()
+    record()
+    assert forward(lib.mlpmoe_forward_f32, T, d_model, widths) == OK
+    assert record()[0] == ["malloc", str(full)]
+
+
+globals()[sys.argv[1]]()
+print("ok")
