@@ -213,7 +213,7 @@ int forward_impl(const void *x, const void *Wg, const void *Wu, const void *Wd, 
 
 // Workspace of the current device for the entry points that take none: the caller's block if one
 // was set, else the library-owned one, grown on demand.  g_ws_mutex must be held by the caller.
-// need: what a new block is made for.  A block that holds least, which the call can run in, is not replaced: a graph may
+// need: what a new block is made for, or least if there is not that much memory.  A block that holds least, which the call can run in, is not replaced: a graph may
 // have been recorded with it.
 int owned_workspace(size_t need, size_t least, hipStream_t stream, void **ptr, size_t *bytes)
 {
@@ -246,12 +246,17 @@ int owned_workspace(size_t need, size_t least, hipStream_t stream, void **ptr, s
             w.bytes = 0;
         }
         void *p = nullptr;
-        if (hipMalloc(&p, need) != hipSuccess) {
+        size_t got = need;
+        if (hipMalloc(&p, got) != hipSuccess) {
             (void)hipGetLastError();
-            return MLPMOE_ERR_WORKSPACE;
+            got = least;
+            if (least == need || hipMalloc(&p, got) != hipSuccess) {
+                (void)hipGetLastError();
+                return MLPMOE_ERR_WORKSPACE;
+            }
         }
         w.ptr = p;
-        w.bytes = need;
+        w.bytes = got;
     }
     *ptr = w.ptr;
     *bytes = w.bytes;
@@ -808,7 +813,16 @@ int mlpmoe_plan_create(const int32_t *branch_offsets, const float *alpha, const 
     (void)hipGetLastError();
     g_err_detail[0] = 0;
     hipError_t e = hipGetDevice(&p->device);
-    if (e == hipSuccess && p->ws_bytes) e = hipMalloc(&p->ws, p->ws_bytes);
+    if (e == hipSuccess && p->ws_bytes) {
+        e = hipMalloc(&p->ws, p->ws_bytes);
+        // the least of a float call grows with T: that of max_T covers every T
+        const size_t least = min_workspace_bytes(max_T, d_model, d_inter, B, elem_bytes);
+        if (e != hipSuccess && elem_bytes == 4 && least < p->ws_bytes) {
+            (void)hipGetLastError();
+            p->ws_bytes = least;
+            e = hipMalloc(&p->ws, p->ws_bytes);
+        }
+    }
     if (e != hipSuccess) {
         (void)note_hip_error("mlpmoe_plan_create: device workspace", e);
         (void)hipGetLastError();

@@ -79,5 +79,25 @@ def graph_block_stays():
     assert record()[0] == ["malloc", str(full)]
 
 
+def short_of_memory():
+    """A float call or plan takes the block without room for partial sums where there is no memory for the larger one."""
+    T, d_model, widths = 64, 256, [1024] * 4
+    least, full = least_and_full(T, d_model, 4096, 4)
+    off, alpha, on, d_inter, B = table(widths)
+    plan = ctypes.c_void_p()
+    fake.fake_largest_allocation(full - 1)
+    assert forward(lib.mlpmoe_forward_f32, T, d_model, widths) == OK
+    assert lib.mlpmoe_plan_create(off, alpha, on, d_model, d_inter, B, 4, T, ctypes.byref(plan)) == OK
+    assert lib.mlpmoe_plan_forward(plan, P, P, P, P, T, P, None) == OK
+    assert [l for l in record() if l[0] == "malloc"] == [["malloc", str(least)]] * 2
+    assert lib.mlpmoe_plan_destroy(plan) == OK and lib.mlpmoe_release() == OK
+    # no memory for that either: refused, and nothing launched
+    record()
+    fake.fake_largest_allocation(least - 1)
+    assert forward(lib.mlpmoe_forward_f32, T, d_model, widths) == ERR_WORKSPACE
+    assert lib.mlpmoe_plan_create(off, alpha, on, d_model, d_inter, B, 4, T, ctypes.byref(plan)) == ERR_HIP and not plan
+    assert verbs(record()) == ["refuse"] * 4
+
+
 globals()[sys.argv[1]]()
 print("ok")
