@@ -108,6 +108,7 @@ size_t mfma_partial_bytes_f32(int T, int d_model, int d_inter);
 
 hipError_t launch_fill_zero(float *out, size_t n, hipStream_t s);
 hipError_t launch_fill_zero16(uint16_t *out, size_t n, hipStream_t s);
+constexpr int kGenericMaxTokens = 65535 * 64;      // token rows the generic kernels' grid holds
 hipError_t launch_generic(const FwdArgs &a, const BranchTable &bt, bool is_bf16);
 hipError_t launch_mfma_bf16(const FwdArgs &a, const BranchTable &bt, bool uneven);
 hipError_t launch_mfma_f32(const FwdArgs &a, const BranchTable &bt);

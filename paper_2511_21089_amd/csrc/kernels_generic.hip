@@ -232,7 +232,7 @@ hipError_t launch_generic_typed(const FwdArgs &a, const BranchTable &bt)
 {
     dim3 g1(ceil_div(a.d_inter, GT), ceil_div(a.T, GT));
     dim3 g2(ceil_div(a.d_model, GT), ceil_div(a.T, GT));
-    if (g1.y > 65535u || g2.y > 65535u) return hipErrorInvalidValue;
+    if (a.T > kGenericMaxTokens) return hipErrorInvalidValue;
     {
     ProfileScope ps(MLPMOE_KERNEL_GATE_UP_GENERIC, a.stream);
     gate_up_generic<TIn, TH><<<g1, GTHREADS, 0, a.stream>>>(

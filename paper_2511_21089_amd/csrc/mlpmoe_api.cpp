@@ -139,10 +139,11 @@ int forward_table(const BranchTable &bt, bool aligned, const void *x, const void
         for (int b = 0; b <= bt.B && aligned; ++b) aligned = bt.off[b] % 8 == 0;
     }
     // bf16 tables with odd branch boundaries run on the MFMA kernels too when rows are whole 16-byte pieces (T = 333 on
-    // 896 x 4864, branches of 406 and 405 neurons: 34 us against 701 us on the generic kernels); a forced path keeps its requirements
+    // 896 x 4864, branches of 406 and 405 neurons: 34 us against 701 us on the generic kernels), except for more token rows than those kernels'
+    // grid holds, an error; a forced path keeps its requirements
     bool uneven = false;
     if (path == MLPMOE_PATH_AUTO) {
-        uneven = !aligned && is_bf16 && d_model % 8 == 0 && d_inter % 8 == 0;
+        uneven = !aligned && is_bf16 && d_model % 8 == 0 && d_inter % 8 == 0 && T <= kGenericMaxTokens;
         path = uneven ? MLPMOE_PATH_MFMA
                       : (!aligned ? MLPMOE_PATH_GENERIC : (T <= 16 ? MLPMOE_PATH_DECODE : MLPMOE_PATH_MFMA));
     }
@@ -180,7 +181,7 @@ int forward_table(const BranchTable &bt, bool aligned, const void *x, const void
     // Float storage takes the float MFMA kernels where rows are whole 16-byte pieces (256 tokens on 896 x 4864: 87 us
     // against 1008 us on the generic kernels); routed calls, other row lengths and more token rows than the generic
     // kernels' grid holds (an error there) stay where they were.
-    if (!is_bf16 && !route && d_model % 4 == 0 && d_inter % 4 == 0 && T <= 65535 * 64) {
+    if (!is_bf16 && !route && d_model % 4 == 0 && d_inter % 4 == 0 && T <= kGenericMaxTokens) {
         e = launch_mfma_f32(a, bt);
     } else if (path == MLPMOE_PATH_GENERIC) {
         e = launch_generic(a, bt, is_bf16);

@@ -99,5 +99,18 @@ def short_of_memory():
     assert verbs(record()) == ["refuse"] * 4
 
 
+def most_tokens():
+    """Tables with odd boundaries and float storage end where the generic kernels' grid ends."""
+    most = 65535 * 64
+    widths, on = [3, 5], [1, 0]
+    for f, route in ((lib.mlpmoe_forward_bf16, False), (lib.mlpmoe_forward_bf16_out_bf16, False),
+                     (lib.mlpmoe_forward_routed_bf16, True), (lib.mlpmoe_forward_f32, False)):
+        assert forward(f, most, 8, widths, on, route) == OK
+        assert "gate_up_mfma" in kernels(record())[-2 if not route else 1]
+        assert forward(f, most + 1, 8, widths, on, route) == ERR_HIP
+        assert "invalid argument" in lib.mlpmoe_last_error_detail().decode()
+        assert not kernels(record())
+
+
 globals()[sys.argv[1]]()
 print("ok")
