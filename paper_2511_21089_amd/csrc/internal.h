@@ -113,6 +113,7 @@ hipError_t launch_generic(const FwdArgs &a, const BranchTable &bt, bool is_bf16)
 hipError_t launch_mfma_bf16(const FwdArgs &a, const BranchTable &bt, bool uneven);
 hipError_t launch_mfma_f32(const FwdArgs &a, const BranchTable &bt);
 size_t route_scratch_bytes(int T, int d_inter);
+bool mfma_routed_holds(int d_inter);               // whatever the table
 hipError_t launch_mfma_routed_bf16(const FwdArgs &a, const BranchTable &bt, bool uneven);
 hipError_t launch_decode_bf16(const FwdArgs &a, const BranchTable &bt);
 hipError_t launch_decode_routed_bf16(const FwdArgs &a, const BranchTable &bt);

@@ -1364,6 +1364,9 @@ size_t route_scratch_bytes(int T, int d_inter)
            align_up(groups * route_list_stride(d_inter) * sizeof(uint32_t), 256);
 }
 
+// Every table of this width has few enough N tiles for the tile list.
+bool mfma_routed_holds(int d_inter) { return d_inter / BNH_MAX + kMaxRuns <= ROUTE_MAX_TILES_N; }
+
 size_t mfma_partial_bytes(int T, int d_model, int d_inter)
 {
     // the largest any tile shape asks for
