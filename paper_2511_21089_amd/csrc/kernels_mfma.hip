@@ -534,10 +534,13 @@ __device__ __forceinline__ uint16_t to_bf16(float v)
     return __builtin_bit_cast(uint16_t, b);
 }
 
-// alpha_b * SiLU(g) * u, as the storage type's kernels form it: with expf and a division for float storage
-__device__ __forceinline__ float gated(float alpha, float g, float u, uint16_t) { return alpha * silu_mul(g, u); }
-__device__ __forceinline__ float gated(float alpha, float g, float u, float)
+// alpha_b * SiLU(g) * u.  kExact: with expf and a division, as the general kernels form it, for the calls that these
+// kernels took over from them (float storage, bf16 tables with odd boundaries).  The reciprocal of silu_mul is 0 below
+// the smallest normal float, which loses SiLU(g) for g < -87.3 however large u is.
+template <bool kExact>
+__device__ __forceinline__ float gated(float alpha, float g, float u)
 {
+    if (!kExact) return alpha * silu_mul(g, u);
     const float s = g / (1.0f + expf(-g));
     return alpha * (s * u);
 }
@@ -674,7 +677,7 @@ __device__ __forceinline__ void gate_up_tile(const E *__restrict__ X, const E *_
                 f32x4 h;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    h[q] = gated(a4[q], accg[i][j][q], accu[i][j][q], E{});
+                    h[q] = gated<kEdges || sizeof(E) == 4>(a4[q], accg[i][j][q], accu[i][j][q]);
                     if (kRouted) h[q] = route[(size_t)t * bt.B + bl[nl + q]] ? h[q] : 0.f;
                 }
                 E *dst = H + (size_t)t * ldh + n0 + nl;

@@ -105,3 +105,18 @@ def test_uneven_split_k(mm):
             check_bf16_flip_aware(got, H, *args, label="split K:")
             ref = got
     assert np.all(np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-30)       # one rounding of the same sums
+
+
+def test_uneven_silu_far_tail(mm):
+    """SiLU(-88) = -5.3e-37: 1 / (1 + exp(88)) is below the smallest normal float, the quotient is not.  Such a gate with a large
+    up value counts, on the kernels for odd boundaries as on the general ones."""
+    one = {-88: 0xC2B0, 1: 0x3F80, 2 ** 120: 0x7B80}
+    for T, route in ((1, None), (300, None), (300, 1)):
+        x, Wg, Wu, Wd = (np.zeros(s, np.uint16) for s in ((T, 8), (16, 8), (16, 8), (8, 16)))
+        x[:, 0], Wg[:3, 0], Wu[:3, 0], Wd[:, 0] = one[1], one[-88], one[2 ** 120], one[1]
+        args = (x, Wg, Wu, Wd, np.array([0, 3, 16], np.int32), np.ones(2, np.float32), np.array([1, 0], np.uint8))
+        route = None if route is None else np.ones((T, 2), np.uint8)
+        got, H = run_gpu_with_hidden(*args, route=route)
+        want = -88.0 / (1.0 + np.exp(88.0)) * 2.0 ** 120            # -0.71
+        assert np.all(np.abs(H[:, :3] - want) <= 2.0 ** -8 * abs(want))
+        assert np.array_equal(got, np.repeat(H[:, :1], 8, axis=1))
