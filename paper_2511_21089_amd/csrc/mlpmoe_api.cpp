@@ -140,11 +140,13 @@ int forward_table(const BranchTable &bt, bool aligned, const void *x, const void
     }
     // bf16 tables with odd branch boundaries run on the MFMA kernels too when rows are whole 16-byte pieces (T = 333 on
     // 896 x 4864, branches of 406 and 405 neurons: 34 us against 701 us on the generic kernels), except for more token rows than those kernels'
-    // grid holds, an error, and for routed layers wider than the tile list holds; a forced path keeps its requirements
+    // grid holds, an error, and for routed layers wider than the tile list holds or so small that the tile list's
+    // launch costs more than it saves (8 x 64, T = 1000: 22 us on the generic kernels, 25 us; 128 x 128: 43 and 27 us);
+    // a forced path keeps its requirements
     bool uneven = false;
     if (path == MLPMOE_PATH_AUTO) {
         uneven = !aligned && is_bf16 && d_model % 8 == 0 && d_inter % 8 == 0 && T <= kGenericMaxTokens &&
-                 (!route || mfma_routed_holds(d_inter));
+                 (!route || (d_model + d_inter >= 256 && mfma_routed_holds(d_inter)));
         path = uneven ? MLPMOE_PATH_MFMA
                       : (!aligned ? MLPMOE_PATH_GENERIC : (T <= 16 ? MLPMOE_PATH_DECODE : MLPMOE_PATH_MFMA));
     }

@@ -102,7 +102,7 @@ def short_of_memory():
 def most_tokens():
     """Tables with odd boundaries and float storage end where the generic kernels' grid ends."""
     most = 65535 * 64
-    widths, on = [3, 5], [1, 0]
+    widths, on = [131, 133], [1, 0]
     for f, route in ((lib.mlpmoe_forward_bf16, False), (lib.mlpmoe_forward_bf16_out_bf16, False),
                      (lib.mlpmoe_forward_routed_bf16, True), (lib.mlpmoe_forward_f32, False)):
         assert forward(f, most, 8, widths, on, route) == OK
@@ -120,6 +120,15 @@ def widest_routed():
             widths = [9, 23] * 31 + [width - 31 * 32 - 1, 1]            # a tile of its own for each short run
             assert forward(lib.mlpmoe_forward_routed_bf16, T, 8, widths, on, True) == OK, lib.mlpmoe_last_error_detail()
             assert any(kernel in k for k in kernels(record())), (width, T)
+
+
+def smallest_routed():
+    """Odd boundaries, routed, on the smallest layers: two launches of the generic kernels, not three or four."""
+    for d_model, width, kernel in ((8, 64, "gate_up_generic"), (8, 240, "gate_up_generic"), (8, 248, "gate_up_mfma_routed"),
+                                   (128, 128, "gate_up_mfma_routed")):
+        for T in (1, 1000):
+            assert forward(lib.mlpmoe_forward_routed_bf16, T, d_model, [13, width - 13], None, True) == OK
+            assert any(kernel in k for k in kernels(record())), (d_model, width, T)
 
 
 globals()[sys.argv[1]]()

@@ -112,9 +112,9 @@ def test_uneven_silu_far_tail(mm):
     up value counts, on the kernels for odd boundaries as on the general ones."""
     one = {-88: 0xC2B0, 1: 0x3F80, 2 ** 120: 0x7B80}
     for T, route in ((1, None), (300, None), (300, 1)):
-        x, Wg, Wu, Wd = (np.zeros(s, np.uint16) for s in ((T, 8), (16, 8), (16, 8), (8, 16)))
+        x, Wg, Wu, Wd = (np.zeros(s, np.uint16) for s in ((T, 8), (256, 8), (256, 8), (8, 256)))
         x[:, 0], Wg[:3, 0], Wu[:3, 0], Wd[:, 0] = one[1], one[-88], one[2 ** 120], one[1]
-        args = (x, Wg, Wu, Wd, np.array([0, 3, 16], np.int32), np.ones(2, np.float32), np.array([1, 0], np.uint8))
+        args = (x, Wg, Wu, Wd, np.array([0, 3, 256], np.int32), np.ones(2, np.float32), np.array([1, 0], np.uint8))
         route = None if route is None else np.ones((T, 2), np.uint8)
         got, H = run_gpu_with_hidden(*args, route=route)
         want = -88.0 / (1.0 + np.exp(88.0)) * 2.0 ** 120            # -0.71
