@@ -1294,11 +1294,16 @@ int down_splits(int T, int d_model, int k_elems, TileShape sh)
 // Estimate for a launch of the down projection.  K loops of at most 16 tiles (what a K split of a narrow layer leaves) have
 // their operands in the caches: a K tile takes SLIM 0.44 and DEEP 0.6 us there, the first loads and the stores of a SLIM
 // workgroup 2.5 us and of a pair of SMALL ones 2.2 us each (896 x 4864 at T = 128 .. 600).
+// SLIM without a K split stays below its long-loop estimate up to 32 tiles, 0.45 and 4.0 us, or a layer of
+// 384 to 640 features is split at T >= 1700 where it need not be (448 x 1408, T = 3565: 36.1 us, unsplit 35.0).
 constexpr int SHORT_K_TILES = 16;
-double down_cost_us(long long tiles, int nk, TileShape sh, double bytes)
+double down_cost_us(long long tiles, int splits, int nk, TileShape sh, double bytes)
 {
+    tiles *= splits;
     double c = launch_cost_us(tiles, nk, sh, bytes);
     const double rounds = (double)((tiles + kCUs - 1) / kCUs);
+    if (sh == TILE_SLIM && splits == 1 && nk > SHORT_K_TILES && nk <= 2 * SHORT_K_TILES)
+        return std::max(rounds * (nk * 0.45 + 4.0), bytes / kDeepStreamBytesPerUs + 4.0);
     if (nk > SHORT_K_TILES) return c;
     if (sh == TILE_SLIM) c = std::max(rounds * (nk * 0.44 + 2.5), bytes / kDeepStreamBytesPerUs + 2.5);
     if (sh == TILE_DEEP) c = std::max(rounds * (nk * 0.6 + 4.4), bytes / kDeepStreamBytesPerUs + 4.4);
@@ -1334,7 +1339,7 @@ DownPlan plan_down(const FwdArgs &a, const BranchTable &bt, bool routed)
         for (int sp : {fill, fill / 2}) {
             if (sp < 1 || (sp != fill && (sh != TILE_SMALL || ceil_div(kt, sp) > SHORT_K_TILES))) continue;
             if (sp > 1 && (size_t)sp * a.T * a.d_model * sizeof(float) > a.partial_bytes) sp = 1;
-            const double c = down_cost_us(tiles * sp, ceil_div(kt, sp), sh, 2.0 * bt.d_eff * (a.d_model + a.T)) +
+            const double c = down_cost_us(tiles, sp, ceil_div(kt, sp), sh, 2.0 * bt.d_eff * (a.d_model + a.T)) +
                              reduce_cost_us(sp, (double)a.T * a.d_model);
             if (c < best_cost) {
                 best = DownPlan{sh, sp};

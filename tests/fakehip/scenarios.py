@@ -131,5 +131,13 @@ def smallest_routed():
             assert any(kernel in k for k in kernels(record())), (d_model, width, T)
 
 
+def unsplit_narrow():
+    """Narrow layers with many tokens, 17 to 32 K tiles: the down projection fills the chip unsplit and stays so."""
+    for d_model, d_inter, T, split in ((448, 1408, 3565, False), (320, 1088, 3088, False), (512, 2048, 4096, False),
+                                       (640, 1600, 1684, True)):        # too few tiles: split
+        assert forward(lib.mlpmoe_forward_bf16, T, d_model, [d_inter]) == OK
+        assert any("reduce_partials" in k for k in kernels(record())) == split, (d_model, d_inter, T)
+
+
 globals()[sys.argv[1]]()
 print("ok")
