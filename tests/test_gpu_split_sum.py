@@ -1,6 +1,6 @@
 """The down projection with K split: the sum of 2 to 32 partial results, around one batch of partial sums and around the
-size from which a thread adds two pieces, and the split planned for short K loops.  Against a float64 product of the
-stored intermediate; the bf16 result is the float one rounded once."""
+size from which a thread adds two pieces (its second piece past the end included), and the split planned for short K
+loops.  Against a float64 product of the stored intermediate; the bf16 result is the float one rounded once."""
 import numpy as np
 import pytest
 
@@ -10,15 +10,28 @@ from paper_2511_21089_amd import synth
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(scope="module")
+def mm():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2511_21089_amd import binding
+    return binding
+
+
 @pytest.mark.parametrize("T,d_model,d_inter", [
-    (17, 64, 8 * 64), (33, 72, 32 * 64), (100, 136, 36 * 64), (50, 64, 40 * 64), (20, 128, 130 * 64),   # 2 .. 32 splits
+    (1500, 512, 16 * 64), (17, 64, 12 * 64), (33, 72, 32 * 64), (100, 136, 36 * 64), (50, 64, 64 * 64),  # 2, 3, 8, 9,
+    (20, 128, 130 * 64),                                                                 # 16 and 32 splits
     (128, 896, 4864), (333, 896, 3656), (600, 896, 4864), (150, 2048, 2048),                             # short K loops
-    (2047, 512, 1024), (2048, 512, 1024), (2049, 512, 1024)])                                            # around 2^18 pieces
-def test_split_sum(T, d_model, d_inter):
+    (2047, 512, 1024), (2048, 512, 1024), (2049, 512, 2048), (1031, 1032, 2048)])                        # around 2^18 pieces
+def test_split_sum(mm, T, d_model, d_inter):
     rng = np.random.default_rng(T + d_inter)
     x, Wg, Wu, Wd = synth.random_layer(rng, T, d_model, d_inter, dtype="bf16", w_scale=0.05)
     args = (x, Wg, Wu, Wd, np.array([0, d_inter], np.int32), np.ones(1, np.float32), np.ones(1, np.uint8))
+    mm.mlpmoe_profile_enable(16)
     got, H = run_gpu_with_hidden(*args)
+    kernels = [name for name, _ in mm.mlpmoe_profile_collect(16)]
+    mm.mlpmoe_profile_disable()
+    assert "splitk_reduce" in kernels                    # this size is still split
     W = widen(Wd).astype(np.float64)
     bound = C_SUM * U24 * (np.abs(H) @ np.abs(W).T) + 1e-30
     assert np.all(np.abs(got - H @ W.T) <= bound)
