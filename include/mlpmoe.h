@@ -63,8 +63,10 @@ enum {
 
 /* Kernel path selection for the *_ws entry points. */
 enum {
-    MLPMOE_PATH_AUTO = 0,    /* library picks: decode for T <= 16, MFMA otherwise and for odd branch boundaries,
-                              * generic if d_model or d_inter is not a multiple of 8                    */
+    MLPMOE_PATH_AUTO = 0,    /* library picks.  bf16: decode for T <= 16, MFMA otherwise and for branch boundaries
+                              * off a multiple of 8, generic if d_model or d_inter is not a multiple of 8.
+                              * Float storage (always AUTO): float MFMA, generic if d_model or d_inter is not
+                              * a multiple of 4 and for routed calls                                       */
     MLPMOE_PATH_GENERIC = 1, /* LDS-tiled FMA kernels: any shape and alignment                        */
     MLPMOE_PATH_MFMA = 2,    /* bf16 MFMA prefill kernels (needs d_model%8==0 and offsets%8==0)       */
     MLPMOE_PATH_DECODE = 3,  /* weight-streaming kernels, T <= 16 (same alignment needs as MFMA)      */
@@ -152,7 +154,9 @@ MLPMOE_API int mlpmoe_compact(const void *W_gate, const void *W_up, const void *
  * Bytes of device workspace a forward call with these sizes may use (gated
  * intermediate H[T, d_inter], split-K partial sums, and the tile tables of the
  * routed forward).  Independent of the branch table.  Returns 0 for invalid sizes.  Float storage
- * also runs in a block without room for the partial sums (less parallel).
+ * also runs in a block without room for the partial sums: the same result bits, less parallel (896 x
+ * 4864, T = 256: 161 us against 86 us).  Its need is not monotone in T: the partial sums of a smaller
+ * T can be larger.
  */
 MLPMOE_API size_t mlpmoe_workspace_bytes(int T, int d_model, int d_inter, int B, int elem_bytes);
 
@@ -161,9 +165,12 @@ MLPMOE_API size_t mlpmoe_workspace_bytes(int T, int d_model, int d_inter, int B,
  *
  *   x, W_gate, W_up, W_down   device, bf16, layouts above, 16-byte aligned bases.
  *   branch_offsets [B+1], alpha [B], active_mask [B]   host.  active_mask[b] == 0:
- *       branch b contributes nothing and none of its weights are read (non-finite
- *       values inside it cannot reach out).  alpha_b == 0 with the mask set is
- *       computed like any other value.
+ *       branch b contributes nothing: no value of its weights, non-finite ones included, reaches out.
+ *       None of them are read where the boundaries beside it are multiples of 8 (float: 4) and d_model
+ *       and d_inter are too.  Otherwise the rest of a 16-byte piece that such a boundary cuts may be read
+ *       and dropped (rows of W_gate / W_up, columns of W_down), as may the first piece of a W_down row
+ *       and, by the generic kernels, the rest of a tile of 64 rows of W_gate / W_up.
+ *       alpha_b == 0 with the mask set is computed like any other value.
  *   T >= 0 tokens (T == 0 is a no-op), d_model >= 1, d_inter = branch_offsets[B] >= 0,
  *   1 <= B <= MLPMOE_MAX_BRANCHES.  d_b == 0 is legal.
  *   out    device float [T, d_model]; every element is written (zeros if nothing is active).
@@ -171,15 +178,17 @@ MLPMOE_API size_t mlpmoe_workspace_bytes(int T, int d_model, int d_inter, int B,
  * Arithmetic: gate and up products accumulate in fp32; h = alpha_b * SiLU(g) * u is
  * formed in fp32 and rounded ONCE to bf16 (nearest even); the down projection
  * accumulates those bf16 values against W_down in fp32 across all branches.
- * Results are bitwise reproducible from run to run: sums are formed in a fixed order; the one place
+ * Results are bitwise reproducible from run to run, and do not depend on the workspace: sums are formed
+ * in an order that follows from the sizes (T among them), the table and the path; the one place
  * that uses floating-point atomics (the decode down projection of wide layers) adds exactly two
  * partial sums into a zero, which gives the same number in either order.
  *
  * Workspace: the block given to mlpmoe_set_workspace() for the current device if there is
  * one -- the call then never allocates and returns MLPMOE_ERR_WORKSPACE if the block is too
  * small.  Otherwise a per-device buffer the library owns and grows with hipMalloc when a call
- * needs more than any earlier one (that growth synchronises the device; while `stream` is
- * recording a graph it is refused with MLPMOE_ERR_WORKSPACE instead).  Either way all calls
+ * cannot run in what earlier ones left (that growth synchronises the device; while `stream` is
+ * recording a graph it is refused with MLPMOE_ERR_WORKSPACE instead).  A float call can run without
+ * room for its partial sums (mlpmoe_workspace_bytes) and never replaces a block for them.  Either way all calls
  * of this kind on one device share one block: calls that overlap in time on one device
  * (different streams) must use the *_ws form with distinct workspaces.
  *
@@ -197,7 +206,8 @@ MLPMOE_API int mlpmoe_forward(const void *x, const void *W_gate, const void *W_u
 
 /*
  * mlpmoe_forward_f32 -- same operation for float x and weights; no intermediate
- * rounding, fp32 accumulation throughout (LDS-tiled FMA kernels, any shape).
+ * rounding, fp32 accumulation throughout (float matrix instructions where d_model and
+ * d_inter are multiples of 4, LDS-tiled FMA kernels otherwise).
  */
 MLPMOE_API int mlpmoe_forward_f32(const float *x, const float *W_gate, const float *W_up, const float *W_down,
                        const int32_t *branch_offsets, const float *alpha,
@@ -250,7 +260,8 @@ MLPMOE_API int mlpmoe_forward_bf16_noalloc(const void *x, const void *W_gate, co
  * mlpmoe_forward_bf16, mlpmoe_forward_f32, mlpmoe_forward_bf16_out_bf16, mlpmoe_forward_routed_*)
  * a caller-owned device block to work in on the CURRENT device, e.g. a PyTorch tensor.  From then
  * on those calls allocate nothing and synchronise nothing on that device: a call that needs more
- * than `bytes` (mlpmoe_workspace_bytes) returns MLPMOE_ERR_WORKSPACE.  dev_ptr: device, 256-byte
+ * than `bytes` (mlpmoe_workspace_bytes; float calls: without the partial sums) returns
+ * MLPMOE_ERR_WORKSPACE.  dev_ptr: device, 256-byte
  * aligned, owned by the caller, who keeps it alive until it is replaced or cleared and all work
  * enqueued with it has finished; its contents are scratch.  dev_ptr == NULL clears the setting
  * (back to the library-owned buffer).  Errors: WORKSPACE (misaligned, or bytes == 0), HIP.
@@ -268,7 +279,8 @@ MLPMOE_API int mlpmoe_hidden_ld(int d_inter);
 
 /*
  * Caller-owned workspace forms.  workspace: device pointer, 256-byte aligned, at
- * least mlpmoe_workspace_bytes(T, d_model, d_inter, B, elem_bytes) bytes; its
+ * least mlpmoe_workspace_bytes(T, d_model, d_inter, B, elem_bytes) bytes (float
+ * calls also take a block without room for the partial sums); its
  * contents are scratch.  path: one of MLPMOE_PATH_*; a path that cannot run the
  * given arguments returns MLPMOE_ERR_UNSUPPORTED and enqueues nothing.
  * These calls never allocate device memory.
@@ -295,7 +307,8 @@ MLPMOE_API int mlpmoe_forward_f32_ws(const float *x, const float *W_gate, const 
  * When d_model and d_inter are multiples of 8 the kernels skip work per (tile of 256 tokens, branch) pair
  * that no token of the tile is routed to -- for T <= 16 and branch offsets that are all multiples of 8
  * (mlpmoe_slice with pad_to = 8) per branch no token takes, whose weights are then never read -- so tokens
- * grouped by route make the call proportionally cheaper; other tables take the generic kernels, which only mask.
+ * grouped by route make the call proportionally cheaper.  Other sizes take the generic kernels, which only mask;
+ * so do branch offsets off a multiple of 8 where d_model + d_inter < 256 or d_inter >= 2^22 - 2^12.
  * The _ws form takes a caller-owned workspace of mlpmoe_workspace_bytes() bytes and never allocates.
  */
 MLPMOE_API int mlpmoe_forward_routed_bf16(const void *x, const void *W_gate, const void *W_up,
@@ -310,7 +323,8 @@ MLPMOE_API int mlpmoe_forward_routed_bf16_ws(const void *x, const void *W_gate, 
 
 /*
  * The routed forward for float x and weights: same reading of the routing, no intermediate rounding,
- * fp32 accumulation throughout (the LDS-tiled FMA kernels; they mask and do not skip).  The _ws form
+ * fp32 accumulation throughout (the LDS-tiled FMA kernels; they mask and do not skip, and add in another
+ * order than mlpmoe_forward_f32's).  The _ws form
  * takes mlpmoe_workspace_bytes(T, d_model, d_inter, B, 4) bytes.
  */
 MLPMOE_API int mlpmoe_forward_routed_f32(const float *x, const float *W_gate, const float *W_up,
@@ -344,7 +358,7 @@ MLPMOE_API int mlpmoe_forward_routed_f32_ws(const float *x, const float *W_gate,
  *                   rounded to float (NaN for branches left alone)
  *   kept            host, 2 * B 64-bit counts or NULL: entries of the block that survive
  *                   (the block size for branches left alone)
- * Allocates and frees a device scratch buffer of B * 131088 bytes (bf16) or B * 655424 bytes (float)
+ * Allocates and frees a device scratch buffer of B * 262176 bytes (bf16) or B * 655424 bytes (float)
  * and synchronises `stream` before it returns, for float storage also once in between (this is
  * offline weight preparation, not part of the forward).
  * Not-a-number entries are not supported (their place in the order is undefined).
@@ -413,7 +427,8 @@ MLPMOE_API int mlpmoe_profile_disable(void);
  *
  *   mlpmoe_plan_create   branch_offsets / alpha / active_mask / sizes as for mlpmoe_forward (host
  *                        arrays, copied); elem_bytes 2 (bf16) or 4 (float); max_T >= 1.  Allocates the
- *                        workspace on the current device.  *plan is NULL on failure.
+ *                        workspace on the current device (for float storage without the partial sums
+ *                        if there is no memory for them).  *plan is NULL on failure.
  *   mlpmoe_plan_forward  x [T, d_model], weights and out [T, d_model] float: device pointers, 16-byte
  *                        aligned, same layouts as mlpmoe_forward; 0 <= T <= max_T (MLPMOE_ERR_SHAPE
  *                        otherwise); launches on `stream`.  Calls that share a plan share its workspace:

@@ -1,6 +1,7 @@
 // Generic path: LDS-tiled FMA kernels that accept any shape and alignment.
 // Serves calls whose d_model or d_inter is not a multiple of 8 (bf16) or 4 (float),
-// and the routed float form.  Also holds the zero-fill and weight-compaction kernels.
+// the routed float form, and routed bf16 calls with odd branch boundaries on the smallest
+// and the widest layers.  Also holds the zero-fill and weight-compaction kernels.
 //
 // Step 1 (Sec. 3.1, inner bracket):  H[t,j] = alpha_b(j) * SiLU(<x_t, Wg_j>) * <x_t, Wu_j>
 // Step 2 (Sec. 3.1, outer product and sum over b):  out[t,m] = sum_{j active} H[t,j] * Wd[m,j]

@@ -437,7 +437,7 @@ __device__ __forceinline__ void mainloop(const E *__restrict__ A_tile, int lda, 
 // are added by edge_steps below: they go from global memory straight into MFMA operand registers, inactive K
 // elements masked to 0 in BOTH operands (nothing of a pruned branch reaches the sum, non-finite values included).
 // What bounds it: one global load latency per four chunks at the end of a tile.  896 x 4864 in 12 branches of 406 / 405
-// neurons, first 9 kept, T = 333: 34 us against 701 us for the general FMA kernels.
+// neurons, first 9 kept, T = 333: 29 us against 703 us for the general FMA kernels.
 constexpr int kMaxEdges = 2 * kMaxRuns;
 struct EdgeList {
     int n;
@@ -645,8 +645,9 @@ __device__ __forceinline__ void gate_up_tile(const E *__restrict__ X, const E *_
                        lds, accg, accu);
 
     // alpha of the tile's neurons -> LDS (the main loop is done with it), from the table in the lanes: a search through
-    // the kernel arguments at this point was a chain of loads with nothing to hide it (4096 x 14336, T = 100: the call 91.3 ->
-    // 85.8 us; 896 x 4864, 9 of 12 branches, T = 333: 34.0 -> 30.4 us; in float, T = 256: 86.4 -> 84.6 us)
+    // the kernel arguments at this point was a chain of loads with nothing to hide it (896 x 4864, 9 of 12 branches, T = 333:
+    // the call 34.0 -> 30.4 us; in float, T = 256: 86.4 -> 84.6 us; 4096 x 14336, T = 100, with the batched sum of partial
+    // results: 93.2 -> 89.8 us)
     float *al = reinterpret_cast<float *>(lds);
     int *bl = reinterpret_cast<int *>(lds + BNH_MAX * sizeof(float));      // branch of each neuron (routing)
     int *on = reinterpret_cast<int *>(lds + 2 * BNH_MAX * sizeof(float));  // neuron in an active branch (kEdges)
@@ -1202,7 +1203,7 @@ using ShapeSlim = ShapeT<BM_SLIM, SLIM_WM, 2, SLIM_D, true>;
 // float MFMA rate (v_mfma_f32_16x16x4_f32, 256 flop per clock and CU, a sixteenth of bf16's), which this small a tile
 // already reaches: it asks the L2 for 16 bytes per clock and CU while the matrix pipe is busy, of about 40 available,
 // and small tiles fill the chip at the sizes float storage is used for (4864 neurons and 256 tokens are 608 tiles; the
-// 128 x (64 + 64) tile would make 152).  The layer at T = 256: 87 us against 1008 us on the general FMA kernels, error
+// 128 x (64 + 64) tile would make 152).  The layer at T = 256: 84 us against 1007 us on the general FMA kernels, error
 // against float64 1.0e-6 against 1.5e-6 (rel.).
 using ShapeF32 = ShapeT<64, 2, 1, 2, false>;
 struct TileDims {
@@ -1293,7 +1294,9 @@ int down_splits(int T, int d_model, int k_elems, TileShape sh)
 
 // Estimate for a launch of the down projection.  K loops of at most 16 tiles (what a K split of a narrow layer leaves) have
 // their operands in the caches: a K tile takes SLIM 0.44 and DEEP 0.6 us there, the first loads and the stores of a SLIM
-// workgroup 2.5 us and of a pair of SMALL ones 2.2 us each (896 x 4864 at T = 128 .. 600).
+// workgroup 2.5 us and of a pair of SMALL ones 2.2 us each (896 x 4864 at T = 128 .. 600).  Checked on 260 drawn layers of
+// 384 .. 4096 features at T = 17 .. 4096, side by side with the estimate for long loops alone: the call 1.13 times faster
+// in the mean with the batched sum, none slower by more than the runs of one side differ.
 // SLIM without a K split stays below its long-loop estimate up to 32 tiles, 0.45 and 4.0 us, or a layer of
 // 384 to 640 features is split at T >= 1700 where it need not be (448 x 1408, T = 3565: 36.1 us, unsplit 35.0).
 constexpr int SHORT_K_TILES = 16;

@@ -106,7 +106,7 @@ size_t h_bytes(int T, int d_inter, int elem_bytes)
 }
 
 // The least workspace a call runs in.  Float storage only gains speed from the partial sums of a K split: a block
-// without room for them is accepted.
+// without room for them is accepted (and gives the same result).
 size_t min_workspace_bytes(int T, int d_model, int d_inter, int B, int elem)
 {
     const size_t full = mlpmoe_workspace_bytes(T, d_model, d_inter, B, elem);
@@ -116,8 +116,9 @@ size_t min_workspace_bytes(int T, int d_model, int d_inter, int B, int elem)
 // Dispatch with a ready branch table: path choice, workspace carving, launch.  No loops over
 // branches, no allocation, no synchronisation.
 // route: per-token routing [T, B] on the device, or nullptr.  Routed calls use the kernels that skip
-// (token tile, branch) pairs nobody is routed to when d_model and d_inter are multiples of 8,
-// and the generic kernels (masking only) otherwise.
+// (token tile, branch) pairs nobody is routed to when d_model and d_inter are multiples of 8
+// (with odd branch boundaries not on the smallest and the widest layers, below), and the generic
+// kernels (masking only) otherwise.
 int forward_table(const BranchTable &bt, bool aligned, const void *x, const void *Wg, const void *Wu,
                   const void *Wd, int T, int d_model, int d_inter, float *out, void *workspace,
                   size_t workspace_bytes, int path, bool is_bf16, hipStream_t stream,
@@ -139,7 +140,7 @@ int forward_table(const BranchTable &bt, bool aligned, const void *x, const void
         for (int b = 0; b <= bt.B && aligned; ++b) aligned = bt.off[b] % 8 == 0;
     }
     // bf16 tables with odd branch boundaries run on the MFMA kernels too when rows are whole 16-byte pieces (T = 333 on
-    // 896 x 4864, branches of 406 and 405 neurons: 34 us against 701 us on the generic kernels), except for more token rows than those kernels'
+    // 896 x 4864, branches of 406 and 405 neurons: 29 us against 703 us on the generic kernels), except for more token rows than those kernels'
     // grid holds, an error, and for routed layers wider than the tile list holds or so small that the tile list's
     // launch costs more than it saves (8 x 64, T = 1000: 22 us on the generic kernels, 25 us; 128 x 128: 43 and 27 us);
     // a forced path keeps its requirements
@@ -181,8 +182,8 @@ int forward_table(const BranchTable &bt, bool aligned, const void *x, const void
     a.route_scratch = reinterpret_cast<uint8_t *>(static_cast<char *>(workspace) + need - route_scratch_bytes(T, d_inter));
 
     hipError_t e;
-    // Float storage takes the float MFMA kernels where rows are whole 16-byte pieces (256 tokens on 896 x 4864: 87 us
-    // against 1008 us on the generic kernels); routed calls, other row lengths and more token rows than the generic
+    // Float storage takes the float MFMA kernels where rows are whole 16-byte pieces (256 tokens on 896 x 4864: 84 us
+    // against 1007 us on the generic kernels); routed calls, other row lengths and more token rows than the generic
     // kernels' grid holds (an error there) stay where they were.
     if (!is_bf16 && !route && d_model % 4 == 0 && d_inter % 4 == 0 && T <= kGenericMaxTokens) {
         e = launch_mfma_f32(a, bt);
