@@ -266,17 +266,14 @@ decode_kernel(const uint16_t *__restrict__ Xin, int ldx, int T,
     }
 }
 
-// Down projection with RT row tiles (16 RT output features) per workgroup and the K blocks dealt to TWO
-// workgroups (blockIdx.y).  Layers with many output features take RT = 2:  Every workgroup of the one-tile
+// Down projection of wide layers with RT row tiles (16 RT output features) per workgroup and the K blocks dealt to TWO
+// workgroups (blockIdx.y).  Every workgroup of the one-tile
 // kernel reads all of H, which at 16 tokens is as many bytes as its weight rows, all from the same
 // L2; here a block of H is used for two weight fragments and each workgroup reads half of H, a quarter
 // of that traffic per weight byte, with all CUs still busy.  The two partial sums of an output are
 // added into `out` with float atomics: out must hold zeros when the kernel starts (the gate+up
 // kernel that runs before it clears it), and 0 + a + b is the same number in either order, so the
-// result does not depend on which workgroup comes first.
-// Narrow layers (few output features) take RT = 1 with 16 waves: twice the workgroups of the one-tile kernel,
-// and a wave's share of K short enough for its ring to hold all of it, so every weight byte is requested
-// as the kernel starts.
+// result does not depend on which workgroup comes first.  Few output features or few tokens: decode_down_rows.
 template <int NW, int U, int RT, bool kRouted = false>
 __global__ void __launch_bounds__(NW * 64)
 decode_down_split(const uint16_t *__restrict__ Hin, int ldx, int T, const uint16_t *__restrict__ Wd, int ldw,
@@ -381,7 +378,7 @@ decode_down_split(const uint16_t *__restrict__ Hin, int ldx, int T, const uint16
     }
 }
 
-// Sets n floats to 0 for the kernel that follows (decode_down_split); p may be null.  Called once the first weights are
+// Sets n floats to 0 for the down kernel that follows, which adds into them; p may be null.  Called once the first weights are
 // requested: loads wait for the stores before them.
 __device__ __forceinline__ void clear_floats(float *__restrict__ p, int n, int threads, int grid)
 {
@@ -639,9 +636,276 @@ decode_gate_up_xreg(const uint16_t *__restrict__ X, int T, const uint16_t *__res
     }
 }
 
+// ---- narrow layers and small batches ---------------------------------------------------------------
+// What bounds them is what a CU's memory path carries and how soon it starts, not HBM: about 40 bytes per clock and CU,
+// for lines that come from the L2 and for lanes that read the zero chunk alike.  A ring kernel on 896 x 4864 moves
+// 288 KB per CU for 68 KB of W_gate and W_up, the rest being slots past the last tile, K blocks past d_model and token
+// columns past T; its down kernel has 112 workgroups with as many loads of H as of W_down.  The kernels below ask for
+// weights once, all of them as the kernel starts, and for nothing else: lanes without a token read past the end of a
+// buffer, which costs no traffic, and there is a workgroup for every small tile, so that all CUs are busy.
+//
+// A tile has 8 (or 4) rows, not 16.  Operand lane l of v_mfma_f32_16x16x32_bf16 holds row l & 15 and K group l >> 4, and
+// here rows 8 .. 15 are rows 0 .. 7 again at the next 32 K elements: one load takes whole 128-byte lines of 8 rows.  With at
+// most 8 tokens the columns 8 .. 15 are the tokens again, at those same K elements, so that one MFMA does both halves: the
+// two diagonal blocks of the result are the two partial sums, what is off the diagonal is never used.  With more tokens
+// each half has an MFMA and an operand of its own (NG = K groups per MFMA, CT = token columns).
+
+// 16-byte loads of at most 2^31 bytes from `base`: lanes without anything to load (!ok) read zeros from past the end.
+struct Window {
+    __amdgpu_buffer_rsrc_t rsrc;
+    __device__ __forceinline__ Window(const void *base, unsigned bytes)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00027000)) {}
+    __device__ __forceinline__ u32x4 ld16(bool ok, unsigned offset) const
+    {
+        return __builtin_amdgcn_raw_buffer_load_b128(rsrc, ok ? offset : 0xffffffffu, 0, 0);
+    }
+};
+
+constexpr int RED_V = 64 + 4, RED_W = 4 * RED_V + 8;     // partial sums in LDS: strides of a register and of a wave (floats)
+
+// Gate+up projection, one workgroup per tile of 8 neurons; wave w takes the K blocks w, w + NW, ..., at most XB of them.
+// 896 x 4864 with the ring kernel replaced by this one alone: T = 1 15.9 -> 14.6 us a step, T = 8 16.8 -> 15.8 us,
+// T = 16 17.9 -> 17.5 us.  Every workgroup loads all of x, which is why wide layers and batches keep the ring kernel (see
+// gate_up_once).  Two tiles per workgroup (half of the x loads): 15.6, 16.7 and 18.3 us; one workgroup per CU with x in
+// registers and 4-neuron tiles: 0.5 to 1 us slower than this as well.
+template <int NW, int XB, int NG, bool kRouted>
+__global__ void __launch_bounds__(NW * 64)
+decode_gate_up_once(const uint16_t *__restrict__ X, int T, const uint16_t *__restrict__ Wg,
+                    const uint16_t *__restrict__ Wu, int d_model, uint16_t *__restrict__ Hout, int ldh,
+                    const uint8_t *__restrict__ route, float *__restrict__ clear, int clear_n, int grid, BranchTable bt)
+{
+    constexpr int NM = 2 / NG, CT = 16 / NG;
+    constexpr int PARTS = NW * 64 / (8 * CT) < NW ? NW * 64 / (8 * CT) : NW;     // lanes that add up one output
+    __shared__ float red[2][NW * RED_W];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r16 = lane & 15, q = lane >> 4;
+    Stretches<kRouted> st(bt, route, T);
+    const BranchLanes br(bt);
+    arrived(st.v_beg, st.v_end);
+    const int row0 = TileCursor<kRouted>(st, blockIdx.x).row0(st);
+    if (row0 < 0) {                                      // with routing the grid covers all active rows
+        clear_floats(clear, clear_n, NW * 64, grid);
+        return;
+    }
+    const uint16_t *zero = reinterpret_cast<const uint16_t *>(g_zero16);
+    const int chunk = (q + 4 * (r16 >> 3)) * 8;          // this lane's K elements of a block
+    const size_t w_off = (size_t)(row0 + (r16 & 7)) * d_model + chunk;
+    const Window x(X, (unsigned)T * (unsigned)d_model * 2u);
+    const bool tok = r16 % CT < T;
+    const int x_k = NG == 2 ? chunk : q * 8;
+    const unsigned x_lane = ((unsigned)(r16 % CT) * (unsigned)d_model + x_k) * 2u;
+    u32x4 wg[XB], wu[XB], xa[XB][NM];
+#pragma unroll
+    for (int j = 0; j < XB; ++j) {
+        const int k = (wave + NW * j) * KB;
+        wg[j] = ld16(k + chunk < d_model ? Wg + w_off + k : zero);
+        wu[j] = ld16(k + chunk < d_model ? Wu + w_off + k : zero);
+#pragma unroll
+        for (int i = 0; i < NM; ++i)
+            xa[j][i] = x.ld16(tok && k + 32 * i + x_k < d_model, x_lane + (k + 32 * i) * 2);
+    }
+    clear_floats(clear, clear_n, NW * 64, grid);
+    f32x4 ag[NM], au[NM];
+#pragma unroll
+    for (int i = 0; i < NM; ++i) ag[i] = au[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < XB; ++j)
+#pragma unroll
+        for (int i = 0; i < NM; ++i) {
+            ag[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wg[j]), as_bf16x8(xa[j][i]), ag[i], 0, 0, 0);
+            au[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wu[j]), as_bf16x8(xa[j][i]), au[i], 0, 0, 0);
+        }
+    // register v of lane l is D[row 4 q + v][col r16]: neuron (4 q + v) % 8, K half q / 2; its columns are those of that half
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        red[0][wave * RED_W + v * RED_V + lane] = NM == 2 && q >= 2 ? ag[NM - 1][v] : ag[0][v];
+        red[1][wave * RED_W + v * RED_V + lane] = NM == 2 && q >= 2 ? au[NM - 1][v] : au[0][v];
+    }
+    __syncthreads();
+    // PARTS lanes per output, the neurons of a token side by side: fixed order of the sum
+    const int p = lane % PARTS, o = threadIdx.x / PARTS, t = o / 8, row = o % 8;
+    float g = 0.f, up = 0.f;
+#pragma unroll
+    for (int i = 0; i < NW / PARTS; ++i)
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const int at = (p * (NW / PARTS) + i) * RED_W + row % 4 * RED_V + (row / 4 + 2 * half) * 16 +
+                           (NG == 2 ? 8 * half : 0) + t % CT;
+            g += red[0][at];
+            up += red[1][at];
+        }
+#pragma unroll
+    for (int d = 1; d < PARTS; d <<= 1) {
+        g += __shfl_xor(g, d);
+        up += __shfl_xor(up, d);
+    }
+    int bn = br.branch(row0);                            // the tile may span branches: only a run's ends are multiples of 8
+    for (int i = bn, next; (next = br.next(i)) <= row0 + 7; ++i) bn += next <= row0 + row ? 1 : 0;
+    const float alpha = __shfl(br.v_alpha, bn);
+    if (p != 0 || t >= T || t >= CT) return;
+    float h = alpha * silu_mul(g, up);
+    if (kRouted) h = route[(size_t)t * bt.B + bn] ? h : 0.f;
+    Hout[(size_t)t * ldh + row0 + row] = to_bf16(h);
+}
+
+// Down projection, one workgroup per R output features and 1 / KS of the K blocks (blockIdx.y); its waves take the blocks
+// of SB elements in turn.  KS = 2: the two sums of an output are added into `out` by float atomics, which the gate+up
+// kernel before has cleared: 0 + a + b is the same number in either order.  KS = 1: plain stores, float or bf16.
+// Fewer rows per workgroup keep more CUs busy and cost more loads of H per weight byte (CT / R of them): see down_shape.
+template <int NW, int U, int R, int NG, int KS, bool kRouted>
+__global__ void __launch_bounds__(NW * 64)
+decode_down_rows(const uint16_t *__restrict__ Hin, int ldx, int T, const uint16_t *__restrict__ Wd, int ldw,
+                 int d_model, float *__restrict__ out, int out_bf16, const uint8_t *__restrict__ route, BranchTable bt)
+{
+    constexpr int KG = 16 / R, NM = KG / NG, CT = 16 / NG, SB = 32 * KG;
+    constexpr int PARTS = NW * 64 / (R * CT) < NW ? NW * 64 / (R * CT) : NW;
+    static_assert(KG % NG == 0 && PARTS >= 1, "K groups per MFMA; a thread for every output");
+    __shared__ float red[NW * RED_W];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r16 = lane & 15, q = lane >> 4;
+    Stretches<kRouted> st(bt, route, T);
+    arrived(st.v_beg, st.v_end);
+    const int row0 = blockIdx.x * R;
+    const int rows = d_model - row0 < R ? d_model - row0 : R;
+    const Window w(Wd + (size_t)row0 * ldw, (unsigned)rows * (unsigned)ldw * 2u);
+    const Window h(Hin, (unsigned)T * (unsigned)ldx * 2u);
+    const int chunk = (q + 4 * (r16 / R)) * 8;           // this lane's K elements of a block
+    const bool row_ok = r16 % R < rows, tok = r16 % CT < T;
+    const unsigned w_lane = (unsigned)(r16 % R) * (unsigned)ldw * 2u;
+    const unsigned h_lane = (unsigned)(r16 % CT) * (unsigned)ldx * 2u;
+
+    // cursor over this wave's blocks: the blocks of all stretches laid end to end, cut into KS contiguous parts
+    int nb_all = 0;
+    for (int r = 0; r < st.count(); ++r) nb_all += (st.end(r) - st.beg(r) + SB - 1) / SB;
+    const int part = (nb_all + KS - 1) / KS;
+    const int first = (int)blockIdx.y * part + wave;
+    const int last = (int)(blockIdx.y + 1) * part < nb_all ? (int)(blockIdx.y + 1) * part : nb_all;
+    const int total = last > first ? (last - first + NW - 1) / NW : 0;
+    int cr = 0, cb = first, issued = 0;
+    auto settle = [&]() {                                // move past stretches the block index overshoots
+        while (cr < st.count()) {
+            const int nb = (st.end(cr) - st.beg(cr) + SB - 1) / SB;
+            if (cb < nb) break;
+            cb -= nb;
+            ++cr;
+        }
+    };
+    settle();
+    u32x4 wa[U], xa[U][NM];
+    auto load = [&](int u) {                             // the block under the cursor, zeros past this wave's last
+        const bool live = cr < st.count() && issued < total;
+        ++issued;
+        const int k = live ? st.beg(cr) + cb * SB : 0;
+        const int kend = live ? st.end(cr) : -1;
+        wa[u] = w.ld16(row_ok && k + chunk < kend, w_lane + (k + chunk) * 2);
+#pragma unroll
+        for (int i = 0; i < NM; ++i) {
+            const int kx = k + (q + 4 * (i * NG + r16 / CT)) * 8;
+            xa[u][i] = h.ld16(tok && kx < kend, h_lane + kx * 2);
+        }
+        cb += NW;
+        settle();
+    };
+    f32x4 acc[NM];
+#pragma unroll
+    for (int i = 0; i < NM; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < U; ++u) load(u);
+    for (int j = 0; j < total; j += U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int i = 0; i < NM; ++i)
+                acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wa[u]), as_bf16x8(xa[u][i]), acc[i], 0, 0, 0);
+            if (j + U < total) load(u);
+        }
+    }
+    // register v of lane l is D[row 4 q + v][col r16]: K group (4 q) / R, whose columns are r16 / CT == group % NG
+    const int group = 4 * q / R;
+    f32x4 mine = acc[0];
+#pragma unroll
+    for (int i = 1; i < NM; ++i) mine = group / NG == i ? acc[i] : mine;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[wave * RED_W + v * RED_V + lane] = mine[v];
+    __syncthreads();
+    // PARTS lanes per output, the features of a token side by side (coalesced stores and atomics): fixed order of the sum
+    const int p = lane % PARTS, o = threadIdx.x / PARTS, t = o / R, row = o % R;
+    float sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < NW / PARTS; ++i)
+#pragma unroll
+        for (int g = 0; g < KG; ++g) {
+            const int d = g * R + row;
+            sum += red[(p * (NW / PARTS) + i) * RED_W + d % 4 * RED_V + d / 4 * 16 + g % NG * CT + t % CT];
+        }
+#pragma unroll
+    for (int d = 1; d < PARTS; d <<= 1) sum += __shfl_xor(sum, d);
+    if (p != 0 || t >= T || t >= CT || row >= rows) return;
+    const size_t at = (size_t)t * d_model + row0 + row;
+    if (KS == 2) atomicAdd(&out[at], sum);
+    else if (out_bf16) reinterpret_cast<uint16_t *>(out)[at] = to_bf16(sum);
+    else out[at] = sum;
+}
+
+// The one-tile workgroups load x (2 T d_model bytes) once per 8 neurons (32 d_model bytes of weights).  Against the
+// ring kernel, us a step at T = 1, 8, 16: 640 features 11.4 / - / 11.9 (12.2 / - / 12.6), 896 14.6 / 15.8 / 17.5 (15.9 /
+// 16.8 / 17.9), 1280 15.5 / 16.9 / 19.5 (17.3 / 18.0 / 19.2), 1536 20.5 / 22.8 / 27.6 (22.4 / 23.2 / 24.9), 2048 25.4 / 28.0
+// / 32.1 (25.3 / 26.2 / 28.0).
+constexpr int ONCE_MAX_D = 1536, ONCE_NW = 4;
+bool gate_up_once(int T, int d_model) { return d_model <= ONCE_MAX_D && T * d_model <= 14336; }
+
+// Rows per workgroup of decode_down_rows, 0: the kernels for wide layers.  us a step with 4 / 8 / 16 rows and with the
+// wide kernels, the gate+up ring kernel before it.
+//   float (two workgroups per row tile with 8 and 16 rows, one with 4):
+//     896 T = 1 12.9 / 12.9 / 14.3 / 15.9, T = 16 16.8 / 14.8 / 16.7 / 17.9;  1280 T = 8 18.3 / 16.1 / 16.3 / 18.0, T = 16 22.8 /
+//     18.6 / 17.9 / 19.2;  2048 T = 1 22.8 / 23.0 / 25.5 / 25.3, T = 8 28.9 / 25.2 / 26.3 / 26.2, T = 16 37.1 / 29.7 / 28.1 / 28.0;
+//     2560 T = 1 29.5 / 29.6 / 33.6 / 36.2, T = 16 50.9 / 40.2 / 40.3 / 42.3;  4096 (K = 14336) T = 1 64.1 / 64.9 / 67.3 / 65.5,
+//     T = 4 72.8 / 68.2 / 70.1 / 66.1.  8 rows where 4 are as good: the order of the sum stays that of 64-element blocks.
+//   bf16 result (one workgroup per row tile):
+//     896 T = 1 12.8 / 14.2 / 16.7 / 18.9, T = 16 16.8 / 17.8 / 21.7 / 22.2;  1280 T = 1 14.9 / 15.1 / 17.9 / 19.4, T = 8 18.3 / 16.5 /
+//     19.8 / 20.7;  2048 T = 1 22.8 / 23.9 / 27.3 / 28.0, T = 16 37.1 / 29.8 / 34.5 / 33.8;  2560 T = 1 29.5 / 32.1 / 32.4 / 32.7,
+//     T = 4 33.2 / 34.9 / 33.3 / 33.9, T = 16 50.9 / 45.6 / 39.8 / 38.9;  4096 T = 1 63.8 / 64.9 / 67.1 / 67.7.
+constexpr int WIDE_TILES = 192;                          // row tiles of 16 from which the wide kernels fill the chip
+int down_shape(int T, int d_model, bool out_bf16)
+{
+    const bool few = T * (long long)d_model <= 4096;
+    if (out_bf16) return d_model <= 1024 || few ? 4 : (d_model < 2560 ? 8 : 0);
+    if (ceil_div(d_model, 16) >= WIDE_TILES) return few ? 8 : 0;
+    return T <= 8 || d_model <= 1024 ? 8 : 16;
+}
+
 constexpr size_t kStreamLdsMax = 160 * 1024;
 
 }  // namespace
+
+template <int XB, bool kRouted>
+static void launch_gate_up_once_xb(const FwdArgs &a, const BranchTable &bt, int tiles, float *clear, int clear_n)
+{
+    const auto kernel = a.T <= 8 ? decode_gate_up_once<ONCE_NW, XB, 2, kRouted> : decode_gate_up_once<ONCE_NW, XB, 1, kRouted>;
+    kernel<<<tiles, ONCE_NW * 64, 0, a.stream>>>(
+        static_cast<const uint16_t *>(a.x), a.T, static_cast<const uint16_t *>(a.Wg), static_cast<const uint16_t *>(a.Wu),
+        a.d_model, static_cast<uint16_t *>(a.H), a.ldh, a.route, clear, clear_n, tiles, bt);
+}
+template <bool kRouted>
+static void launch_gate_up_once(const FwdArgs &a, const BranchTable &bt, int tiles, float *clear, int clear_n)
+{
+    static_assert(ONCE_MAX_D <= 6 * ONCE_NW * KB, "K blocks per wave");
+    const int xb = ceil_div(ceil_div(a.d_model, KB), ONCE_NW);
+    if (xb <= 2) launch_gate_up_once_xb<2, kRouted>(a, bt, tiles, clear, clear_n);
+    else if (xb <= 4) launch_gate_up_once_xb<4, kRouted>(a, bt, tiles, clear, clear_n);
+    else launch_gate_up_once_xb<6, kRouted>(a, bt, tiles, clear, clear_n);
+}
+
+// 8 waves with 5 K blocks each requested as the kernel starts (8 blocks of half the size with 16 rows).
+template <int R, int NG, int KS, bool kRouted>
+static void launch_down_rows(const FwdArgs &a, const BranchTable &bt)
+{
+    decode_down_rows<8, R == 16 ? 8 : 5, R, NG, KS, kRouted><<<dim3(ceil_div(a.d_model, R), KS), 8 * 64, 0, a.stream>>>(
+        static_cast<const uint16_t *>(a.H), a.ldh, a.T, static_cast<const uint16_t *>(a.Wd), a.d_inter, a.d_model, a.out,
+        a.out_bf16 ? 1 : 0, a.route, bt);
+}
 
 template <bool kRouted>
 static hipError_t launch_decode_impl(const FwdArgs &a, const BranchTable &bt)
@@ -664,7 +928,11 @@ static hipError_t launch_decode_impl(const FwdArgs &a, const BranchTable &bt)
     float *clear = split_down ? a.out : nullptr;
     const int clear_n = split_down ? a.T * a.d_model : 0;
     const uint16_t *Wg = static_cast<const uint16_t *>(a.Wg), *Wu = static_cast<const uint16_t *>(a.Wu);
-    if (persistent) {
+    if (gate_up_once(a.T, a.d_model)) {
+        ProfileScope ps(MLPMOE_KERNEL_DECODE_GATE_UP, a.stream);
+        launch_gate_up_once<kRouted>(a, bt, (int)tiles1, clear, clear_n);
+        if (launch_status("decode gate+up (one tile per workgroup) launch") != hipSuccess) return hipErrorLaunchFailure;
+    } else if (persistent) {
         // per device, set up on the first call there: CU count and the LDS limit of the kernel that stages x
         static std::mutex mu;
         static int cus_of[64] = {0};              // one table per instantiation (attribute is per kernel)
@@ -713,13 +981,20 @@ static hipError_t launch_decode_impl(const FwdArgs &a, const BranchTable &bt)
         if (launch_status("decode gate_up launch") != hipSuccess) return hipErrorLaunchFailure;
     }
     ProfileScope ps(MLPMOE_KERNEL_DECODE_DOWN, a.stream);
-    if (split_down && tiles2 >= 192)
+    const int rows = persistent ? down_shape(a.T, a.d_model, a.out_bf16) : 0;
+    if (split_down && rows == 16)
+        launch_down_rows<16, 1, 2, kRouted>(a, bt);
+    else if (split_down && rows == 8)
+        a.T <= 8 ? launch_down_rows<8, 2, 2, kRouted>(a, bt) : launch_down_rows<8, 1, 2, kRouted>(a, bt);
+    else if (split_down)
         decode_down_split<4, 8, 2, kRouted><<<dim3(ceil_div(a.d_model, 32), 2), 4 * 64, 0, a.stream>>>(
             H, a.ldh, a.T, static_cast<const uint16_t *>(a.Wd), a.d_inter, a.d_model, a.out, a.route, bt);
-    else if (split_down)
-        decode_down_split<16, 4, 1, kRouted><<<dim3(tiles2, 2), 16 * 64, 0, a.stream>>>(
-            H, a.ldh, a.T, static_cast<const uint16_t *>(a.Wd), a.d_inter, a.d_model, a.out, a.route, bt);
-    else if (tiles2 >= 192)
+    else if (!kRouted && rows == 8)
+        a.T <= 8 ? launch_down_rows<8, 2, 1, false>(a, bt) : launch_down_rows<8, 1, 1, false>(a, bt);
+    else if (!kRouted && rows == 4)
+        a.T <= 4 ? launch_down_rows<4, 4, 1, false>(a, bt)
+                 : (a.T <= 8 ? launch_down_rows<4, 2, 1, false>(a, bt) : launch_down_rows<4, 1, 1, false>(a, bt));
+    else if (tiles2 >= WIDE_TILES)
         decode_kernel<DEC_NW2, DEC_U2, false, kRouted><<<tiles2, DEC_NW2 * 64, 0, a.stream>>>(
             H, a.ldh, a.T, static_cast<const uint16_t *>(a.Wd), nullptr, a.d_inter, a.d_model, nullptr,
             a.ldh, a.out, a.out_bf16 ? 1 : 0, a.route, bt);
