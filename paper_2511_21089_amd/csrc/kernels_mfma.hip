@@ -221,7 +221,8 @@ __device__ __forceinline__ void mainloop(const E *__restrict__ A_tile, int lda, 
     constexpr int BNH = 32 * NB;                  // rows of each B block
     constexpr int PL = BMT / 8 / NWAVES;          // 1 KiB wave-loads per wave per A part
     constexpr int PLB = 8 * NB / NWAVES;          // ... per B part
-    constexpr int N_SLOTS = MI * NB / 2;          // slots of 4 MFMAs per K step
+    constexpr int SLOT = MI * NB >= 2 ? 4 : 2;    // MFMAs (of one chunk element) per slot
+    constexpr int N_SLOTS = MI * NB * 2 / SLOT;   // slots per K step
     constexpr int N_PIECES = 2 * NB + MI;         // fragment pieces per K step
     constexpr int RPS = (N_PIECES + N_SLOTS - 1) / N_SLOTS < 2 ? 2 : (N_PIECES + N_SLOTS - 1) / N_SLOTS;   // fragment reads per slot
     // Ring geometry in bytes: where the A part of the first K tile and its B part sit, how far the next tile's
@@ -233,9 +234,8 @@ __device__ __forceinline__ void mainloop(const E *__restrict__ A_tile, int lda, 
     constexpr int RING_STEP = kStaged ? stage_bytes(BMT, NB) : 2 * part_bytes(BMT, NB);
     constexpr int RING_BYTES = lds_bytes(BMT, NB, D, kStaged);
     static_assert(D >= 2, "one tile in use, at least one more on its way");
-    static_assert((N_SLOTS % PL == 0 || PL % N_SLOTS == 0) && (N_SLOTS % PLB == 0 || PLB % N_SLOTS == 0) &&
-                      PL % 2 == 0 && PLB % 2 == 0,
-                  "loads spread evenly over the slots, slab parity is load parity");
+    static_assert((N_SLOTS % PL == 0 || PL % N_SLOTS == 0) && (N_SLOTS % PLB == 0 || PLB % N_SLOTS == 0),
+                  "loads spread evenly over the slots");
     const int nk = kt_end - kt_begin;
     if (nk <= 0) return;
     const int tid = threadIdx.x;
@@ -246,13 +246,14 @@ __device__ __forceinline__ void mainloop(const E *__restrict__ A_tile, int lda, 
     // ---- global side: per-lane byte offsets of this wave's loads, relative to the tile pointers
     const int lr = lane >> 3;                     // row inside the 8-row slab of one wave-load
     const int cl0 = (lane & 7) ^ lr;              // logical chunk fetched in even slabs; odd slabs: cl0 ^ 1
+    const int a_cl0 = cl0 ^ (wave * PL & 1), b_cl0 = cl0 ^ (wave * PLB & 1);      // ... in this wave's first slab
     const bool second = wave >= NWAVES / 2;       // this wave fills the rows of the second B block
     const int b_valid = second ? b1_valid : b0_valid;
     unsigned a_off[PL], b_off[PLB];
 #pragma unroll
     for (int n = 0; n < PL; ++n) {
         const int slab = wave * PL + n;
-        const int cl = cl0 ^ (n & 1);             // PL is even, so slab parity is n parity
+        const int cl = a_cl0 ^ (n & 1);
         int ra = slab * 8 + lr;
         ra = ra < a_valid ? ra : a_valid - 1;
         a_off[n] = (unsigned)ra * (unsigned)lda * ES + (unsigned)cl * 16u;
@@ -260,7 +261,7 @@ __device__ __forceinline__ void mainloop(const E *__restrict__ A_tile, int lda, 
 #pragma unroll
     for (int n = 0; n < PLB; ++n) {
         const int slab = wave * PLB + n;          // 0 .. 8 NB - 1; the second half are B1's rows
-        const int cl = cl0 ^ (n & 1);
+        const int cl = b_cl0 ^ (n & 1);
         int rb = (slab % (4 * NB)) * 8 + lr;
         rb = rb < b_valid ? rb : b_valid - 1;
         b_off[n] = (unsigned)rb * (unsigned)ldb * ES + (unsigned)cl * 16u;
@@ -293,15 +294,15 @@ __device__ __forceinline__ void mainloop(const E *__restrict__ A_tile, int lda, 
     struct Part {
         const char *src;                          // tile pointer moved to the part's K offset
         char *dst;                                // this wave's first slab in the part's ring slot
-        bool ok[2];                               // chunk inside the K range, for even / odd slabs
+        bool ok[2];                               // chunk inside the K range, for this wave's even / odd loads
     };
-    auto part_of = [&](const Issue &q, const char *base, char *w_dst) {
+    auto part_of = [&](const Issue &q, const char *base, char *w_dst, int first_cl) {
         Part pt;
         const int kend = q.left > 0 ? q.kend : -(1 << 30);
         pt.src = base + (size_t)q.k * ES;
         pt.dst = w_dst + q.off;
-        pt.ok[0] = q.k + cl0 * CHUNK < kend;
-        pt.ok[1] = q.k + (cl0 ^ 1) * CHUNK < kend;
+        pt.ok[0] = q.k + first_cl * CHUNK < kend;
+        pt.ok[1] = q.k + (first_cl ^ 1) * CHUNK < kend;
         return pt;
     };
     auto dma_part = [&](int n, const Part &pt, const unsigned *off) {
@@ -364,14 +365,14 @@ __device__ __forceinline__ void mainloop(const E *__restrict__ A_tile, int lda, 
             // asking at 1, cannot cut in, which the older wave otherwise always does) and drops
             // to 0 for its loads and address arithmetic, which then run under the other's turn.
             __builtin_amdgcn_s_setprio(1);
-            mfma_n(cur_f, 4 * g, 0);
+            mfma_n(cur_f, SLOT * g, 0);
             __builtin_amdgcn_s_setprio(3);
 #pragma unroll
-            for (int q = 1; q < 4; ++q) mfma_n(cur_f, 4 * g + q, 0);
+            for (int q = 1; q < SLOT; ++q) mfma_n(cur_f, SLOT * g + q, 0);
 #pragma unroll
             for (int e = 1; e < MFMAS_PER_CHUNK<E>; ++e)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) mfma_n(cur_f, 4 * g + q, e);
+                for (int q = 0; q < SLOT; ++q) mfma_n(cur_f, SLOT * g + q, e);
             __builtin_amdgcn_s_setprio(0);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -403,7 +404,7 @@ __device__ __forceinline__ void mainloop(const E *__restrict__ A_tile, int lda, 
     }
 #pragma unroll
     for (int p = 0; p < D; ++p) {
-        const Part pa = part_of(qa, a_base, wa_dst), pb = part_of(qb, b_base, wb_dst);
+        const Part pa = part_of(qa, a_base, wa_dst, a_cl0), pb = part_of(qb, b_base, wb_dst, b_cl0);
 #pragma unroll
         for (int n = 0; n < PL; ++n) dma_part(n, pa, a_off);
 #pragma unroll
@@ -418,13 +419,13 @@ __device__ __forceinline__ void mainloop(const E *__restrict__ A_tile, int lda, 
 
     int rd = 0;                                   // byte offset in the ring of the A part of the tile in use
     for (int it = 0; it < nk; ++it) {
-        const Part pa = part_of(qa, a_base, wa_dst);
+        const Part pa = part_of(qa, a_base, wa_dst, a_cl0);
         k_step(f0, f1, rd, 1, 1, pa);             // + A part of tile it+D
         advance(qa);
         // tile it+1 has landed (the newer tiles and the A part just issued may be in flight); tile it's slots are free
         pipeline_barrier<(D - 2) * (PL + PLB) + PL>();
         rd = rd + RING_STEP < RING_BYTES ? rd + RING_STEP : rd + RING_STEP - RING_BYTES;
-        const Part pb = part_of(qb, b_base, wb_dst);
+        const Part pb = part_of(qb, b_base, wb_dst, b_cl0);
         k_step(f1, f0, rd, 0, 2, pb);             // + B part of tile it+D
         advance(qb);
     }
@@ -1205,7 +1206,11 @@ using ShapeSlim = ShapeT<BM_SLIM, SLIM_WM, 2, SLIM_D, true>;
 // and small tiles fill the chip at the sizes float storage is used for (4864 neurons and 256 tokens are 608 tiles; the
 // 128 x (64 + 64) tile would make 152).  The layer at T = 256: 84 us against 1007 us on the general FMA kernels, error
 // against float64 1.0e-6 against 1.5e-6 (rel.).
+// Gate+up also with 32 tokens: half the work per tile where 64 leave the last round of workgroups emptier, and with four
+// K tiles requested ahead where there are at most two workgroups per CU to hide each other's latency (see pick_f32_tokens).
 using ShapeF32 = ShapeT<64, 2, 1, 2, false>;
+using ShapeF32Half = ShapeT<32, 2, 1, 2, false>;
+using ShapeF32HalfDeep = ShapeT<32, 2, 1, 4, false>;
 struct TileDims {
     int bm, bn;       // tokens, B rows per block (a tile has two blocks)
     int per_cu;       // workgroups resident per CU
@@ -1522,16 +1527,20 @@ hipError_t launch_mfma_routed_bf16(const FwdArgs &a, const BranchTable &bt, bool
                   : down_and_reduce<true, false>(a, bt, DownPlan{sh, splits}, NoEdges{});
 }
 
-// Float storage.  K split of the down projection: the factor with the shortest estimate, a K tile of 32 floats taking a
-// workgroup 0.43 us of matrix pipe (workgroups that share a CU take turns), about 2 us for its first loads and its
-// stores, and the separate sum about 4 us plus its traffic.  Depends on T through whole token tiles only.
+// Float storage.  K split of the down projection: the factor with the shortest estimate.  A K tile of 32 floats takes a
+// workgroup that has its CU to itself 0.7 us (of which 0.43 matrix pipe: nothing hides its waits) and workgroups that
+// share a CU 0.45 us each, the first loads and the stores about 3 us, the separate sum about 4 us plus its traffic.
+// 896 x 4864, whole call, splits of about one workgroup per CU before: T = 256 91 -> 80 us (4 -> 9 splits), T = 500 158 ->
+// 134 us (2 -> 9).
+// Depends on T through whole token tiles only.
 static int f32_down_splits(int T, int d_model, int kt)
 {
     const long long tiles_m = ceil_div(T, ShapeF32::BMT), tiles = tiles_m * ceil_div(d_model, 64 * ShapeF32::NB);
     int best = 1;
     double best_us = 1e30;
     for (int s = 1; s <= 16 && s <= std::max(1, kt / 4); ++s) {
-        double us = (double)((tiles * s + kCUs - 1) / kCUs) * (ceil_div(kt, s) * 0.43 + 2.0);
+        const double per_cu = (double)((tiles * s + kCUs - 1) / kCUs);
+        double us = ceil_div(kt, s) * std::max(0.7, 0.45 * per_cu) + 3.0;
         if (s > 1) us += 4.0 + (s + 1.0) * (double)(tiles_m * ShapeF32::BMT) * d_model * 4.0 / 5e6;
         if (us < best_us) {
             best = s;
@@ -1539,6 +1548,16 @@ static int f32_down_splits(int T, int d_model, int kt)
         }
     }
     return best;
+}
+
+// Token rows per gate+up tile.  Rounds of 64-token tiles against half rounds of 32-token ones, of which a CU holds four at a
+// time: a fifth runs alone and hides nothing.  896 x 4864, whole call, 64 / 32 tokens: T = 128 58.7 / 53.7 us, T = 256
+// 91.2 / 96.3 us; 1280 x 3328, T = 200 87.6 / 80.7 us; 512 x 2560, T = 300 39.7 / 41.8 us.
+static int pick_f32_tokens(long long tiles_n, int T)
+{
+    const long long whole = tiles_n * ceil_div(T, ShapeF32::BMT), half = tiles_n * ceil_div(T, ShapeF32Half::BMT);
+    const long long cost64 = 2 * ((whole + kCUs - 1) / kCUs), cost32 = (half + kCUs - 1) / kCUs + (half > 4 * kCUs ? 1 : 0);
+    return cost32 < cost64 ? 32 : 64;
 }
 
 size_t mfma_partial_bytes_f32(int T, int d_model, int d_inter)
@@ -1550,7 +1569,15 @@ size_t mfma_partial_bytes_f32(int T, int d_model, int d_inter)
 template <bool kEdges, typename Ed>
 static hipError_t launch_mfma_f32_runs(const FwdArgs &a, const BranchTable &outer, const BranchTable &inner, const Ed &edges)
 {
-    if (launch_gate_up<ShapeF32, kEdges, float>(a, outer) != hipSuccess) return hipErrorLaunchFailure;
+    long long tiles_n = 0;
+    for (int r = 0; r < outer.n_runs; ++r) tiles_n += ceil_div(outer.run_end[r] - outer.run_start[r], 32 * ShapeF32::NB);
+    const bool half = pick_f32_tokens(tiles_n, a.T) == 32;
+    // T = 60 42.9 us, with four K tiles ahead 38.9 us; T = 20 41.2 and 30.5 us; T = 128 (608 tiles) 53.7 and 56.0 us
+    const bool deep = tiles_n * ceil_div(a.T, ShapeF32Half::BMT) <= 2 * kCUs;
+    const hipError_t e = !half ? launch_gate_up<ShapeF32, kEdges, float>(a, outer)
+                               : (deep ? launch_gate_up<ShapeF32HalfDeep, kEdges, float>(a, outer)
+                                       : launch_gate_up<ShapeF32Half, kEdges, float>(a, outer));
+    if (e != hipSuccess) return hipErrorLaunchFailure;
     // The order of the sums depends on the sizes and the table alone: at most the splits that the workspace is sized for
     // (short runs have more K tiles than the width they add up to), and a workspace without room for the partial sums
     // changes who adds them up, not the result (896 x 4864, T = 256: 161 us in the least block, 86 us in a full one).
