@@ -1225,7 +1225,7 @@ long long gate_up_tiles(const BranchTable &bt, int T, TileShape sh)
     return n * ceil_div(T, kTileDims[sh].bm);
 }
 
-// Estimated duration in microseconds of a launch of `tiles` tiles with nk K tiles each that streams
+// Estimated duration in microseconds of a launch of the down projection, `tiles` tiles with nk K tiles each that stream
 // `bytes` of weights and activations, fitted to measurements on the two benchmark layers (T = 64 .. 4096):
 // a K tile of a WIDE tile takes about 1.48 us at the clocks the chip sustains on this work, a NARROW one
 // 0.62 of that, a SMALL one 0.4 (two share a CU, each at a quarter of a WIDE tile's flops but bound by the
@@ -1233,7 +1233,8 @@ long long gate_up_tiles(const BranchTable &bt, int T, TileShape sh)
 // (first loads, epilogue, hand-over) is about 7.4 / 5.2 us and 1.5 us for SMALL, whose neighbour on the CU
 // computes meanwhile; DEEP (SMALL's tile alone on its CU) 0.75 and 4.4 us; SLIM 0.6 and 3.5 us.  A launch that
 // has few tiles per CU cannot stream faster than about 3.5 TB/s, 5 TB/s with DEEP's and SLIM's longer queues of
-// requests.
+// requests, 3 TB/s with SMALL's (4096 x 14336, T = 200 as 512 SMALL tiles 54.0, as 256 NARROW ones 49.6 us with event brackets;
+// T = 256 57.2 and 51.9; 3072 x 8192, T = 160 34.4 and 32.0).
 constexpr double kDeepStreamBytesPerUs = 5.0e6;
 double launch_cost_us(long long tiles, int nk, TileShape sh, double bytes)
 {
@@ -1245,7 +1246,8 @@ double launch_cost_us(long long tiles, int nk, TileShape sh, double bytes)
     else
         c = (double)per_cu * (nk * per_k[sh] + fixed[sh]);
     // DEEP keeps twice the bytes in flight
-    return std::max(c, bytes / (sh == TILE_DEEP || sh == TILE_SLIM ? kDeepStreamBytesPerUs : 3.5e6) + fixed[sh]);
+    const double rate = sh == TILE_DEEP || sh == TILE_SLIM ? kDeepStreamBytesPerUs : (sh == TILE_SMALL ? 3.0e6 : 3.5e6);
+    return std::max(c, bytes / rate + fixed[sh]);
 }
 
 // Wide tiles that MIXED runs as wide, per XCD (32 per full round of 256), or -1 if MIXED does not apply:
@@ -1260,17 +1262,33 @@ int mixed_wide_per_xcd(long long wide_tiles)
 // Pieces MIXED cuts each left-over wide tile into: quarters when they fit one round, else halves.
 int mixed_rest_parts(long long wide_tiles) { return wide_tiles % kCUs <= kCUs / 4 ? 4 : 2; }
 
+// Estimate for a launch of the gate+up projection, whose K loops are as short as d_model: fitted to the kernel alone with
+// every shape on twelve layers, 384 x 1024 .. 4096 x 14336, at 18 batches T = 17 .. 4096, and checked on whole calls (half a
+// per cent from the fastest shape in the mean).  A round of workgroups takes `round` + nk K tiles of per_k, SMALL 1.45 + 1.05 per K tile
+// where two share a CU and 0.73 for an odd one; few tiles stream the weights at the given rate.
+// Against launch_cost_us, which is fitted to long K loops: 896 x 4864, T = 64 SMALL 13.9 -> SLIM 11.2 us (with event brackets),
+// T = 256 (6 x 38 tiles) SMALL 16.5 -> DEEP 14.8; 2048 x 5504, T = 32 SMALL 31.5 -> SLIM 19.5, T = 200 32.3 -> DEEP 24.8; 3072 x
+// 8192, T = 64 46.2 -> SLIM 33.9, T = 200 46.4 -> DEEP 37.9; 4096 x 11008, T = 96 60.7 -> DEEP 44.3.
+double gate_up_cost_us(long long tiles, int nk, TileShape sh, double bytes)
+{
+    static const double per_k[N_TILE_SHAPES] = {1.21, 0.87, 1.05, 1.21, 0.6, 0.394}, round[N_TILE_SHAPES] = {4.5, 2.1, 1.45, 4.5, 3.9, 2.7};
+    static const double bytes_per_us[N_TILE_SHAPES] = {3.2e6, 3.9e6, 4.05e6, 3.2e6, 6.1e6, 6.3e6};
+    const long long per_cu = (tiles + kCUs - 1) / kCUs;
+    const double c = sh == TILE_SMALL ? (double)(per_cu / 2) * (nk * per_k[sh] + round[sh]) + (double)(per_cu % 2) * (nk * 0.73 + round[sh])
+                                      : (double)per_cu * (nk * per_k[sh] + round[sh]);
+    return std::max(c, bytes / bytes_per_us[sh] + round[sh]);
+}
+
 TileShape pick_gate_up_tile(const BranchTable &bt, int T, int d_model)
 {
     const int nk = ceil_div(d_model, BK);
     const double bytes = 4.0 * bt.d_eff * d_model;            // W_gate and W_up rows of the active neurons, once
     const long long wide = gate_up_tiles(bt, T, TILE_WIDE);
     TileShape best = TILE_WIDE;
-    double best_cost = launch_cost_us(wide, nk, TILE_WIDE, bytes);
+    double best_cost = gate_up_cost_us(wide, nk, TILE_WIDE, bytes);
     for (TileShape sh : {TILE_NARROW, TILE_SMALL, TILE_DEEP, TILE_SLIM}) {
-        if (sh == TILE_SLIM && T > BM_SLIM) continue;           // more tokens: a taller tile reuses the weights
-        const double c = launch_cost_us(gate_up_tiles(bt, T, sh), nk, sh, bytes);
-        if (c < best_cost * 0.97) {
+        const double c = gate_up_cost_us(gate_up_tiles(bt, T, sh), nk, sh, bytes);
+        if (c < best_cost) {
             best = sh;
             best_cost = c;
         }
@@ -1278,9 +1296,9 @@ TileShape pick_gate_up_tile(const BranchTable &bt, int T, int d_model)
     if (mixed_wide_per_xcd(wide) >= 0) {
         // the full rounds as wide tiles, then one round of narrow ones, or of quarters (measured 2 us shorter
         // at 14 K tiles)
-        const double c = launch_cost_us(wide / kCUs * kCUs, nk, TILE_WIDE, 0.0) + launch_cost_us(kCUs, nk, TILE_NARROW, 0.0) -
+        const double c = gate_up_cost_us(wide / kCUs * kCUs, nk, TILE_WIDE, 0.0) + gate_up_cost_us(kCUs, nk, TILE_NARROW, 0.0) -
                          (mixed_rest_parts(wide) == 4 ? 2.0 : 0.0);
-        if (c < best_cost * 0.97) best = TILE_MIXED;
+        if (c < best_cost) best = TILE_MIXED;
     }
     return best;
 }
