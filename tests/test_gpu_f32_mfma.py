@@ -1,4 +1,4 @@
-"""Float storage on the float MFMA kernels (d_model and d_inter multiples of 4): token and feature tails, K tails, runs
+"""Float storage on the MFMA kernels (d_model and d_inter multiples of 4): token and feature tails, K tails, runs
 that start and end inside a 16-byte chunk, the K split with and without room for its partial sums.  Against float64,
 with the error fp32 sums may have and non-finite weights in every pruned branch."""
 import numpy as np
@@ -134,3 +134,26 @@ def test_f32_token_tiles(mm, widths, mask, T):
     """Gate+up tiles of 32 tokens (one workgroup per CU with four K tiles ahead: T = 31, 32; three: T = 97, 128) and of 64."""
     args = make(widths, mask, T, 72, seed=T)
     check(run_gpu(*poison_pruned(args)), *args)
+
+
+@pytest.mark.parametrize("T,d_model,widths", [(5, 64, [64, 64]), (70, 132, [129, 129, 258]), (40, 72, [4864])])
+def test_f32_infinities(mm, T, d_model, widths):
+    """Infinities, NaNs and sums that overflow, in x and in every matrix: each result is the infinity or NaN that float
+    arithmetic gives, and everything else what it is without them.  Tiny values (below 2^-100) are held as well."""
+    x, Wg, Wu, Wd, off, alpha, mask = make(widths, [1] * len(widths), T, d_model, seed=3)
+    x[4] *= 1e-30
+    clean = [a.copy() for a in (x, Wg, Wu, Wd)]
+    x[1, 3], x[2, 5], x[3, 7] = np.inf, np.nan, 3e38
+    Wg[10, 7], Wu[20, 9], Wd[4, 11], Wd[6, 13] = 2.0, -np.inf, np.inf, np.nan
+    clean[1][10, 7] = 2.0
+    got = run_gpu(x, Wg, Wu, Wd, off, alpha, mask)
+    a = np.repeat(alpha, np.diff(off))
+    with np.errstate(all="ignore"):
+        g, u = x @ Wg.T, x @ Wu.T
+        ref = (a * (g / (1 + np.exp(-g)) * u)) @ Wd.T
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)]) and np.array_equal(np.isinf(got), np.isinf(ref))
+    rows, cols = [0, 4], [m for m in range(d_model) if m not in (4, 6)]
+    Wu[20, 9], Wd[4, 11], Wd[6, 13] = clean[2][20, 9], clean[3][4, 11], clean[3][6, 13]
+    got = run_gpu(x, Wg, Wu, Wd, off, alpha, mask)[rows]
+    check(got[:, cols], clean[0][rows], clean[1], clean[2], clean[3][cols], off, alpha, mask)
