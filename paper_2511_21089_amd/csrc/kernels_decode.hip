@@ -36,10 +36,10 @@ constexpr int KQ = 16, KH = 8;
 __device__ const uint32_t g_zero16[4] = {0, 0, 0, 0};
 
 // 16-byte load through the global (not flat) path: every pointer handed in is device memory.
-__device__ __forceinline__ u32x4 ld16(const uint16_t *p)
+__device__ __forceinline__ u32x4 ld16(const void *p)
 {
     typedef const __attribute__((address_space(1))) u32x4 *gptr;
-    return *(gptr)(const void *)p;
+    return *(gptr)p;
 }
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
@@ -120,7 +120,7 @@ struct TileCursor {
     __device__ __forceinline__ void settle(const Stretches<kRouted> &st)
     {
         while (r < st.count()) {
-            const int n = (st.end(r) - st.beg(r)) / 8;   // stretch lengths are multiples of 8
+            const int n = (st.end(r) - st.beg(r) + 7) / 8;   // whole tiles but for tables with odd boundaries
             if (t < n) break;
             t -= n;
             ++r;
@@ -131,6 +131,7 @@ struct TileCursor {
         t += step;
         settle(st);
     }
+    __device__ __forceinline__ int end(const Stretches<kRouted> &st) const { return st.end(r); }
     // first row of the tile under the cursor, -1 past the last tile
     __device__ __forceinline__ int row0(const Stretches<kRouted> &st) const { return r < st.count() ? st.beg(r) + t * 8 : -1; }
 };
@@ -661,6 +662,44 @@ struct Window {
     }
 };
 
+// What E, the storage type, and kEdges, a table whose run boundaries are not multiples of a 16-byte chunk, change: a chunk is
+// 8 bf16 values, one MFMA, or 4 floats, four v_mfma_f32_16x16x4_f32; SiLU is formed with expf and a division, as by the
+// general kernels.  With kEdges the last tile of a run has fewer rows, and the K blocks of the down projection start at the chunk that a run
+// starts in: the elements of a chunk that are not the run's are masked in BOTH operands, so that nothing of a pruned branch
+// and no value of H that was never written reaches the sum, non-finite ones included.
+template <typename E>
+struct RowElem {
+    static constexpr int CH = 16 / sizeof(E), KBLK = 8 * CH;    // elements of a chunk, of a 128-byte line
+};
+template <typename E>
+__device__ __forceinline__ f32x4 mfma_chunk(u32x4 w, u32x4 x, f32x4 acc)
+{
+    if constexpr (sizeof(E) == 2) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(w), as_bf16x8(x), acc, 0, 0, 0);
+    } else {
+        const f32x4 wf = __builtin_bit_cast(f32x4, w), xf = __builtin_bit_cast(f32x4, x);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[e], xf[e], acc, 0, 0, 0);
+        return acc;
+    }
+}
+// the elements lo .. hi - 1 of a chunk
+template <typename E>
+__device__ __forceinline__ u32x4 keep_elements(u32x4 v, int lo, int hi)
+{
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        if constexpr (sizeof(E) == 4) {
+            v[w] = w >= lo && w < hi ? v[w] : 0u;
+        } else {
+            v[w] &= (2 * w >= lo && 2 * w < hi ? 0x0000ffffu : 0u) | (2 * w + 1 >= lo && 2 * w + 1 < hi ? 0xffff0000u : 0u);
+        }
+    }
+    return v;
+}
+__device__ __forceinline__ void store_h(uint16_t *p, float v) { *p = to_bf16(v); }
+__device__ __forceinline__ void store_h(float *p, float v) { *p = v; }
+
 constexpr int RED_V = 64 + 4, RED_W = 4 * RED_V + 8;     // partial sums in LDS: strides of a register and of a wave (floats)
 
 // Gate+up projection, one workgroup per tile of 8 neurons; wave w takes the K blocks w, w + NW, ..., at most XB of them.
@@ -668,13 +707,14 @@ constexpr int RED_V = 64 + 4, RED_W = 4 * RED_V + 8;     // partial sums in LDS:
 // T = 16 17.9 -> 17.5 us.  Every workgroup loads all of x, which is why wide layers and batches keep the ring kernel (see
 // gate_up_once).  Two tiles per workgroup (half of the x loads): 15.6, 16.7 and 18.3 us; one workgroup per CU with x in
 // registers and 4-neuron tiles: 0.5 to 1 us slower than this as well.
-template <int NW, int XB, int NG, bool kRouted>
+template <int NW, int XB, int NG, bool kRouted, bool kEdges, typename E>
 __global__ void __launch_bounds__(NW * 64)
-decode_gate_up_once(const uint16_t *__restrict__ X, int T, const uint16_t *__restrict__ Wg,
-                    const uint16_t *__restrict__ Wu, int d_model, uint16_t *__restrict__ Hout, int ldh,
+decode_gate_up_once(const E *__restrict__ X, int T, const E *__restrict__ Wg,
+                    const E *__restrict__ Wu, int d_model, E *__restrict__ Hout, int ldh,
                     const uint8_t *__restrict__ route, float *__restrict__ clear, int clear_n, int grid, BranchTable bt)
 {
-    constexpr int NM = 2 / NG, CT = 16 / NG;
+    constexpr int NM = 2 / NG, CT = 16 / NG, CH = RowElem<E>::CH, KBLK = RowElem<E>::KBLK;
+    constexpr unsigned ES = sizeof(E);
     constexpr int PARTS = NW * 64 / (8 * CT) < NW ? NW * 64 / (8 * CT) : NW;     // lanes that add up one output
     __shared__ float red[2][NW * RED_W];
     const int lane = threadIdx.x & 63;
@@ -683,27 +723,31 @@ decode_gate_up_once(const uint16_t *__restrict__ X, int T, const uint16_t *__res
     Stretches<kRouted> st(bt, route, T);
     const BranchLanes br(bt);
     arrived(st.v_beg, st.v_end);
-    const int row0 = TileCursor<kRouted>(st, blockIdx.x).row0(st);
+    const TileCursor<kRouted> cur(st, blockIdx.x);
+    const int row0 = cur.row0(st);
     if (row0 < 0) {                                      // with routing the grid covers all active rows
         clear_floats(clear, clear_n, NW * 64, grid);
         return;
     }
-    const uint16_t *zero = reinterpret_cast<const uint16_t *>(g_zero16);
-    const int chunk = (q + 4 * (r16 >> 3)) * 8;          // this lane's K elements of a block
-    const size_t w_off = (size_t)(row0 + (r16 & 7)) * d_model + chunk;
-    const Window x(X, (unsigned)T * (unsigned)d_model * 2u);
+    constexpr bool kPart = kEdges || sizeof(E) == 4;     // runs of floats are whole chunks of 4: half a tile may be left
+    const int rows = kPart && cur.end(st) - row0 < 8 ? cur.end(st) - row0 : 8;
+    const E *zero = reinterpret_cast<const E *>(g_zero16);
+    const int chunk = (q + 4 * (r16 >> 3)) * CH;         // this lane's K elements of a block
+    const int w_row = kPart && (r16 & 7) >= rows ? rows - 1 : r16 & 7;
+    const size_t w_off = (size_t)(row0 + w_row) * d_model + chunk;
+    const Window x(X, (unsigned)T * (unsigned)d_model * ES);
     const bool tok = r16 % CT < T;
-    const int x_k = NG == 2 ? chunk : q * 8;
-    const unsigned x_lane = ((unsigned)(r16 % CT) * (unsigned)d_model + x_k) * 2u;
+    const int x_k = NG == 2 ? chunk : q * CH;
+    const unsigned x_lane = ((unsigned)(r16 % CT) * (unsigned)d_model + x_k) * ES;
     u32x4 wg[XB], wu[XB], xa[XB][NM];
 #pragma unroll
     for (int j = 0; j < XB; ++j) {
-        const int k = (wave + NW * j) * KB;
+        const int k = (wave + NW * j) * KBLK;
         wg[j] = ld16(k + chunk < d_model ? Wg + w_off + k : zero);
         wu[j] = ld16(k + chunk < d_model ? Wu + w_off + k : zero);
 #pragma unroll
         for (int i = 0; i < NM; ++i)
-            xa[j][i] = x.ld16(tok && k + 32 * i + x_k < d_model, x_lane + (k + 32 * i) * 2);
+            xa[j][i] = x.ld16(tok && k + 4 * CH * i + x_k < d_model, x_lane + (k + 4 * CH * i) * ES);
     }
     clear_floats(clear, clear_n, NW * 64, grid);
     f32x4 ag[NM], au[NM];
@@ -713,8 +757,8 @@ decode_gate_up_once(const uint16_t *__restrict__ X, int T, const uint16_t *__res
     for (int j = 0; j < XB; ++j)
 #pragma unroll
         for (int i = 0; i < NM; ++i) {
-            ag[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wg[j]), as_bf16x8(xa[j][i]), ag[i], 0, 0, 0);
-            au[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wu[j]), as_bf16x8(xa[j][i]), au[i], 0, 0, 0);
+            ag[i] = mfma_chunk<E>(wg[j], xa[j][i], ag[i]);
+            au[i] = mfma_chunk<E>(wu[j], xa[j][i], au[i]);
         }
     // register v of lane l is D[row 4 q + v][col r16]: neuron (4 q + v) % 8, K half q / 2; its columns are those of that half
 #pragma unroll
@@ -741,24 +785,26 @@ decode_gate_up_once(const uint16_t *__restrict__ X, int T, const uint16_t *__res
         up += __shfl_xor(up, d);
     }
     int bn = br.branch(row0);                            // the tile may span branches: only a run's ends are multiples of 8
-    for (int i = bn, next; (next = br.next(i)) <= row0 + 7; ++i) bn += next <= row0 + row ? 1 : 0;
+    for (int i = bn, next; (next = br.next(i)) <= row0 + rows - 1; ++i) bn += next <= row0 + row ? 1 : 0;
     const float alpha = __shfl(br.v_alpha, bn);
-    if (p != 0 || t >= T || t >= CT) return;
-    float h = alpha * silu_mul(g, up);
+    if (p != 0 || t >= T || t >= CT || row >= rows) return;
+    float h = kEdges || sizeof(E) == 4 ? alpha * (g / (1.0f + expf(-g)) * up) : alpha * silu_mul(g, up);
     if (kRouted) h = route[(size_t)t * bt.B + bn] ? h : 0.f;
-    Hout[(size_t)t * ldh + row0 + row] = to_bf16(h);
+    store_h(Hout + (size_t)t * ldh + row0 + row, h);
 }
 
 // Down projection, one workgroup per R output features and 1 / KS of the K blocks (blockIdx.y); its waves take the blocks
 // of SB elements in turn.  KS = 2: the two sums of an output are added into `out` by float atomics, which the gate+up
 // kernel before has cleared: 0 + a + b is the same number in either order.  KS = 1: plain stores, float or bf16.
 // Fewer rows per workgroup keep more CUs busy and cost more loads of H per weight byte (CT / R of them): see down_shape.
-template <int NW, int U, int R, int NG, int KS, bool kRouted>
+template <int NW, int U, int R, int NG, int KS, bool kRouted, bool kEdges, typename E>
 __global__ void __launch_bounds__(NW * 64)
-decode_down_rows(const uint16_t *__restrict__ Hin, int ldx, int T, const uint16_t *__restrict__ Wd, int ldw,
+decode_down_rows(const E *__restrict__ Hin, int ldx, int T, const E *__restrict__ Wd, int ldw,
                  int d_model, float *__restrict__ out, int out_bf16, const uint8_t *__restrict__ route, BranchTable bt)
 {
-    constexpr int KG = 16 / R, NM = KG / NG, CT = 16 / NG, SB = 32 * KG;
+    constexpr int CH = RowElem<E>::CH;
+    constexpr unsigned ES = sizeof(E);
+    constexpr int KG = 16 / R, NM = KG / NG, CT = 16 / NG, SB = 4 * CH * KG;
     constexpr int PARTS = NW * 64 / (R * CT) < NW ? NW * 64 / (R * CT) : NW;
     static_assert(KG % NG == 0 && PARTS >= 1, "K groups per MFMA; a thread for every output");
     __shared__ float red[NW * RED_W];
@@ -769,16 +815,19 @@ decode_down_rows(const uint16_t *__restrict__ Hin, int ldx, int T, const uint16_
     arrived(st.v_beg, st.v_end);
     const int row0 = blockIdx.x * R;
     const int rows = d_model - row0 < R ? d_model - row0 : R;
-    const Window w(Wd + (size_t)row0 * ldw, (unsigned)rows * (unsigned)ldw * 2u);
-    const Window h(Hin, (unsigned)T * (unsigned)ldx * 2u);
-    const int chunk = (q + 4 * (r16 / R)) * 8;           // this lane's K elements of a block
+    const Window w(Wd + (size_t)row0 * ldw, (unsigned)rows * (unsigned)ldw * ES);
+    const Window h(Hin, (unsigned)T * (unsigned)ldx * ES);
+    const int chunk = (q + 4 * (r16 / R)) * CH;          // this lane's K elements of a block
     const bool row_ok = r16 % R < rows, tok = r16 % CT < T;
-    const unsigned w_lane = (unsigned)(r16 % R) * (unsigned)ldw * 2u;
-    const unsigned h_lane = (unsigned)(r16 % CT) * (unsigned)ldx * 2u;
+    const unsigned w_lane = (unsigned)(r16 % R) * (unsigned)ldw * ES;
+    const unsigned h_lane = (unsigned)(r16 % CT) * (unsigned)ldx * ES;
+    // where the blocks of a stretch start: with kEdges at the chunk that it starts in
+    auto first_k = [&](int r) { return kEdges ? st.beg(r) / CH * CH : st.beg(r); };
+    auto blocks = [&](int r) { return st.end(r) > st.beg(r) ? (st.end(r) - first_k(r) + SB - 1) / SB : 0; };
 
     // cursor over this wave's blocks: the blocks of all stretches laid end to end, cut into KS contiguous parts
     int nb_all = 0;
-    for (int r = 0; r < st.count(); ++r) nb_all += (st.end(r) - st.beg(r) + SB - 1) / SB;
+    for (int r = 0; r < st.count(); ++r) nb_all += blocks(r);
     const int part = (nb_all + KS - 1) / KS;
     const int first = (int)blockIdx.y * part + wave;
     const int last = (int)(blockIdx.y + 1) * part < nb_all ? (int)(blockIdx.y + 1) * part : nb_all;
@@ -786,7 +835,7 @@ decode_down_rows(const uint16_t *__restrict__ Hin, int ldx, int T, const uint16_
     int cr = 0, cb = first, issued = 0;
     auto settle = [&]() {                                // move past stretches the block index overshoots
         while (cr < st.count()) {
-            const int nb = (st.end(cr) - st.beg(cr) + SB - 1) / SB;
+            const int nb = blocks(cr);
             if (cb < nb) break;
             cb -= nb;
             ++cr;
@@ -794,16 +843,22 @@ decode_down_rows(const uint16_t *__restrict__ Hin, int ldx, int T, const uint16_
     };
     settle();
     u32x4 wa[U], xa[U][NM];
+    int k_of[U], beg_of[U], end_of[U];                   // kEdges: first K of the block in the slot, its stretch
     auto load = [&](int u) {                             // the block under the cursor, zeros past this wave's last
         const bool live = cr < st.count() && issued < total;
         ++issued;
-        const int k = live ? st.beg(cr) + cb * SB : 0;
+        const int k = live ? first_k(cr) + cb * SB : 0;
         const int kend = live ? st.end(cr) : -1;
-        wa[u] = w.ld16(row_ok && k + chunk < kend, w_lane + (k + chunk) * 2);
+        wa[u] = w.ld16(row_ok && k + chunk < kend, w_lane + (k + chunk) * ES);
 #pragma unroll
         for (int i = 0; i < NM; ++i) {
-            const int kx = k + (q + 4 * (i * NG + r16 / CT)) * 8;
-            xa[u][i] = h.ld16(tok && kx < kend, h_lane + kx * 2);
+            const int kx = k + (q + 4 * (i * NG + r16 / CT)) * CH;
+            xa[u][i] = h.ld16(tok && kx < kend, h_lane + kx * ES);
+        }
+        if (kEdges) {
+            k_of[u] = k;
+            beg_of[u] = live ? st.beg(cr) : 0;
+            end_of[u] = kend;
         }
         cb += NW;
         settle();
@@ -816,9 +871,16 @@ decode_down_rows(const uint16_t *__restrict__ Hin, int ldx, int T, const uint16_
     for (int j = 0; j < total; j += U) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+            if (kEdges && (k_of[u] < beg_of[u] || k_of[u] + SB > end_of[u])) {
+                wa[u] = keep_elements<E>(wa[u], beg_of[u] - k_of[u] - chunk, end_of[u] - k_of[u] - chunk);
 #pragma unroll
-            for (int i = 0; i < NM; ++i)
-                acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wa[u]), as_bf16x8(xa[u][i]), acc[i], 0, 0, 0);
+                for (int i = 0; i < NM; ++i) {
+                    const int kx = k_of[u] + (q + 4 * (i * NG + r16 / CT)) * CH;
+                    xa[u][i] = keep_elements<E>(xa[u][i], beg_of[u] - kx, end_of[u] - kx);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < NM; ++i) acc[i] = mfma_chunk<E>(wa[u], xa[u][i], acc[i]);
             if (j + U < total) load(u);
         }
     }
@@ -854,6 +916,7 @@ decode_down_rows(const uint16_t *__restrict__ Hin, int ldx, int T, const uint16_
 // 16.8 / 17.9), 1280 15.5 / 16.9 / 19.5 (17.3 / 18.0 / 19.2), 1536 20.5 / 22.8 / 27.6 (22.4 / 23.2 / 24.9), 2048 25.4 / 28.0
 // / 32.1 (25.3 / 26.2 / 28.0).
 constexpr int ONCE_MAX_D = 1536, ONCE_NW = 4;
+constexpr int ROWS_MAX_D = 2048;                         // float storage and odd boundaries: what 8 waves hold of x
 bool gate_up_once(int T, int d_model) { return d_model <= ONCE_MAX_D && T * d_model <= 14336; }
 
 // Rows per workgroup of decode_down_rows, 0: the kernels for wide layers.  us a step with 4 / 8 / 16 rows and with the
@@ -880,31 +943,64 @@ constexpr size_t kStreamLdsMax = 160 * 1024;
 
 }  // namespace
 
-template <int XB, bool kRouted>
+template <int NW, int XB, bool kRouted, bool kEdges, typename E>
 static void launch_gate_up_once_xb(const FwdArgs &a, const BranchTable &bt, int tiles, float *clear, int clear_n)
 {
-    const auto kernel = a.T <= 8 ? decode_gate_up_once<ONCE_NW, XB, 2, kRouted> : decode_gate_up_once<ONCE_NW, XB, 1, kRouted>;
-    kernel<<<tiles, ONCE_NW * 64, 0, a.stream>>>(
-        static_cast<const uint16_t *>(a.x), a.T, static_cast<const uint16_t *>(a.Wg), static_cast<const uint16_t *>(a.Wu),
-        a.d_model, static_cast<uint16_t *>(a.H), a.ldh, a.route, clear, clear_n, tiles, bt);
+    const auto kernel = a.T <= 8 ? decode_gate_up_once<NW, XB, 2, kRouted, kEdges, E> : decode_gate_up_once<NW, XB, 1, kRouted, kEdges, E>;
+    kernel<<<tiles, NW * 64, 0, a.stream>>>(
+        static_cast<const E *>(a.x), a.T, static_cast<const E *>(a.Wg), static_cast<const E *>(a.Wu),
+        a.d_model, static_cast<E *>(a.H), a.ldh, a.route, clear, clear_n, tiles, bt);
 }
-template <bool kRouted>
+// d_model is at most ONCE_MAX_D (bf16) or ROWS_MAX_D.
+template <bool kRouted, bool kEdges = false, typename E = uint16_t>
 static void launch_gate_up_once(const FwdArgs &a, const BranchTable &bt, int tiles, float *clear, int clear_n)
 {
-    static_assert(ONCE_MAX_D <= 6 * ONCE_NW * KB, "K blocks per wave");
-    const int xb = ceil_div(ceil_div(a.d_model, KB), ONCE_NW);
-    if (xb <= 2) launch_gate_up_once_xb<2, kRouted>(a, bt, tiles, clear, clear_n);
-    else if (xb <= 4) launch_gate_up_once_xb<4, kRouted>(a, bt, tiles, clear, clear_n);
-    else launch_gate_up_once_xb<6, kRouted>(a, bt, tiles, clear, clear_n);
+    static_assert(ONCE_MAX_D <= 6 * ONCE_NW * RowElem<uint16_t>::KBLK && ROWS_MAX_D <= 8 * 8 * RowElem<float>::KBLK, "K blocks per wave");
+    const int xb = ceil_div(ceil_div(a.d_model, RowElem<E>::KBLK), ONCE_NW);
+    if (xb <= 2) launch_gate_up_once_xb<ONCE_NW, 2, kRouted, kEdges, E>(a, bt, tiles, clear, clear_n);
+    else if (xb <= 4) launch_gate_up_once_xb<ONCE_NW, 4, kRouted, kEdges, E>(a, bt, tiles, clear, clear_n);
+    else if (xb <= 6) launch_gate_up_once_xb<ONCE_NW, 6, kRouted, kEdges, E>(a, bt, tiles, clear, clear_n);
+    if constexpr (kEdges || sizeof(E) == 4) {
+        if (xb > 6 && xb <= 8) launch_gate_up_once_xb<ONCE_NW, 8, kRouted, kEdges, E>(a, bt, tiles, clear, clear_n);
+        else if (xb > 8 && xb <= 12) launch_gate_up_once_xb<8, 6, kRouted, kEdges, E>(a, bt, tiles, clear, clear_n);
+        else if (xb > 12) launch_gate_up_once_xb<8, 8, kRouted, kEdges, E>(a, bt, tiles, clear, clear_n);
+    }
 }
 
 // 8 waves with 5 K blocks each requested as the kernel starts (8 blocks of half the size with 16 rows).
-template <int R, int NG, int KS, bool kRouted>
+template <int R, int NG, int KS, bool kRouted, bool kEdges = false, typename E = uint16_t>
 static void launch_down_rows(const FwdArgs &a, const BranchTable &bt)
 {
-    decode_down_rows<8, R == 16 ? 8 : 5, R, NG, KS, kRouted><<<dim3(ceil_div(a.d_model, R), KS), 8 * 64, 0, a.stream>>>(
-        static_cast<const uint16_t *>(a.H), a.ldh, a.T, static_cast<const uint16_t *>(a.Wd), a.d_inter, a.d_model, a.out,
+    decode_down_rows<8, R == 16 ? 8 : 5, R, NG, KS, kRouted, kEdges, E><<<dim3(ceil_div(a.d_model, R), KS), 8 * 64, 0, a.stream>>>(
+        static_cast<const E *>(a.H), a.ldh, a.T, static_cast<const E *>(a.Wd), a.d_inter, a.d_model, a.out,
         a.out_bf16 ? 1 : 0, a.route, bt);
+}
+
+// T <= 16, float storage or a bf16 table with odd boundaries (kEdges), sizes that decode_rows_takes accepts.
+template <bool kEdges, typename E>
+static hipError_t launch_decode_rows_impl(const FwdArgs &a, const BranchTable &bt)
+{
+    long long tiles = 0;
+    for (int r = 0; r < bt.n_runs; ++r) tiles += (bt.run_end[r] - bt.run_start[r] + 7) / 8;
+    {
+        ProfileScope ps(MLPMOE_KERNEL_DECODE_GATE_UP, a.stream);
+        launch_gate_up_once<false, kEdges, E>(a, bt, (int)tiles, a.out_bf16 ? nullptr : a.out, a.out_bf16 ? 0 : a.T * a.d_model);
+    }
+    if (launch_status("decode gate+up (rows) launch") != hipSuccess) return hipErrorLaunchFailure;
+    ProfileScope ps(MLPMOE_KERNEL_DECODE_DOWN, a.stream);
+    const int rows = down_shape(a.T, a.d_model, a.out_bf16);
+    if (!a.out_bf16) {
+        if (rows == 16) launch_down_rows<16, 1, 2, false, kEdges, E>(a, bt);
+        else a.T <= 8 ? launch_down_rows<8, 2, 2, false, kEdges, E>(a, bt) : launch_down_rows<8, 1, 2, false, kEdges, E>(a, bt);
+    }
+    if constexpr (sizeof(E) == 2) {
+        if (a.out_bf16 && rows == 8)
+            a.T <= 8 ? launch_down_rows<8, 2, 1, false, kEdges, E>(a, bt) : launch_down_rows<8, 1, 1, false, kEdges, E>(a, bt);
+        else if (a.out_bf16)
+            a.T <= 4 ? launch_down_rows<4, 4, 1, false, kEdges, E>(a, bt)
+                     : (a.T <= 8 ? launch_down_rows<4, 2, 1, false, kEdges, E>(a, bt) : launch_down_rows<4, 1, 1, false, kEdges, E>(a, bt));
+    }
+    return launch_status("decode down (rows) launch");
 }
 
 template <bool kRouted>
@@ -1009,5 +1105,28 @@ hipError_t launch_decode_bf16(const FwdArgs &a, const BranchTable &bt) { return 
 
 // Per-token routing, T <= 16: the kernels read a.route themselves and need no scratch.
 hipError_t launch_decode_routed_bf16(const FwdArgs &a, const BranchTable &bt) { return launch_decode_impl<true>(a, bt); }
+
+// Float storage, and bf16 tables with odd boundaries, at T <= 16: which sizes the row kernels take (else the prefill
+// kernels).  The line is where loading x and H once per workgroup, and with more than 8 tokens twice the MFMAs, costs as much as
+// the prefill kernels' idle token rows.  us a call, prefill / row kernels:
+//   odd boundaries, 12 branches, 9 kept, bf16 result: 1280 x 5000, T = 1 22.1 / 11.1, T = 16 23.0 / 16.6; 1600 x 6000, T = 1 26.2 /
+//     14.9, T = 16 27.4 / 22.2;
+//   floats: 512 x 2048, T = 1 19.4 / 7.8, T = 16 19.9 / 10.3; 896 x 4864, T = 1 31.1 / 19.4, T = 8 30.9 / 22.0, T = 12 31.0 / 31.9; 2048 x
+//     8000, T = 1 62.7 / 44.8, T = 8 62.9 / 52.0, T = 12 63.8 / 73.7.
+bool decode_rows_takes(int T, int d_model, bool out_bf16, bool is_bf16)
+{
+    if (T > 16 || d_model > ROWS_MAX_D || down_shape(T, d_model, out_bf16) == 0) return false;
+    return is_bf16 ? T * d_model <= 25600 : T <= 8 || T * d_model <= 8192;
+}
+
+hipError_t launch_decode_rows_bf16(const FwdArgs &a, const BranchTable &bt) { return launch_decode_rows_impl<true, uint16_t>(a, bt); }
+
+// d_model and d_inter are multiples of 4.
+hipError_t launch_decode_rows_f32(const FwdArgs &a, const BranchTable &bt)
+{
+    bool even = true;
+    for (int r = 0; r < bt.n_runs; ++r) even = even && bt.run_start[r] % 4 == 0 && bt.run_end[r] % 4 == 0;
+    return even ? launch_decode_rows_impl<false, float>(a, bt) : launch_decode_rows_impl<true, float>(a, bt);
+}
 
 }  // namespace mlpmoe

@@ -1,10 +1,13 @@
 """The decode kernels for narrow layers and small batches at the edges of their tiles and of the rules that pick them: 4, 8
 and 16 output features per workgroup, one and two K groups per MFMA (T = 4 / 5, 8 / 9), widths that end inside a K block,
-runs that start and end anywhere in steps of 8, branches that meet inside a tile, float and bf16 results, routing."""
+runs that start and end anywhere in steps of 8, branches that meet inside a tile, float and bf16 results, routing; tables
+with odd boundaries and float storage."""
 import numpy as np
 import pytest
 
-from gpu_util import check_bf16_flip_aware, flip_terms, run_gpu_with_hidden
+import test_gpu_f32_mfma
+import test_gpu_uneven
+from gpu_util import check_bf16_flip_aware, flip_terms, run_gpu, run_gpu_with_hidden
 from oracle import round_to_bf16
 from paper_2511_21089_amd import synth
 
@@ -69,3 +72,31 @@ def test_routed_rows(d_model, T):
     ones, _ = run_gpu_with_hidden(*L, route=np.ones((T, 4), np.uint8))
     plain, _ = run_gpu_with_hidden(*L)
     assert np.array_equal(ones, plain)
+
+
+SIZES = [(1, 72), (4, 1032), (5, 264), (8, 136), (9, 72), (16, 520), (3, 1544), (12, 1288)]
+
+
+@pytest.mark.parametrize("T,d_model", SIZES)
+@pytest.mark.parametrize("name", sorted(test_gpu_uneven.TABLES))
+def test_odd_boundaries(name, T, d_model):
+    """Runs that start and end inside a chunk, one run inside a chunk, runs of one neuron; NaN and infinities in every pruned
+    branch and in every H that is not written."""
+    args = test_gpu_uneven.make(name, T, d_model, seed=T)
+    bad = test_gpu_uneven.poison_pruned(args)
+    got, H = run_gpu_with_hidden(*bad)
+    active = np.repeat(args[6] != 0, np.diff(args[4]))
+    assert np.all(np.isnan(H[:, ~active])) and np.all(np.isfinite(got))
+    check_bf16_flip_aware(got, H, *args, label="%s T=%d:" % (name, T))
+    got16, H16 = run_gpu_with_hidden(*bad, out_bf16=True)
+    assert np.array_equal(H16[:, active], H[:, active])
+    f = flip_terms(H16, *args)
+    own = f["H"] @ f["Wd"].T
+    assert np.all(np.abs(got16 - own) <= f["sum_err"] + 2.0 ** -8 * (np.abs(own) + f["sum_err"]) + 1e-30)
+
+
+@pytest.mark.parametrize("T,d_model", [(1, 68), (4, 1028), (5, 260), (8, 132), (9, 4), (16, 516), (2, 2044), (12, 1284)])
+@pytest.mark.parametrize("name", sorted(test_gpu_f32_mfma.TABLES))
+def test_float_storage(name, T, d_model):
+    args = test_gpu_f32_mfma.make(*test_gpu_f32_mfma.TABLES[name], T, d_model, seed=T)
+    test_gpu_f32_mfma.check(run_gpu(*test_gpu_f32_mfma.poison_pruned(args)), *args)
