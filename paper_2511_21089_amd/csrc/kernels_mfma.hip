@@ -687,11 +687,12 @@ __device__ __forceinline__ bool tile_of(int id, int tiles_m, int tiles_n, int &t
 }
 
 // Scratch of the routed kernels, filled by route_tile_list from route[T, B]:
-//   tile_need[tm * B + b]  != 0 if some token of token tile tm (256 tokens) is routed to branch b;
-//   counts[g], list[g * stride + i]: the live gate+up tiles of token-tile group g (GROUP_M token
-//   tiles) in the order the kernel walks them: by N tile, then by token tile.  An entry is
-//   tn * gsz + (tm - g * GROUP_M), gsz = token tiles in the group.  A tile is live if some token of
-//   its token tile is routed to an active branch that owns one of its neurons.
+//   tile_need[tm * B + b]  bit h set if some token of half h (128 tokens) of token tile tm (256 tokens) is routed to branch b;
+//   counts[g], list[g * stride + i]: the live gate+up tiles of token-tile group g (GROUP_M token tiles), first those that
+//   both halves of their tokens need (list[g * stride + stride - 1] of them), then those that one half needs, each by N tile, then by
+//   token tile.  An entry is tn * gsz + (tm - g * GROUP_M), gsz = token tiles in the group, plus ROUTE_HALF times the half (1 or 2)
+//   that needs it.  A tile is live if some token of its token tile is routed to an active branch that owns one of its neurons.
+constexpr uint32_t ROUTE_HALF = 1u << 28;
 struct RouteTiles {
     const uint8_t *tile_need;
     const uint32_t *counts;
@@ -864,43 +865,95 @@ gate_up_mfma_mixed(const uint16_t *__restrict__ X, const uint16_t *__restrict__ 
 // (one contiguous stretch of the list per XCD), the ids left over exit.  The down projection skips the same (token
 // tile, branch) pairs, and H is multiplied by the token's route bit, so that it is exactly 0 where a token does not
 // take a branch.
-// How many tiles are live is known on the device only, so the split of the last round into halves or quarters (see
-// gate_up_mfma_mixed, same rule, also when there is no full round) is decided here by every workgroup.
-// 4096 x 14336, 16 branches, T = 1900, 7 sequences of 4 branches each (about 336 live tiles): 186 us against 205 us with a
-// second round of whole tiles (the whole call 292 against 312 us).  Workgroups past the last item cost nothing that
-// shows: a loop over the items in two rounds of workgroups instead took 194 us, in one round 185 us, and spills.
-// grid.x = 8 * (ids_per_xcd(all tiles) + kCUs / XCDS): the most workgroups any number of live tiles asks for.
+// Of a live tile that only one half of its 256 tokens needs (sequences of a few hundred tokens end inside nearly every tile: 140
+// of about 340 at 4096 x 14336, 16 branches, T = 1900, 7 sequences of 4 branches each) that half is computed, as two quarters of
+// 128 tokens x (64 + 64), and zeros are stored for the other; the quarters come after the whole tiles and fill the CUs that those
+// leave idle.  A quarter takes 3/8 of a whole tile's time (4096 features, all operands reused: 37 and 102 us, 2048: 22 and 58, 896: 13
+// and 33; 128 x (128 + 128) 71, 36 and 22, no less than two quarters).  Whole tiles may be cut into four as well: none, a last
+// partial round, or all, whichever ends first (T = 700, 60 tiles and 120 one-half tiles: cutting the last partial round whatever the rest
+// took 231 us, 180 as decided here, 182 before).  Without one-half tiles a last round of 65 to 128 tiles takes 256 x (64 + 64)
+// halves.  How many tiles are live is known on the device only, so every workgroup decides.  The call above: 165 -> 143 us, the
+// whole call 279 -> 263 us; 2048 x 8192, T = 500 81 -> 71; 4096 x 14336, T = 100 115 -> 97 us.
+// Workgroups past the last item cost nothing that shows.
+// grid.x = 8 * (ids_per_xcd(all tiles) + route_extra_ids(all tiles)): the most workgroups any number of live tiles asks for.
+struct RoutedSplit {
+    int cut;              // whole tiles that are cut
+    int pieces;           // into so many: 4 quarters or 2 halves
+};
+// When a round of `wholes` whole tiles (8 units of time each) and `quarters` (3 units) started in that order ends.
+__device__ __forceinline__ int routed_end(int wholes, int quarters)
+{
+    const int full = wholes / kCUs * 8, r = wholes % kCUs;
+    int m = r > 0 ? 8 : 0;
+    const int least = (3 * quarters + 8 * r) / kCUs;
+    m = m > least ? m : least;
+    while ((kCUs - r) * (m / 3) + (m > 8 ? r * ((m - 8) / 3) : 0) < quarters) ++m;
+    return full + m;
+}
+__device__ __forceinline__ RoutedSplit routed_split(int both, int singles)
+{
+    const int rest = both % kCUs;
+    if (singles == 0 && rest > kCUs / 4) return RoutedSplit{rest <= kCUs / 2 ? rest : 0, 2};
+    RoutedSplit best{0, 4};
+    int end = routed_end(both, 2 * singles);
+    const int with_rest = routed_end(both - rest, 2 * singles + 4 * rest);
+    if (with_rest < end) {
+        best.cut = rest;
+        end = with_rest;
+    }
+    if (both <= kCUs && routed_end(0, 2 * singles + 4 * both) < end) best.cut = both;
+    return best;
+}
+// 2 ids per one-half tile and 4 per whole tile that is cut (at most 256, fewer than 128 if in halves), beyond one per tile.
+__host__ __device__ inline int route_extra_ids(long long tiles) { return (int)((tiles + 3LL * kCUs) / XCDS) + 3; }
+
 template <int WM, bool kEdges>
 __global__ void __launch_bounds__(WM * 128)
 gate_up_mfma_routed(const uint16_t *__restrict__ X, const uint16_t *__restrict__ Wg,
                     const uint16_t *__restrict__ Wu, uint16_t *__restrict__ H, int T, int d_model, int ldh,
                     int tiles_m, const uint8_t *__restrict__ route, RouteTiles rt, BranchTable bt)
 {
+    constexpr int HALF = BM / 2;
     __shared__ __attribute__((aligned(1024))) char lds[lds_bytes(BM, 4)];
     const int groups = (tiles_m + GROUP_M - 1) / GROUP_M;
-    int total = 0;
-    for (int g = 0; g < groups; ++g) total += (int)rt.counts[g];
-    const int P = ids_per_xcd(total);
-    const int rest = total % kCUs;
-    const int parts = rest == 0 || rest > kCUs / 2 ? 1 : (rest <= kCUs / 4 ? 4 : 2);     // pieces of a left-over tile
-    const int whole_per_xcd = parts == 1 ? P : total / kCUs * (kCUs / XCDS);
+    int live = 0, both = 0;                            // live tiles, and those that both halves need
+    for (int g = 0; g < groups; ++g) {
+        live += (int)rt.counts[g];
+        both += (int)rt.list[(size_t)g * rt.stride + rt.stride - 1];
+    }
+    const int singles = live - both;
+    const RoutedSplit split = routed_split(both, singles);
+    const int wholes = both - split.cut, pieces = 2 * singles + split.pieces * split.cut;
     const int xcd = blockIdx.x % XCDS;
-    const int xcd_end = (xcd + 1) * P < total ? (xcd + 1) * P : total;
-    int k = blockIdx.x / XCDS, piece = -1;
-    if (k >= whole_per_xcd) {
-        if (parts == 1) return;
-        piece = (k - whole_per_xcd) % parts;
-        k = whole_per_xcd + (k - whole_per_xcd) / parts;
+    int k = blockIdx.x / XCDS;
+    const int whole_per_xcd = ids_per_xcd(wholes), piece_per_xcd = ids_per_xcd(pieces);
+    int whole = -1, single = -1, piece = -1;           // the item: which whole tile or which one-half tile, which piece of it
+    if (k < whole_per_xcd) {
+        whole = xcd * whole_per_xcd + k;
+        if (whole >= wholes) return;
+    } else {
+        k -= whole_per_xcd;
+        const int i = xcd * piece_per_xcd + k;
+        if (k >= piece_per_xcd || i >= pieces) return;
+        if (i < 2 * singles) {
+            single = i / 2;
+            piece = i % 2;
+        } else {
+            whole = wholes + (i - 2 * singles) / split.pieces;
+            piece = (i - 2 * singles) % split.pieces;
+        }
     }
-    const int logical = xcd * P + k;
-    if (logical >= xcd_end) return;
-    int g = 0, before = 0;
-    for (; g < groups - 1; ++g) {
-        const int c = (int)rt.counts[g];
-        if (logical < before + c) break;
-        before += c;
+    int g = 0, at = whole >= 0 ? whole : single;       // entry `at` of the group's whole tiles or one-half tiles
+    int first = 0;
+    for (;; ++g) {
+        const int c = (int)rt.counts[g], w = (int)rt.list[(size_t)g * rt.stride + rt.stride - 1];
+        const int n = whole >= 0 ? w : c - w;
+        first = whole >= 0 ? 0 : w;
+        if (at < n || g == groups - 1) break;
+        at -= n;
     }
-    const int e = (int)rt.list[(size_t)g * rt.stride + (logical - before)];
+    const uint32_t entry = rt.list[(size_t)g * rt.stride + first + at];
+    const int e = (int)(entry % ROUTE_HALF);
     const int m0 = g * GROUP_M;
     const int gsz = tiles_m - m0 < GROUP_M ? tiles_m - m0 : GROUP_M;
     const int tm = m0 + e % gsz, tn = e / gsz;
@@ -911,14 +964,31 @@ gate_up_mfma_routed(const uint16_t *__restrict__ X, const uint16_t *__restrict__
         return;
     }
     n0 += (piece % 2) * 64;
-    if (n0 >= n_end) return;                                       // the run ends in the first half
-    if (parts == 2) {
+    if (n0 >= n_end) return;                                       // the run ends in the first half of the neurons
+    if (n_end - n0 > 64) n_end = n0 + 64;
+    if (single < 0 && split.pieces == 2) {
         gate_up_tile<BM, WM, 2, 2, false, true, kEdges>(X, Wg, Wu, H, T, d_model, ldh, route, bt, lds, tm, n0, n_end);
-    } else {
-        const int tq = 2 * tm + piece / 2;                         // token tile of 128
-        if (tq * (BM / 2) >= T) return;                            // the last token tile ends in its first half
-        gate_up_tile<BM / 2, WM, 2, QUARTER_D, false, true, kEdges>(X, Wg, Wu, H, T, d_model, ldh, route, bt, lds, tq,
-                                                                    n0, n_end);
+        return;
+    }
+    // token tile of 128; some token needs it, so it exists
+    const int half = single >= 0 ? (int)(entry / ROUTE_HALF) : 1 + piece / 2;
+    gate_up_tile<HALF, WM, 2, QUARTER_D, false, true, kEdges>(X, Wg, Wu, H, T, d_model, ldh, route, bt, lds, 2 * tm + half - 1,
+                                                              n0, n_end);
+    if (single < 0) return;
+    // zeros for the other half, neurons n0 .. n_end - 1 (kEdges: those of active branches, noted by gate_up_tile)
+    const int *on = reinterpret_cast<const int *>(lds + 2 * BNH_MAX * sizeof(float));
+    const int t_first = (2 * tm + 2 - half) * HALF, t_last = t_first + HALF < T ? t_first + HALF : T;
+    for (int i = threadIdx.x; i < HALF * 8; i += WM * 128) {
+        const int t = t_first + i / 8, nl = i % 8 * 8;
+        if (t >= t_last || n0 + nl >= n_end) continue;
+        uint16_t *dst = H + (size_t)t * ldh + n0 + nl;
+        if constexpr (kEdges) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (on[nl + q]) dst[q] = 0;
+        } else {
+            *reinterpret_cast<u32x4 *>(dst) = u32x4{0, 0, 0, 0};
+        }
     }
 }
 
@@ -1054,28 +1124,22 @@ __global__ void __launch_bounds__(1024)
 route_tile_list(const uint8_t *__restrict__ route, uint8_t *__restrict__ tile_need, uint32_t *__restrict__ counts,
                 uint32_t *__restrict__ list, int stride, int T, int tiles_m, int tiles_n, BranchTable bt)
 {
-    __shared__ uint8_t need[GROUP_M][MLPMOE_MAX_BRANCHES];
-    __shared__ uint8_t live[ROUTE_MAX_TILES_N];
+    constexpr int HALVES = 2 * GROUP_M, HALF = BM / 2;
+    __shared__ uint8_t need[HALVES][MLPMOE_MAX_BRANCHES];
+    __shared__ uint16_t need_bits[MLPMOE_MAX_BRANCHES];    // bit h: half h of the group needs the branch
+    __shared__ uint16_t live[ROUTE_MAX_TILES_N];
     __shared__ int s_off[MLPMOE_MAX_BRANCHES + 1], s_run_start[MLPMOE_MAX_BRANCHES], s_run_end[MLPMOE_MAX_BRANCHES];
-    __shared__ int wave_sum[16];
+    __shared__ int wave_both[16], wave_one[16];
     const int B = bt.B;
     const int g = blockIdx.x, m0 = g * GROUP_M;
     const int gsz = tiles_m - m0 < GROUP_M ? tiles_m - m0 : GROUP_M;
-    for (int i = threadIdx.x; i < GROUP_M * MLPMOE_MAX_BRANCHES; i += 1024) (&need[0][0])[i] = 0;
+    for (int i = threadIdx.x; i < HALVES * MLPMOE_MAX_BRANCHES; i += 1024) (&need[0][0])[i] = 0;
     if (threadIdx.x < 64) {
-        // branch table -> LDS: constant indices keep the reads of the kernel arguments scalar
-        const int l = threadIdx.x;
-        int v_off = 0, v_start = 0, v_end = 0;
-#pragma unroll
-        for (int i = 0; i < MLPMOE_MAX_BRANCHES; ++i) v_off = l == i ? bt.off[i] : v_off;
-#pragma unroll
-        for (int i = 0; i < kMaxRuns; ++i) {
-            v_start = l == i ? bt.run_start[i] : v_start;
-            v_end = l == i ? bt.run_end[i] : v_end;
-        }
-        s_off[l] = v_off;
-        s_run_start[l] = v_start;
-        s_run_end[l] = v_end;
+        // branch table -> LDS, one entry per lane
+        const int l = threadIdx.x, r = l < kMaxRuns ? l : kMaxRuns - 1;
+        s_off[l] = bt.off[l];
+        s_run_start[l] = bt.run_start[r];
+        s_run_end[l] = bt.run_end[r];
         if (l == 0) s_off[MLPMOE_MAX_BRANCHES] = bt.off[MLPMOE_MAX_BRANCHES];
     }
     __syncthreads();
@@ -1102,7 +1166,7 @@ route_tile_list(const uint8_t *__restrict__ route, uint8_t *__restrict__ tile_ne
             int t = i / B, b = i - t * B;
 #pragma unroll
             for (int k = 0; k < 16; ++k) {
-                if (((v[u][k / 4] >> (8 * (k % 4))) & 0xffu) && !need[t / BM][b]) need[t / BM][b] = 1;
+                if (((v[u][k / 4] >> (8 * (k % 4))) & 0xffu) && !need[t / HALF][b]) need[t / HALF][b] = 1;
                 if (++b == B) {
                     b = 0;
                     ++t;
@@ -1121,13 +1185,21 @@ route_tile_list(const uint8_t *__restrict__ route, uint8_t *__restrict__ tile_ne
         for (int u = 0; u < 8; ++u)
             if (v[u]) {
                 const int i = i0 + u * 1024;
-                if (!need[(i / B) / BM][i % B]) need[(i / B) / BM][i % B] = 1;
+                if (!need[(i / B) / HALF][i % B]) need[(i / B) / HALF][i % B] = 1;
             }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < gsz * B; i += 1024) tile_need[(size_t)m0 * B + i] = need[i / B][i % B];
+    for (int i = threadIdx.x; i < gsz * B; i += 1024)
+        tile_need[(size_t)m0 * B + i] = need[2 * (i / B)][i % B] | need[2 * (i / B) + 1][i % B] << 1;
+    if (threadIdx.x < MLPMOE_MAX_BRANCHES) {
+        unsigned bits = 0;
+#pragma unroll
+        for (int h = 0; h < HALVES; ++h) bits |= need[h][threadIdx.x] ? 1u << h : 0u;
+        need_bits[threadIdx.x] = (uint16_t)bits;
+    }
+    __syncthreads();
 
-    // live[tn]: bit j says tile (m0 + j, tn) is live; one thread per N tile.  The branch table was
+    // live[tn]: bits 2 j, 2 j + 1 say that a half of tile (m0 + j, tn) is live; one thread per N tile.  The branch table was
     // copied to LDS above, so that the walks over runs and branches are chains of LDS reads.
     for (int tn = threadIdx.x; tn < tiles_n; tn += 1024) {
         int n0 = 0, n1 = 0, left = tn;
@@ -1145,36 +1217,54 @@ route_tile_list(const uint8_t *__restrict__ route, uint8_t *__restrict__ tile_ne
         for (int b = 0; b < B; ++b) {
             const int lo = s_off[b], hi = s_off[b + 1];
             if (!((bt.active >> b) & 1ULL) || hi <= lo || hi <= n0 || lo >= n1) continue;   // owns no neuron of the tile
-            for (int j = 0; j < GROUP_M; ++j) bits |= need[j][b] ? 1u << j : 0u;
+            bits |= need_bits[b];
         }
-        live[tn] = (uint8_t)bits;
+        live[tn] = (uint16_t)bits;
     }
     __syncthreads();
 
-    // compaction in list order (by N tile, then token tile): every thread takes a contiguous stretch
-    // of N tiles, an exclusive prefix over the threads gives its first position
+    // compaction in list order (by N tile, then token tile; tiles with both halves live first): every thread takes a contiguous
+    // stretch of N tiles, an exclusive prefix over the threads gives its first positions
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int per = (tiles_n + 1023) / 1024;
     const int tn0 = threadIdx.x * per;
     const int tn1 = tn0 + per < tiles_n ? tn0 + per : tiles_n;
-    int mine = 0;
-    for (int tn = tn0; tn < tn1; ++tn) mine += __popc((unsigned)live[tn]);
-    int incl = mine;
+    const auto both_of = [](unsigned l) { return l & (l >> 1) & 0x5555u; };      // bit 2 j: both halves of tile j
+    const auto one_of = [](unsigned l) { return (l ^ (l >> 1)) & 0x5555u; };     // bit 2 j: one of them
+    int n_both = 0, n_one = 0;
+    for (int tn = tn0; tn < tn1; ++tn) {
+        n_both += __popc(both_of(live[tn]));
+        n_one += __popc(one_of(live[tn]));
+    }
+    int incl_both = n_both, incl_one = n_one;
     for (int d = 1; d < 64; d <<= 1) {
-        const int v = __shfl_up(incl, d);
-        incl += lane >= d ? v : 0;
+        const int v = __shfl_up(incl_both, d), w = __shfl_up(incl_one, d);
+        incl_both += lane >= d ? v : 0;
+        incl_one += lane >= d ? w : 0;
     }
-    if (lane == 63) wave_sum[wave] = incl;
+    if (lane == 63) {
+        wave_both[wave] = incl_both;
+        wave_one[wave] = incl_one;
+    }
     __syncthreads();
-    int pos = incl - mine, total = 0;
+    int pos_both = incl_both - n_both, pos_one = incl_one - n_one, all_both = 0, all_one = 0;
     for (int w = 0; w < 16; ++w) {
-        pos += w < wave ? wave_sum[w] : 0;
-        total += wave_sum[w];
+        pos_both += w < wave ? wave_both[w] : 0;
+        pos_one += w < wave ? wave_one[w] : 0;
+        all_both += wave_both[w];
+        all_one += wave_one[w];
     }
-    if (threadIdx.x == 0) counts[g] = (uint32_t)total;
+    uint32_t *out = list + (size_t)g * stride;
+    if (threadIdx.x == 0) {
+        counts[g] = (uint32_t)(all_both + all_one);
+        out[stride - 1] = (uint32_t)all_both;
+    }
     for (int tn = tn0; tn < tn1; ++tn)
-        for (int j = 0; j < gsz; ++j)
-            if ((live[tn] >> j) & 1) list[(size_t)g * stride + pos++] = (uint32_t)(tn * gsz + j);
+        for (int j = 0; j < gsz; ++j) {
+            const unsigned h = (live[tn] >> (2 * j)) & 3u;
+            if (h == 3) out[pos_both++] = (uint32_t)(tn * gsz + j);
+            else if (h) out[all_both + pos_one++] = (uint32_t)(tn * gsz + j) + h * ROUTE_HALF;
+        }
 }
 
 // out[i] = sum_z partial[z][i], summed in z order: deterministic.  out_bf16: out holds bf16 values.
@@ -1527,13 +1617,13 @@ static hipError_t launch_gate_up_routed(const FwdArgs &a, const BranchTable &bt)
     const int tiles_m = ceil_div(a.T, BM);
     long long tiles_n = 0;
     for (int r = 0; r < bt.n_runs; ++r) tiles_n += ceil_div(bt.run_end[r] - bt.run_start[r], BNH_MAX);
-    const long long grid = (long long)XCDS * (ids_per_xcd(tiles_m * tiles_n) + kCUs / XCDS);
+    const long long grid = (long long)XCDS * (ids_per_xcd(tiles_m * tiles_n) + route_extra_ids(tiles_m * tiles_n));
     if (grid > 0x7fffffffLL) return note_hip_error("gate_up_mfma_routed grid", hipErrorInvalidValue);
     uint8_t *need = a.route_scratch;
     uint32_t *counts = reinterpret_cast<uint32_t *>(a.route_scratch + route_need_bytes(a.T));
     uint32_t *list = reinterpret_cast<uint32_t *>(a.route_scratch + route_need_bytes(a.T) + route_counts_bytes(a.T));
     const int stride = route_list_stride(a.d_inter);
-    if ((long long)GROUP_M * tiles_n > stride || tiles_n > ROUTE_MAX_TILES_N)
+    if ((long long)GROUP_M * tiles_n > stride - 1 || tiles_n > ROUTE_MAX_TILES_N)
         return note_hip_error("route tile list size", hipErrorInvalidValue);
     {
         ProfileScope ps(MLPMOE_KERNEL_ROUTE_TILES, a.stream);

@@ -4,7 +4,7 @@ branches switched on."""
 import numpy as np
 import pytest
 
-from gpu_util import C_SUM, U24, run_gpu_with_hidden, widen
+from gpu_util import C_SUM, U24, check_bf16_flip_aware, run_gpu_with_hidden, widen
 from paper_2511_21089_amd import synth
 
 pytestmark = pytest.mark.gpu
@@ -30,3 +30,25 @@ def test_live_tiles(tiles, T):
     assert np.array_equal(H[:, active], plain[:, active])
     Hd, W = np.where(active, plain, 0.0), widen(Wd).astype(np.float64)
     assert np.all(np.abs(got - Hd @ W.T) <= C_SUM * U24 * (np.abs(Hd) @ np.abs(W).T) + 1e-30)
+
+
+@pytest.mark.parametrize("T", [100, 128, 129, 256, 300, 700, 2100])
+@pytest.mark.parametrize("widths", [[128, 256, 64, 192, 128, 320], [4096, 2048, 8192, 4096], [101, 259, 65, 191, 130, 318]],
+                         ids=["small", "rounds", "odd"])
+def test_halves_of_token_tiles(widths, T):
+    """Halves of 256-token tiles that take other branches than the other half, branches that nobody takes, and halves that take
+    nothing: what one half alone needs is computed for it, and the other half's H is 0, not what the workspace held (NaN)."""
+    B = len(widths)
+    off = np.concatenate([[0], np.cumsum(widths)]).astype(np.int32)
+    rng = np.random.default_rng(T + B)
+    x, Wg, Wu, Wd = synth.random_layer(rng, T, 64, int(off[-1]), dtype="bf16", w_scale=0.1)
+    alpha = rng.uniform(0.8, 1.25, size=B).astype(np.float32)
+    route = np.zeros((T, B), np.uint8)
+    for lo in range(0, T, 128):
+        take = rng.uniform(size=B) < 0.4
+        route[lo:lo + 128] = take & (rng.uniform(size=(min(128, T - lo), B)) < 0.9)
+    mask = np.ones(B, np.uint8)
+    mask[B - 1] = 0
+    args = (x, Wg, Wu, Wd, off, alpha, mask)
+    got, H = run_gpu_with_hidden(*args, route=route)
+    check_bf16_flip_aware(got, H, *args, route=route, label="halves:")
