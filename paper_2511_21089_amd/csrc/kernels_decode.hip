@@ -16,6 +16,7 @@
 // Eight-neuron tiles keep the tile count a multiple of the CU count for the usual widths
 // (14336 / 8 = 7 * 256) and never straddle a run boundary (boundaries are multiples of 8).
 #include <mutex>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -54,6 +55,17 @@ __device__ __forceinline__ uint16_t to_bf16(float v)
     const __bf16 b = (__bf16)v;
     return __builtin_bit_cast(uint16_t, b);
 }
+
+// 16-byte loads of at most 2^31 bytes from `base`: lanes without anything to load (!ok) read zeros from past the end.
+struct Window {
+    __amdgpu_buffer_rsrc_t rsrc;
+    __device__ __forceinline__ Window(const void *base, unsigned bytes)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00027000)) {}
+    __device__ __forceinline__ u32x4 ld16(bool ok, unsigned offset) const
+    {
+        return __builtin_amdgcn_raw_buffer_load_b128(rsrc, ok ? offset : 0xffffffffu, 0, 0);
+    }
+};
 
 // Uses two registers that were just loaded, so that their loads are waited for here, once, and not at every lane read
 // in a loop that has weights in flight.
@@ -275,6 +287,8 @@ decode_kernel(const uint16_t *__restrict__ Xin, int ldx, int T,
 // added into `out` with float atomics: out must hold zeros when the kernel starts (the gate+up
 // kernel that runs before it clears it), and 0 + a + b is the same number in either order, so the
 // result does not depend on which workgroup comes first.  Few output features or few tokens: decode_down_rows.
+// Slots of the ring past a wave's last block, and absent tokens, read past the end of a buffer: zeros that nobody fetches
+// (with the gate+up kernel's last tile likewise: 4096 x 14336, T = 16 70.2 -> 68.8 us a step, T = 4 65.0 -> 64.4).
 template <int NW, int U, int RT, bool kRouted = false>
 __global__ void __launch_bounds__(NW * 64)
 decode_down_split(const uint16_t *__restrict__ Hin, int ldx, int T, const uint16_t *__restrict__ Wd, int ldw,
@@ -289,16 +303,16 @@ decode_down_split(const uint16_t *__restrict__ Hin, int ldx, int T, const uint16
     Stretches<kRouted> st(bt, route, T);
     arrived(st.v_beg, st.v_end);
     const int row0 = blockIdx.x * (16 * RT);
-    const uint16_t *wrow[RT];
+    const Window w(Wd + (size_t)row0 * ldw, 16u * RT * (unsigned)ldw * 2u), h(Hin, (unsigned)T * (unsigned)ldx * 2u);
+    unsigned w_lane[RT];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
-        int m = row0 + rt * 16 + r16;
-        m = m < d_model ? m : d_model - 1;               // clamped rows are computed but never stored
-        wrow[rt] = Wd + (size_t)m * ldw + q * KQ;
+        int m = rt * 16 + r16;
+        m = row0 + m < d_model ? m : d_model - 1 - row0; // clamped rows are computed but never stored
+        w_lane[rt] = ((unsigned)m * (unsigned)ldw + q * KQ) * 2u;
     }
     const bool tok = r16 < T;
-    const uint16_t *xp = Hin + (size_t)(tok ? r16 : 0) * ldx + q * KQ;
-    const uint16_t *zero = reinterpret_cast<const uint16_t *>(g_zero16);
+    const unsigned h_lane = ((unsigned)r16 * (unsigned)ldx + q * KQ) * 2u;
 
     // cursor over this wave's blocks.  The K blocks of all ranges, laid end to end, are cut into KS
     // contiguous parts, one per workgroup (a workgroup then reads long contiguous pieces of its rows);
@@ -324,7 +338,7 @@ decode_down_split(const uint16_t *__restrict__ Hin, int ldx, int T, const uint16
 
     u32x4 wa[U][RT][2], xa[U][2];
     auto load_block = [&](int u) {                       // loads the block under the cursor, then advances
-        const bool live = cr < n_ranges && issued < total;     // past its part a wave loads zeros
+        const bool live = cr < n_ranges && issued < total;     // past its part a wave asks for nothing
         ++issued;
         const int k = live ? st.beg(cr) + cb * KB : 0;
         const int kend = live ? st.end(cr) : -1;
@@ -332,11 +346,11 @@ decode_down_split(const uint16_t *__restrict__ Hin, int ldx, int T, const uint16
         const bool ok0 = kl < kend, ok1 = kl + KH < kend;
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
-            wa[u][rt][0] = ld16(ok0 ? wrow[rt] + k : zero);
-            wa[u][rt][1] = ld16(ok1 ? wrow[rt] + k + KH : zero);
+            wa[u][rt][0] = w.ld16(ok0, w_lane[rt] + k * 2);
+            wa[u][rt][1] = w.ld16(ok1, w_lane[rt] + (k + KH) * 2);
         }
-        xa[u][0] = ld16((ok0 && tok) ? xp + k : zero);
-        xa[u][1] = ld16((ok1 && tok) ? xp + k + KH : zero);
+        xa[u][0] = h.ld16(ok0 && tok, h_lane + k * 2);
+        xa[u][1] = h.ld16(ok1 && tok, h_lane + (k + KH) * 2);
         cb += stride;
         settle();
     };
@@ -590,7 +604,8 @@ decode_gate_up_xreg(const uint16_t *__restrict__ X, int T, const uint16_t *__res
     int it = 0;
     TileCursor<kRouted> cur(st, blockIdx.x);
     int row0 = cur.row0(st);
-    while (row0 >= 0) {
+    // one revolution of the ring; more: with the loads of the tiles behind it
+    const auto revolve = [&](auto more) {
 #pragma unroll
         for (int tt = 0; tt < TPR; ++tt) {           // tile tt of this revolution uses ring slots tt * XB ...
             if (row0 < 0) break;
@@ -602,7 +617,7 @@ decode_gate_up_xreg(const uint16_t *__restrict__ X, int T, const uint16_t *__res
                     const int u = XB < U ? tt * XB + ju : ju;
                     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wa[u][0]), as_bf16x8(xr[j0 + ju][0]), acc, 0, 0, 0);
                     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wa[u][1]), as_bf16x8(xr[j0 + ju][1]), acc, 0, 0, 0);
-                    load_next(u);
+                    if (decltype(more)::value) load_next(u);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -634,6 +649,14 @@ decode_gate_up_xreg(const uint16_t *__restrict__ X, int T, const uint16_t *__res
             cur.advance(st, grid);
             row0 = cur.row0(st);
         }
+    };
+    if constexpr (XB == U) {
+        // a revolution is a tile: the last one asks for nothing (the zeros it asked for otherwise were 128 KB on a CU's memory
+        // path, in front of its last stores)
+        while (row0 >= 0 && l_row0 >= 0) revolve(std::true_type{});
+        if (row0 >= 0) revolve(std::false_type{});
+    } else {
+        while (row0 >= 0) revolve(std::true_type{});
     }
 }
 
@@ -650,17 +673,6 @@ decode_gate_up_xreg(const uint16_t *__restrict__ X, int T, const uint16_t *__res
 // most 8 tokens the columns 8 .. 15 are the tokens again, at those same K elements, so that one MFMA does both halves: the
 // two diagonal blocks of the result are the two partial sums, what is off the diagonal is never used.  With more tokens
 // each half has an MFMA and an operand of its own (NG = K groups per MFMA, CT = token columns).
-
-// 16-byte loads of at most 2^31 bytes from `base`: lanes without anything to load (!ok) read zeros from past the end.
-struct Window {
-    __amdgpu_buffer_rsrc_t rsrc;
-    __device__ __forceinline__ Window(const void *base, unsigned bytes)
-        : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00027000)) {}
-    __device__ __forceinline__ u32x4 ld16(bool ok, unsigned offset) const
-    {
-        return __builtin_amdgcn_raw_buffer_load_b128(rsrc, ok ? offset : 0xffffffffu, 0, 0);
-    }
-};
 
 // What E, the storage type, and kEdges, a table whose run boundaries are not multiples of a 16-byte chunk, change: a chunk is
 // 8 bf16 values, one MFMA, or 4 floats, four v_mfma_f32_16x16x4_f32; SiLU is formed with expf and a division, as by the

@@ -1371,7 +1371,8 @@ void uneven_runs(const BranchTable &bt, UnevenRuns &u)
 // SLIM: 64 tokens x (64 + 64) with 4 waves and a staged ring of five K tiles requested ahead (144 KiB, one
 // workgroup per CU): the A rows of a K tile take a third of a stage, so more bytes of the B operand are in
 // flight per CU than with any other shape; for outputs with few token rows per output feature (a down
-// projection with a short d_model can then do without a K split) and for batches of at most 64 tokens.
+// projection with a short d_model can then do without a K split) and for gate+up projections whose 64-token tiles fit one
+// round of workgroups.
 enum TileShape { TILE_WIDE = 0, TILE_NARROW = 1, TILE_SMALL = 2, TILE_MIXED = 3, TILE_DEEP = 4, TILE_SLIM = 5 };
 constexpr int N_TILE_SHAPES = 6;
 constexpr int DEEP_D = 4, SLIM_D = 5;
