@@ -63,10 +63,11 @@ enum {
 
 /* Kernel path selection for the *_ws entry points. */
 enum {
-    MLPMOE_PATH_AUTO = 0,    /* library picks.  bf16: decode for T <= 16, MFMA otherwise and for branch boundaries
-                              * off a multiple of 8, generic if d_model or d_inter is not a multiple of 8.
-                              * Float storage (always AUTO): MFMA, generic if d_model or d_inter is not
-                              * a multiple of 4 and for routed calls                                       */
+    MLPMOE_PATH_AUTO = 0,    /* library picks.  bf16: decode for T <= 16, MFMA otherwise; with branch boundaries
+                              * off a multiple of 8 decode for small T * d_model (not routed), else MFMA; generic if
+                              * d_model or d_inter is not a multiple of 8.  Float storage (always AUTO): decode for
+                              * T <= 8 (narrow layers: 16), else MFMA, generic if d_model or d_inter is not a
+                              * multiple of 4 and for routed calls                                         */
     MLPMOE_PATH_GENERIC = 1, /* LDS-tiled FMA kernels: any shape and alignment                        */
     MLPMOE_PATH_MFMA = 2,    /* bf16 MFMA prefill kernels (needs d_model%8==0 and offsets%8==0)       */
     MLPMOE_PATH_DECODE = 3,  /* weight-streaming kernels, T <= 16 (same alignment needs as MFMA)      */
