@@ -61,7 +61,14 @@ constexpr int SMALL_WM = 2;                          // ... of the 128-token til
 constexpr int BM_SLIM = 64;                          // tokens per tile of the slim kernels: 4 waves of 32 x (32+32)
 constexpr int SLIM_WM = 2;
 
-enum { DST_F32 = 0, DST_BF16 = 1 };     // how down_mfma writes its result
+// How down_mfma writes its result.  DST_THROUGH: partial sums of at most THROUGH_BYTES, stored past the L2 (sc1), so that the end
+// of the kernel has no dirty lines to write back before the sum may start.  896 x 4864: T = 64 20.9 -> 20.3 us a call, T = 500 34.5 ->
+// 33.1, T = 333 in 12 branches, 9 kept 26.4 -> 25.7; 2048 x 5504, T = 100 34.7 -> 34.1.  Not for more bytes (4096 x 14336, T = 512, 67 MB:
+// 163.5 -> 168.3 with H stored so as well) nor where W_down itself streams from HBM (4096 x 14336: T = 100 85.2 -> 84.5, but T = 64 79.4 ->
+// 80.5).
+enum { DST_F32 = 0, DST_BF16 = 1, DST_THROUGH = 2 };
+constexpr size_t THROUGH_BYTES = 16u << 20, THROUGH_WEIGHTS = 64u << 20;      // partial sums, W_down
+constexpr int STORE_SC1 = 16;           // cache policy of a buffer store: sc1
 
 // 16 zero bytes: K chunks that fall past the end of a range are fetched from here.
 __device__ const uint32_t g_zero_chunk[4] = {0, 0, 0, 0};
@@ -993,7 +1000,7 @@ gate_up_mfma_routed(const uint16_t *__restrict__ X, const uint16_t *__restrict__
 }
 
 // grid.x = 8 * ids_per_xcd(splits * tilesM * tilesN); dst = out (splits == 1) or partial[split][T][d_model].
-// dst_mode: DST_F32 plain float stores; DST_BF16 (only with splits == 1) dst holds bf16 values, each sum
+// dst_mode: DST_F32 plain float stores, DST_THROUGH the same past the L2; DST_BF16 (only with splits == 1) dst holds bf16 values, each sum
 // rounded once (RNE).
 // kRouted: the K loop of token tile tm walks only the branches some token of the tile is routed
 // to (tile_need); H is 0 for the tokens of the tile that do not take a branch.
@@ -1094,6 +1101,21 @@ down_mfma(const E *__restrict__ H, const E *__restrict__ Wd, float *__restrict__
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int tcol = lane & 15, q4 = lane >> 4;
+    if (dst_mode == DST_THROUGH) {
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(dst, 0, (unsigned)THROUGH_BYTES, 0x00027000);
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            const int t = t0 + wm * (MI * 16) + i * 16 + tcol;
+#pragma unroll
+            for (int j = 0; j < 2 * NB; ++j) {
+                const int m = n0 + j / NB * BNH + wn * (16 * NB) + j % NB * 16 + 4 * q4;
+                if (t < T && m < d_model)
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, j < NB ? acc0[i][j % NB] : acc1[i][j % NB]), rsrc,
+                                                           (unsigned)(((z * T + t) * d_model + m) * 4), 0, STORE_SC1);
+            }
+        }
+        return;
+    }
     float *o = dst + (size_t)z * T * d_model;
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
@@ -1673,7 +1695,12 @@ static hipError_t launch_down(const FwdArgs &a, const BranchTable &bt, int split
     down_mfma<BMT, WM, NB, S::D, S::kStaged, kRouted, kEdges, kSerial><<<(unsigned)grid, WM * 128, 0, a.stream>>>(
         static_cast<const E *>(a.H), static_cast<const E *>(a.Wd),
         splits > 1 && !kSerial ? a.partial : a.out, a.T, a.d_model, a.d_inter, a.ldh, tiles_m, tiles_n, splits, kt_total,
-        (a.out_bf16 && splits == 1) ? DST_BF16 : DST_F32, a.route_scratch, bt, edges);
+        (a.out_bf16 && splits == 1) ? DST_BF16
+                                    : (splits > 1 && !kSerial && (size_t)splits * a.T * a.d_model * sizeof(float) <= THROUGH_BYTES &&
+                                               (size_t)a.d_model * a.d_inter * sizeof(E) <= THROUGH_WEIGHTS
+                                           ? DST_THROUGH
+                                           : DST_F32),
+        a.route_scratch, bt, edges);
     return launch_status("down_mfma launch");
 }
 

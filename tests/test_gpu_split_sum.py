@@ -37,3 +37,12 @@ def test_split_sum(mm, T, d_model, d_inter):
     assert np.all(np.abs(got - H @ W.T) <= bound)
     low, _ = run_gpu_with_hidden(*args, out_bf16=True)
     assert np.all(np.abs(low - got) <= 2.0 ** -8 * np.abs(got) + 1e-30)
+
+
+# Partial sums of at most 16 MiB under a W_down of at most 64 MiB are stored past the L2: around both limits (four splits
+# of 1170 x 896 floats end 4 KiB below 16 MiB; 4096 x 8192 is 64 MiB in bf16), and with tiles that end inside T and d_model.
+@pytest.mark.parametrize("T,d_model,d_inter", [
+    (65, 904, 4864), (129, 1032, 4096), (1170, 896, 4864), (1171, 896, 4864), (2048, 896, 4864), (65, 4096, 8192),
+    (65, 4096, 8200)])
+def test_partial_sums_around_the_store_limits(mm, T, d_model, d_inter):
+    test_split_sum(mm, T, d_model, d_inter)
