@@ -174,7 +174,8 @@ MLPMOE_API size_t mlpmoe_workspace_bytes(int T, int d_model, int d_inter, int B,
  *       alpha_b == 0 with the mask set is computed like any other value.
  *   T >= 0 tokens (T == 0 is a no-op), d_model >= 1, d_inter = branch_offsets[B] >= 0,
  *   1 <= B <= MLPMOE_MAX_BRANCHES.  d_b == 0 is legal.
- *   out    device float [T, d_model]; every element is written (zeros if nothing is active).
+ *   out    device float [T, d_model]; every element is written (zeros if nothing is active).  It may overlap x:
+ *          the result has the same bits (T <= 16: a launch more).
  *
  * Arithmetic: gate and up products accumulate in fp32; h = alpha_b * SiLU(g) * u is
  * formed in fp32 and rounded ONCE to bf16 (nearest even); the down projection

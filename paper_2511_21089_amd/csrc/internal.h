@@ -57,6 +57,7 @@ struct FwdArgs {
     const void *x, *Wg, *Wu, *Wd;
     float *out;         // [T, d_model] float, or the same number of bf16 values when out_bf16
     bool out_bf16 = false;
+    bool in_place = false;            // out overlaps x, W_gate or W_up: nothing of it is written before gate+up has ended
     int T, d_model, d_inter;
     void *H;            // gated intermediate [T, ldh], bf16 or float
     int ldh;

@@ -988,6 +988,14 @@ static void launch_down_rows(const FwdArgs &a, const BranchTable &bt)
         a.out_bf16 ? 1 : 0, a.route, bt);
 }
 
+// The sums that two workgroups add into need `out` at zero.  The gate+up kernel clears it beside its own work, except where
+// that would take x or weights from its other workgroups: a launch of its own then (896 x 4864, T = 8 in place: one launch more).
+static float *cleared_by_gate_up(const FwdArgs &a, bool added_into) { return added_into && !a.in_place ? a.out : nullptr; }
+static hipError_t clear_in_place(const FwdArgs &a, bool added_into)
+{
+    return added_into && a.in_place ? launch_fill_zero(a.out, (size_t)a.T * a.d_model, a.stream) : hipSuccess;
+}
+
 // T <= 16, float storage or a bf16 table with odd boundaries (kEdges), sizes that decode_rows_takes accepts.
 template <bool kEdges, typename E>
 static hipError_t launch_decode_rows_impl(const FwdArgs &a, const BranchTable &bt)
@@ -996,9 +1004,10 @@ static hipError_t launch_decode_rows_impl(const FwdArgs &a, const BranchTable &b
     for (int r = 0; r < bt.n_runs; ++r) tiles += (bt.run_end[r] - bt.run_start[r] + 7) / 8;
     {
         ProfileScope ps(MLPMOE_KERNEL_DECODE_GATE_UP, a.stream);
-        launch_gate_up_once<false, kEdges, E>(a, bt, (int)tiles, a.out_bf16 ? nullptr : a.out, a.out_bf16 ? 0 : a.T * a.d_model);
+        launch_gate_up_once<false, kEdges, E>(a, bt, (int)tiles, cleared_by_gate_up(a, !a.out_bf16), a.T * a.d_model);
     }
-    if (launch_status("decode gate+up (rows) launch") != hipSuccess) return hipErrorLaunchFailure;
+    if (launch_status("decode gate+up (rows) launch") != hipSuccess || clear_in_place(a, !a.out_bf16) != hipSuccess)
+        return hipErrorLaunchFailure;
     ProfileScope ps(MLPMOE_KERNEL_DECODE_DOWN, a.stream);
     const int rows = down_shape(a.T, a.d_model, a.out_bf16);
     if (!a.out_bf16) {
@@ -1033,8 +1042,8 @@ static hipError_t launch_decode_impl(const FwdArgs &a, const BranchTable &bt)
     // into `out` with atomics; `out` is cleared by the persistent gate+up kernel, so the pair is only used
     // together.
     const bool split_down = persistent && !a.out_bf16;
-    float *clear = split_down ? a.out : nullptr;
-    const int clear_n = split_down ? a.T * a.d_model : 0;
+    float *clear = cleared_by_gate_up(a, split_down);
+    const int clear_n = a.T * a.d_model;
     const uint16_t *Wg = static_cast<const uint16_t *>(a.Wg), *Wu = static_cast<const uint16_t *>(a.Wu);
     if (gate_up_once(a.T, a.d_model)) {
         ProfileScope ps(MLPMOE_KERNEL_DECODE_GATE_UP, a.stream);
@@ -1088,6 +1097,7 @@ static hipError_t launch_decode_impl(const FwdArgs &a, const BranchTable &bt)
             X, a.d_model, a.T, Wg, Wu, a.d_model, a.d_model, H, a.ldh, nullptr, 0, a.route, bt);
         if (launch_status("decode gate_up launch") != hipSuccess) return hipErrorLaunchFailure;
     }
+    if (clear_in_place(a, split_down) != hipSuccess) return hipErrorLaunchFailure;
     ProfileScope ps(MLPMOE_KERNEL_DECODE_DOWN, a.stream);
     const int rows = persistent ? down_shape(a.T, a.d_model, a.out_bf16) : 0;
     if (split_down && rows == 16)

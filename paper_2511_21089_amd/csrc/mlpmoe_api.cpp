@@ -113,6 +113,12 @@ size_t min_workspace_bytes(int T, int d_model, int d_inter, int B, int elem)
     return elem == 4 && full > 0 && T > 0 ? full - mfma_partial_bytes_f32(T, d_model, d_inter) : full;
 }
 
+bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
+{
+    const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
+    return p < q + b_bytes && q < p + a_bytes;
+}
+
 // Dispatch with a ready branch table: path choice, workspace carving, launch.  No loops over
 // branches, no allocation, no synchronisation.
 // route: per-token routing [T, B] on the device, or nullptr.  Routed calls use the kernels that skip
@@ -169,6 +175,9 @@ int forward_table(const BranchTable &bt, bool aligned, const void *x, const void
     FwdArgs a;
     a.x = x; a.Wg = Wg; a.Wu = Wu; a.Wd = Wd; a.out = out;
     a.out_bf16 = out_bf16;
+    const size_t out_bytes = (size_t)T * d_model * (out_bf16 ? 2 : 4), w_bytes = (size_t)d_inter * d_model * elem;
+    a.in_place = overlap(out, out_bytes, x, (size_t)T * d_model * elem) || overlap(out, out_bytes, Wg, w_bytes) ||
+                 overlap(out, out_bytes, Wu, w_bytes);
     a.T = T; a.d_model = d_model; a.d_inter = d_inter;
     a.H = workspace;
     a.ldh = h_ld(d_inter);

@@ -139,5 +139,22 @@ def unsplit_narrow():
         assert any("reduce_partials" in k for k in kernels(record())) == split, (d_model, d_inter, T)
 
 
+def in_place():
+    """A result over x: the decode gate+up kernel, whose workgroups read all of x, does not clear it; a launch behind it does."""
+    ptr = ctypes.c_void_p
+    for f, x, out, n in ((lib.mlpmoe_forward_f32, 1 << 20, 1 << 20, 3), (lib.mlpmoe_forward_f32, 1 << 20, (1 << 20) + 16, 3),
+                         (lib.mlpmoe_forward_f32, 1 << 20, (1 << 20) - 16, 3), (lib.mlpmoe_forward_bf16, 1 << 20, 1 << 20, 3),
+                         (lib.mlpmoe_forward_f32, 1 << 20, (1 << 20) + 8 * 256 * 4, 2),
+                         (lib.mlpmoe_forward_f32, 1 << 20, (1 << 20) - 8 * 256 * 4, 2),
+                         (lib.mlpmoe_forward_f32, 1 << 20, 2 << 20, 3), (lib.mlpmoe_forward_f32, 1 << 20, 3 << 20, 3)):
+        for widths in ([128, 128], [101, 155]):
+            off, alpha, on, d_inter, B = table(widths, [1, 0])
+            # W_gate and W_up at 2 and 3 MiB
+            assert f(ptr(x), ptr(2 << 20), ptr(3 << 20), ptr(8 << 20), off, alpha, on, 8, 256, d_inter, B, ptr(out), None) == OK
+            names = kernels(record())
+            assert len(names) == n and "gate_up_once" in names[0] and "down_rows" in names[-1], names
+            assert n == 2 or "fill_zero" in names[1], names
+
+
 globals()[sys.argv[1]]()
 print("ok")
