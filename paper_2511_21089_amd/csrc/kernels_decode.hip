@@ -923,13 +923,23 @@ decode_down_rows(const E *__restrict__ Hin, int ldx, int T, const E *__restrict_
     else out[at] = sum;
 }
 
-// The one-tile workgroups load x (2 T d_model bytes) once per 8 neurons (32 d_model bytes of weights).  Against the
-// ring kernel, us a step at T = 1, 8, 16: 640 features 11.4 / - / 11.9 (12.2 / - / 12.6), 896 14.6 / 15.8 / 17.5 (15.9 /
-// 16.8 / 17.9), 1280 15.5 / 16.9 / 19.5 (17.3 / 18.0 / 19.2), 1536 20.5 / 22.8 / 27.6 (22.4 / 23.2 / 24.9), 2048 25.4 / 28.0
-// / 32.1 (25.3 / 26.2 / 28.0).
-constexpr int ONCE_MAX_D = 1536, ONCE_NW = 4;
+// The one-tile workgroups start sooner than the ring kernel and load x (2 T d_model bytes) once per 8 neurons (32 d_model bytes
+// of weights): the rule bounds what they load of x in all, and with more than 8 tokens, where a K block takes twice the
+// loads and registers, d_model as well.  us a call, ring / one tile:
+//   T <= 8:  896 x 4800 T = 8 (8.6 MB of x) 12.1 / 11.2, 1280 x 6912 T = 8 (18 MB) 21.2 / 20.2, 1536 x 8256 T = 8 (25 MB) 24.3 / 24.2, 896 x
+//     16384 T = 8 (29 MB) 26.0 / 25.4;  past the line 896 x 24576 T = 8 (44 MB) 33.6 / 34.4, 1280 x 16384 T = 8 (42 MB) 37.5 / 38.5, 1280 x
+//     32768 T = 8 (84 MB) 66.6 / 68.5.  896 x 65536 T = 1 (15 MB) 69.3 / 68.0.
+//   T > 8:  640 x 3456 T = 16 (9 MB) 10.8 / 10.3, 896 x 4800 T = 16 (17 MB) 13.5 / 13.3, 1024 x 5504 T = 16 (23 MB) 15.5 / 15.4, 768 x 8192 T =
+//     16 (25 MB) 17.8 / 17.7;  past the line 896 x 8192 T = 16 (29 MB) 18.6 / 18.7, 896 x 16384 T = 10 (37 MB) 27.3 / 28.6, T = 16 29.9 / 32.4;
+//     1152 x 6208 T = 10 18.9 / 19.9, 1280 x 6912 T = 10 20.4 / 21.3, 1408 x 7552 T = 10 21.6 / 22.8.
+constexpr int ONCE_MAX_D = 1536, ONCE_MAX_D_16 = 1024, ONCE_NW = 4;
+constexpr long long ONCE_X_BYTES = 32 << 20, ONCE_X_BYTES_16 = 24 << 20;
 constexpr int ROWS_MAX_D = 2048;                         // float storage and odd boundaries: what 8 waves hold of x
-bool gate_up_once(int T, int d_model) { return d_model <= ONCE_MAX_D && T * d_model <= 14336; }
+bool gate_up_once(int T, int d_model, long long tiles)
+{
+    const long long x_bytes = 2LL * T * d_model * tiles;
+    return T <= 8 ? d_model <= ONCE_MAX_D && x_bytes <= ONCE_X_BYTES : d_model <= ONCE_MAX_D_16 && x_bytes <= ONCE_X_BYTES_16;
+}
 
 // Rows per workgroup of decode_down_rows, 0: the kernels for wide layers.  us a step with 4 / 8 / 16 rows and with the
 // wide kernels, the gate+up ring kernel before it.
@@ -1045,7 +1055,7 @@ static hipError_t launch_decode_impl(const FwdArgs &a, const BranchTable &bt)
     float *clear = cleared_by_gate_up(a, split_down);
     const int clear_n = a.T * a.d_model;
     const uint16_t *Wg = static_cast<const uint16_t *>(a.Wg), *Wu = static_cast<const uint16_t *>(a.Wu);
-    if (gate_up_once(a.T, a.d_model)) {
+    if (gate_up_once(a.T, a.d_model, tiles1)) {
         ProfileScope ps(MLPMOE_KERNEL_DECODE_GATE_UP, a.stream);
         launch_gate_up_once<kRouted>(a, bt, (int)tiles1, clear, clear_n);
         if (launch_status("decode gate+up (one tile per workgroup) launch") != hipSuccess) return hipErrorLaunchFailure;

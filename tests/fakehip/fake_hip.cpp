@@ -94,6 +94,7 @@ int hipGetDevice(int *d)
     return 0;
 }
 int hipSetDevice(int) { return 0; }
+int hipGetDevicePropertiesR0600(void *, int) { return 0; }      // the number of CUs stays what it was: only grids depend on it
 int hipDeviceSynchronize(void) { return 0; }
 int hipStreamSynchronize(void *) { return 0; }
 int hipFuncSetAttribute(const void *, int, int) { return 0; }
