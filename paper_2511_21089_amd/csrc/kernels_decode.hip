@@ -279,14 +279,15 @@ decode_kernel(const uint16_t *__restrict__ Xin, int ldx, int T,
     }
 }
 
-// Down projection of wide layers with RT row tiles (16 RT output features) per workgroup and the K blocks dealt to TWO
+// Down projection of wide layers and of a long K, with RT row tiles (16 RT output features) per workgroup and the K blocks dealt to TWO
 // workgroups (blockIdx.y).  Every workgroup of the one-tile
 // kernel reads all of H, which at 16 tokens is as many bytes as its weight rows, all from the same
 // L2; here a block of H is used for two weight fragments and each workgroup reads half of H, a quarter
 // of that traffic per weight byte, with all CUs still busy.  The two partial sums of an output are
 // added into `out` with float atomics: out must hold zeros when the kernel starts (the gate+up
 // kernel that runs before it clears it), and 0 + a + b is the same number in either order, so the
-// result does not depend on which workgroup comes first.  Few output features or few tokens: decode_down_rows.
+// result does not depend on which workgroup comes first.  RT = 1 with 16 waves: fewer output features and a
+// long K (down_long_k).  Few output features or few tokens otherwise: decode_down_rows.
 // Slots of the ring past a wave's last block, and absent tokens, read past the end of a buffer: zeros that nobody fetches
 // (with the gate+up kernel's last tile likewise: 4096 x 14336, T = 16 70.2 -> 68.8 us a step, T = 4 65.0 -> 64.4).
 template <int NW, int U, int RT, bool kRouted = false>
@@ -961,6 +962,19 @@ int down_shape(int T, int d_model, bool out_bf16)
     return T <= 8 || d_model <= 1024 ? 8 : 16;
 }
 
+// Layers of 1032 to 3064 features leave decode_down_rows with unequal numbers of workgroups per CU, or with idle CUs; while K is
+// short nobody waits for them, a long K is bound by the bytes in flight of the busiest CU, and 16 waves of decode_down_split on a row
+// tile have more.  K = neurons of active branches.  us a call, rows / 16 waves, K = 8192, 16384 and 32768:
+//   1280 T = 1 17.7 / 18.8, 30.9 / 30.2, 53.7 / 52.8;  T = 8 21.5 / 21.4, 38.5 / 35.7, 68.8 / 63.1;  T = 16 23.5 / 23.8, 39.9 / 38.8, 74.2 / 70.1
+//   2048 T = 1 23.5 / 25.4, 41.3 / 40.7, 74.9 / 75.6;  T = 8 25.6 / 26.3, 45.1 / 43.0, 82.0 / 78.9;  T = 16 28.4 / 28.0, 49.0 / 47.1, 88.7 / 85.3
+//   2560 T = 1 29.1 / 34.9, 53.7 / 58.3;  T = 8 33.0 / 37.5, 59.5 / 63.4;  T = 16 39.8 / 41.2, 72.2 / 70.3, 138.4 / 131.1
+//   1024 T = 1 24.4 / 26.7 (16384), T = 8 47.9 / 54.2 (32768), T = 16 53.7 / 60.9.
+bool down_long_k(int T, int d_model, int k)
+{
+    if (d_model <= 1024 || ceil_div(d_model, 16) >= WIDE_TILES) return false;
+    return T > 8 ? k > (d_model <= 2048 ? 8128 : 12288) : d_model <= 2048 && k > 12288;
+}
+
 constexpr size_t kStreamLdsMax = 160 * 1024;
 
 }  // namespace
@@ -1110,7 +1124,10 @@ static hipError_t launch_decode_impl(const FwdArgs &a, const BranchTable &bt)
     if (clear_in_place(a, split_down) != hipSuccess) return hipErrorLaunchFailure;
     ProfileScope ps(MLPMOE_KERNEL_DECODE_DOWN, a.stream);
     const int rows = persistent ? down_shape(a.T, a.d_model, a.out_bf16) : 0;
-    if (split_down && rows == 16)
+    if (split_down && down_long_k(a.T, a.d_model, bt.d_eff))
+        decode_down_split<16, 4, 1, kRouted><<<dim3(tiles2, 2), 16 * 64, 0, a.stream>>>(
+            H, a.ldh, a.T, static_cast<const uint16_t *>(a.Wd), a.d_inter, a.d_model, a.out, a.route, bt);
+    else if (split_down && rows == 16)
         launch_down_rows<16, 1, 2, kRouted>(a, bt);
     else if (split_down && rows == 8)
         a.T <= 8 ? launch_down_rows<8, 2, 2, kRouted>(a, bt) : launch_down_rows<8, 1, 2, kRouted>(a, bt);

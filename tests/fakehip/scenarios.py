@@ -167,5 +167,18 @@ def decode_gate_up():
         assert ("gate_up_once" if once else "gate_up_xreg") in name, (T, d_model, d_inter, name)
 
 
+def decode_down():
+    """Narrow layers with a long K: the 16-wave kernel adds up the halves; all others as before it."""
+    for T, d_model, d_inter, kernel in ((8, 1280, 12288, "down_rows"), (8, 1280, 12352, "down_splitILi16"), (16, 1280, 8128, "down_rows"),
+                                        (16, 1280, 8192, "down_splitILi16"), (1, 1032, 16384, "down_splitILi16"), (16, 1024, 32768, "down_rows"),
+                                        (8, 2056, 32768, "down_rows"), (16, 2560, 12288, "down_rows"), (16, 2560, 12296, "down_splitILi16"),
+                                        (16, 3064, 16384, "down_splitILi4")):
+        assert forward(lib.mlpmoe_forward_bf16, T, d_model, [d_inter]) == OK, lib.mlpmoe_last_error_detail()
+        name = kernels(record())[-1]
+        assert kernel in name, (T, d_model, d_inter, name)
+        assert forward(lib.mlpmoe_forward_bf16_out_bf16, T, d_model, [d_inter]) == OK
+        assert "down_split" not in kernels(record())[-1]
+
+
 globals()[sys.argv[1]]()
 print("ok")
