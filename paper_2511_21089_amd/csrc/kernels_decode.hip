@@ -947,16 +947,22 @@ bool gate_up_once(int T, int d_model, long long tiles)
 //   float (two workgroups per row tile with 8 and 16 rows, one with 4):
 //     896 T = 1 12.9 / 12.9 / 14.3 / 15.9, T = 16 16.8 / 14.8 / 16.7 / 17.9;  1280 T = 8 18.3 / 16.1 / 16.3 / 18.0, T = 16 22.8 /
 //     18.6 / 17.9 / 19.2;  2048 T = 1 22.8 / 23.0 / 25.5 / 25.3, T = 8 28.9 / 25.2 / 26.3 / 26.2, T = 16 37.1 / 29.7 / 28.1 / 28.0;
-//     2560 T = 1 29.5 / 29.6 / 33.6 / 36.2, T = 16 50.9 / 40.2 / 40.3 / 42.3;  4096 (K = 14336) T = 1 64.1 / 64.9 / 67.3 / 65.5,
-//     T = 4 72.8 / 68.2 / 70.1 / 66.1.  8 rows where 4 are as good: the order of the sum stays that of 64-element blocks.
+//     2560 T = 1 29.5 / 29.6 / 33.6 / 36.2, T = 16 50.9 / 40.2 / 40.3 / 42.3.  8 rows where 4 are as good: the order of the sum
+//     stays that of 64-element blocks.
+//     Wide layers, K = 3.5 d_model, 8 rows / wide kernel, T = 1, 2 and 4:  3072 41.2 / 42.6, 41.6 / 42.8, 42.8 / 43.2;  3584 54.2 / 53.9, 55.0 /
+//     54.4, 57.2 / 54.6;  4096 64.5 / 64.8, 65.3 / 65.2, 68.1 / 65.6;  5120 103.5 / 115.1, 104.4 / 116.2, 108.6 / 118.6;  6144 138.7 / 147.5,
+//     140.1 / 148.8, 147.2 / 151.3;  8192 234.1 / 239.6, 237.0 / 241.3, 247.6 / 242.7;  16384 x 16384 292.0 / 308.8, 294.2 / 310.0.
 //   bf16 result (one workgroup per row tile):
-//     896 T = 1 12.8 / 14.2 / 16.7 / 18.9, T = 16 16.8 / 17.8 / 21.7 / 22.2;  1280 T = 1 14.9 / 15.1 / 17.9 / 19.4, T = 8 18.3 / 16.5 /
-//     19.8 / 20.7;  2048 T = 1 22.8 / 23.9 / 27.3 / 28.0, T = 16 37.1 / 29.8 / 34.5 / 33.8;  2560 T = 1 29.5 / 32.1 / 32.4 / 32.7,
-//     T = 4 33.2 / 34.9 / 33.3 / 33.9, T = 16 50.9 / 45.6 / 39.8 / 38.9;  4096 T = 1 63.8 / 64.9 / 67.1 / 67.7.
+//     896 T = 1 12.8 / 14.2 / 16.7 / 18.9, T = 16 16.8 / 17.8 / 21.7 / 22.2;  1280 T = 8 18.3 / 16.5 / 19.8 / 20.7;  2048 T = 16 37.1 /
+//     29.8 / 34.5 / 33.8;  2560 T = 16 50.9 / 45.6 / 39.8 / 38.9.
+//     4 / 8 rows, K = 4.5 d_model, T = 1, 2 and 4:  1152 13.2 / 13.5, 13.8 / 13.9, 15.2 / 14.7;  1536 17.9 / 17.6, 18.6 / 18.0, 20.4 / 19.1 (K =
+//     8256, T = 2 20.7 / 21.2);  1792 21.6 / 22.2, 22.2 / 22.4, 23.9 / 23.2;  2048 25.5 / 26.4, 26.1 / 26.6, 27.9 / 27.2.
+//     4 rows / wide kernel, K = 3.5 d_model, T = 1, 2 and 4:  2560 32.3 / 37.0, 33.4 / 37.5, 36.3 / 38.3;  3584 53.8 / 55.4, 55.7 / 56.1, 60.7 /
+//     57.1;  4096 63.8 / 67.4, 65.7 / 68.3, 72.1 / 69.3;  6144 137.8 / 153.8, 141.3 / 155.9;  8192 232.7 / 237.2, 238.2 / 239.2, 262.5 / 243.8.
 constexpr int WIDE_TILES = 192;                          // row tiles of 16 from which the wide kernels fill the chip
 int down_shape(int T, int d_model, bool out_bf16)
 {
-    const bool few = T * (long long)d_model <= 4096;
+    const bool few = T <= 2;
     if (out_bf16) return d_model <= 1024 || few ? 4 : (d_model < 2560 ? 8 : 0);
     if (ceil_div(d_model, 16) >= WIDE_TILES) return few ? 8 : 0;
     return T <= 8 || d_model <= 1024 ? 8 : 16;

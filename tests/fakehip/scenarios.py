@@ -167,6 +167,18 @@ def decode_gate_up():
         assert ("gate_up_once" if once else "gate_up_xreg") in name, (T, d_model, d_inter, name)
 
 
+def decode_few_tokens():
+    """One or two tokens: fewer rows per workgroup, with a bf16 result and on every wide layer."""
+    f32, b16 = lib.mlpmoe_forward_bf16, lib.mlpmoe_forward_bf16_out_bf16
+    rows8, rows4 = "down_rowsILi8ELi5ELi8", "down_rowsILi8ELi5ELi4"
+    for f, T, d_model, kernel in ((f32, 1, 4096, rows8), (f32, 2, 4096, rows8), (f32, 3, 4096, "down_split"), (f32, 1, 16384, rows8),
+                                  (b16, 1, 1152, rows4), (b16, 2, 2056, rows4), (b16, 3, 1152, rows8),
+                                  (b16, 2, 8192, rows4), (b16, 3, 4096, "decode_kernel")):
+        assert forward(f, T, d_model, [1024]) == OK, lib.mlpmoe_last_error_detail()
+        name = kernels(record())[-1]
+        assert kernel in name, (T, d_model, name)
+
+
 def decode_down():
     """Narrow layers with a long K: the 16-wave kernel adds up the halves; all others as before it."""
     for T, d_model, d_inter, kernel in ((8, 1280, 12288, "down_rows"), (8, 1280, 12352, "down_splitILi16"), (16, 1280, 8128, "down_rows"),

@@ -20,6 +20,7 @@ CASES = [
     (1024, [1000, 24, 1024], [], 14), (1032, [520, 1528], [], 13), (1536, [2048, 64], [], 9), (1544, [1080], [], 3),
     (2552, [264, 512], [0], 16), (2560, [776], [], 1), (3064, [200, 312], [], 8), (3072, [512], [], 1), (3080, [264, 256], [], 2),
     (4096, [1024], [], 1), (4104, [328, 512], [1], 1),
+    (1792, [264], [], 2), (5128, [72], [], 2), (8200, [16, 56], [0], 1),
     (1032, [72, 12296, 24], [0], 3), (1800, [8200], [], 15), (2104, [8, 12480], [0], 9),      # a long K
 ]
 
