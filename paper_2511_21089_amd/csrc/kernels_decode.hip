@@ -929,17 +929,18 @@ decode_down_rows(const E *__restrict__ Hin, int ldx, int T, const E *__restrict_
 // loads and registers, d_model as well.  us a call, ring / one tile:
 //   T <= 8:  896 x 4800 T = 8 (8.6 MB of x) 12.1 / 11.2, 1280 x 6912 T = 8 (18 MB) 21.2 / 20.2, 1536 x 8256 T = 8 (25 MB) 24.3 / 24.2, 896 x
 //     16384 T = 8 (29 MB) 26.0 / 25.4;  past the line 896 x 24576 T = 8 (44 MB) 33.6 / 34.4, 1280 x 16384 T = 8 (42 MB) 37.5 / 38.5, 1280 x
-//     32768 T = 8 (84 MB) 66.6 / 68.5.  896 x 65536 T = 1 (15 MB) 69.3 / 68.0.
+//     32768 T = 8 (84 MB) 66.6 / 68.5.  896 x 65536 T = 1 (15 MB) 69.3 / 68.0, T = 4 (59 MB) 74.2 / 73.1; 1536 x 32768 T = 4 (50 MB) 65.6 / 65.6.
 //   T > 8:  640 x 3456 T = 16 (9 MB) 10.8 / 10.3, 896 x 4800 T = 16 (17 MB) 13.5 / 13.3, 1024 x 5504 T = 16 (23 MB) 15.5 / 15.4, 768 x 8192 T =
 //     16 (25 MB) 17.8 / 17.7;  past the line 896 x 8192 T = 16 (29 MB) 18.6 / 18.7, 896 x 16384 T = 10 (37 MB) 27.3 / 28.6, T = 16 29.9 / 32.4;
 //     1152 x 6208 T = 10 18.9 / 19.9, 1280 x 6912 T = 10 20.4 / 21.3, 1408 x 7552 T = 10 21.6 / 22.8.
 constexpr int ONCE_MAX_D = 1536, ONCE_MAX_D_16 = 1024, ONCE_NW = 4;
-constexpr long long ONCE_X_BYTES = 32 << 20, ONCE_X_BYTES_16 = 24 << 20;
+constexpr long long ONCE_X_BYTES_4 = 64 << 20, ONCE_X_BYTES_8 = 32 << 20, ONCE_X_BYTES_16 = 24 << 20;
 constexpr int ROWS_MAX_D = 2048;                         // float storage and odd boundaries: what 8 waves hold of x
 bool gate_up_once(int T, int d_model, long long tiles)
 {
     const long long x_bytes = 2LL * T * d_model * tiles;
-    return T <= 8 ? d_model <= ONCE_MAX_D && x_bytes <= ONCE_X_BYTES : d_model <= ONCE_MAX_D_16 && x_bytes <= ONCE_X_BYTES_16;
+    if (T > 8) return d_model <= ONCE_MAX_D_16 && x_bytes <= ONCE_X_BYTES_16;
+    return d_model <= ONCE_MAX_D && x_bytes <= (T > 4 ? ONCE_X_BYTES_8 : ONCE_X_BYTES_4);
 }
 
 // Rows per workgroup of decode_down_rows, 0: the kernels for wide layers.  us a step with 4 / 8 / 16 rows and with the

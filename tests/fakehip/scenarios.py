@@ -161,7 +161,7 @@ def decode_gate_up():
     for T, d_model, d_inter, once in ((1, 896, 4864, 1), (8, 896, 4864, 1), (16, 896, 4864, 1), (16, 1024, 5504, 1), (8, 1536, 8192, 1),
                                       (9, 1024, 4096, 1), (9, 1032, 4096, 0), (10, 1152, 6208, 0), (12, 1280, 6912, 0),
                                       (8, 1536, 10880, 1), (8, 1536, 11008, 0), (8, 1280, 32768, 0), (16, 896, 8192, 0),
-                                      (1, 896, 65536, 1), (1, 1544, 1024, 0)):
+                                      (4, 896, 65536, 1), (1, 1544, 1024, 0)):
         assert forward(lib.mlpmoe_forward_bf16, T, d_model, [d_inter]) == OK, lib.mlpmoe_last_error_detail()
         name = kernels(record())[0]
         assert ("gate_up_once" if once else "gate_up_xreg") in name, (T, d_model, d_inter, name)
