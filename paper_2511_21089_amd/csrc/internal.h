@@ -117,7 +117,7 @@ size_t route_scratch_bytes(int T, int d_inter);
 bool mfma_routed_holds(int d_inter);               // whatever the table
 hipError_t launch_mfma_routed_bf16(const FwdArgs &a, const BranchTable &bt, bool uneven);
 hipError_t launch_decode_bf16(const FwdArgs &a, const BranchTable &bt);
-bool decode_rows_takes(int T, int d_model, bool out_bf16, bool is_bf16);
+bool decode_rows_takes(int T, int d_model, int d_eff, bool out_bf16, bool is_bf16);
 hipError_t launch_decode_rows_bf16(const FwdArgs &a, const BranchTable &bt);     // odd boundaries
 hipError_t launch_decode_rows_f32(const FwdArgs &a, const BranchTable &bt);
 hipError_t launch_decode_routed_bf16(const FwdArgs &a, const BranchTable &bt);

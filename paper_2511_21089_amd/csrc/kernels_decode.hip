@@ -1166,13 +1166,16 @@ hipError_t launch_decode_routed_bf16(const FwdArgs &a, const BranchTable &bt) { 
 // kernels).  The line is where loading x and H once per workgroup, and with more than 8 tokens twice the MFMAs, costs as much as
 // the prefill kernels' idle token rows.  us a call, prefill / row kernels:
 //   odd boundaries, 12 branches, 9 kept, bf16 result: 1280 x 5000, T = 1 22.1 / 11.1, T = 16 23.0 / 16.6; 1600 x 6000, T = 1 26.2 /
-//     14.9, T = 16 27.4 / 22.2;
+//     14.9, T = 16 27.4 / 22.2; with more active neurons the prefill kernels fill the chip: 1280 features, 9222 neurons T = 12 29.5 / 28.9,
+//     T = 16 29.8 / 31.6, 12294 T = 8 28.9 / 27.5, T = 9 29.0 / 30.1, T = 16 29.5 / 36.2, 24582 T = 8 52.0 / 51.0, T = 16 52.8 / 70.3, 49158 T = 4 89.9 /
+//     86.9, T = 8 91.0 / 97.5; 1600 features, 9222 T = 9 30.6 / 30.0, T = 12 30.8 / 32.5;
 //   floats: 512 x 2048, T = 1 19.4 / 7.8, T = 16 19.9 / 10.3; 896 x 4864, T = 1 31.1 / 19.4, T = 8 30.9 / 22.0, T = 12 31.0 / 31.9; 2048 x
 //     8000, T = 1 62.7 / 44.8, T = 8 62.9 / 52.0, T = 12 63.8 / 73.7.
-bool decode_rows_takes(int T, int d_model, bool out_bf16, bool is_bf16)
+bool decode_rows_takes(int T, int d_model, int d_eff, bool out_bf16, bool is_bf16)
 {
     if (T > 16 || d_model > ROWS_MAX_D || down_shape(T, d_model, out_bf16) == 0) return false;
-    return is_bf16 ? T * d_model <= 25600 : T <= 8 || T * d_model <= 8192;
+    if (!is_bf16) return T <= 8 || T * d_model <= 8192;
+    return T * d_model <= 25600 && (T <= 4 || d_eff <= (T > 8 ? 8192 : 32768));
 }
 
 hipError_t launch_decode_rows_bf16(const FwdArgs &a, const BranchTable &bt) { return launch_decode_rows_impl<true, uint16_t>(a, bt); }

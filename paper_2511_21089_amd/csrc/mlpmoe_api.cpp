@@ -195,13 +195,13 @@ int forward_table(const BranchTable &bt, bool aligned, const void *x, const void
     // against 1007 us on the generic kernels) and a few tokens the decode kernels' row form; routed calls, other row lengths and more token rows than the generic
     // kernels' grid holds (an error there) stay where they were.
     if (!is_bf16 && !route && d_model % 4 == 0 && d_inter % 4 == 0 && T <= kGenericMaxTokens) {
-        e = decode_rows_takes(T, d_model, false, false) ? launch_decode_rows_f32(a, bt) : launch_mfma_f32(a, bt);
+        e = decode_rows_takes(T, d_model, bt.d_eff, false, false) ? launch_decode_rows_f32(a, bt) : launch_mfma_f32(a, bt);
     } else if (path == MLPMOE_PATH_GENERIC) {
         e = launch_generic(a, bt, is_bf16);
     } else if (route) {
         e = path == MLPMOE_PATH_MFMA ? launch_mfma_routed_bf16(a, bt, uneven) : launch_decode_routed_bf16(a, bt);
     } else if (path == MLPMOE_PATH_MFMA) {
-        e = uneven && decode_rows_takes(T, d_model, out_bf16, true) ? launch_decode_rows_bf16(a, bt) : launch_mfma_bf16(a, bt, uneven);
+        e = uneven && decode_rows_takes(T, d_model, bt.d_eff, out_bf16, true) ? launch_decode_rows_bf16(a, bt) : launch_mfma_bf16(a, bt, uneven);
     } else {
         e = launch_decode_bf16(a, bt);
     }

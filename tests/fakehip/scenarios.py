@@ -192,5 +192,15 @@ def decode_down():
         assert "down_split" not in kernels(record())[-1]
 
 
+def decode_odd_boundaries():
+    """Tables with odd boundaries and so many active neurons that the prefill kernels fill the chip stay on those."""
+    for T, d_model, active, rows in ((16, 896, 8191, 1), (9, 896, 8193, 0), (16, 1600, 8191, 1), (8, 1280, 32767, 1), (8, 1280, 32769, 0),
+                                     (4, 1280, 49157, 1), (1, 2048, 49157, 1), (13, 2048, 1001, 0), (17, 512, 1001, 0)):
+        for f in (lib.mlpmoe_forward_bf16, lib.mlpmoe_forward_bf16_out_bf16):
+            assert forward(f, T, d_model, [active, 8 - active % 8 + 64], [1, 0]) == OK, lib.mlpmoe_last_error_detail()
+            name = kernels(record())[0]
+            assert ("gate_up_once" if rows else "gate_up_mfma") in name, (T, d_model, active, name)
+
+
 globals()[sys.argv[1]]()
 print("ok")
