@@ -695,16 +695,20 @@ __device__ __forceinline__ bool tile_of(int id, int tiles_m, int tiles_n, int &t
 
 // Scratch of the routed kernels, filled by route_tile_list from route[T, B]:
 //   tile_need[tm * B + b]  bit h set if some token of half h (128 tokens) of token tile tm (256 tokens) is routed to branch b;
-//   counts[g], list[g * stride + i]: the live gate+up tiles of token-tile group g (GROUP_M token tiles), first those that
-//   both halves of their tokens need (list[g * stride + stride - 1] of them), then those that one half needs, each by N tile, then by
-//   token tile.  An entry is tn * gsz + (tm - g * GROUP_M), gsz = token tiles in the group, plus ROUTE_HALF times the half (1 or 2)
-//   that needs it.  A tile is live if some token of its token tile is routed to an active branch that owns one of its neurons.
-constexpr uint32_t ROUTE_HALF = 1u << 28;
+//   counts[g], list[g * stride + i]: the live gate+up tiles of token-tile group g (GROUP_M token tiles), as numbers tn * gsz +
+//   (tm - g * GROUP_M), gsz = token tiles in the group.  The lower 16 bits of the words have them by N tile, then by token tile; the
+//   upper 16 bits have first those that both halves of their tokens need (list[g * stride + stride - 1] of them), then those that one half
+//   needs, plus ROUTE_SECOND if it is the second half, each again by N tile, then by token tile.  Layers with larger numbers (d_inter beyond
+//   about 500000) have the first order alone, as whole words.  A tile is live if some token of its token tile is routed to an active
+//   branch that owns one of its neurons.
+constexpr uint32_t ROUTE_SECOND = 1u << 15;
 struct RouteTiles {
     const uint8_t *tile_need;
     const uint32_t *counts;
     const uint32_t *list;
     int stride;
+    bool words;           // list entries are whole words
+    int most;             // items that the grid has workgroups for
 };
 
 // N tile tn (counted over the runs of active branches, tiles of bnh neurons) -> its first neuron and
@@ -872,48 +876,58 @@ gate_up_mfma_mixed(const uint16_t *__restrict__ X, const uint16_t *__restrict__ 
 // (one contiguous stretch of the list per XCD), the ids left over exit.  The down projection skips the same (token
 // tile, branch) pairs, and H is multiplied by the token's route bit, so that it is exactly 0 where a token does not
 // take a branch.
-// Of a live tile that only one half of its 256 tokens needs (sequences of a few hundred tokens end inside nearly every tile: 140
-// of about 340 at 4096 x 14336, 16 branches, T = 1900, 7 sequences of 4 branches each) that half is computed, as two quarters of
-// 128 tokens x (64 + 64), and zeros are stored for the other; the quarters come after the whole tiles and fill the CUs that those
-// leave idle.  A quarter takes 3/8 of a whole tile's time (4096 features, all operands reused: 37 and 102 us, 2048: 22 and 58, 896: 13
-// and 33; 128 x (128 + 128) 71, 36 and 22, no less than two quarters).  Whole tiles may be cut into four as well: none, a last
-// partial round, or all, whichever ends first (T = 700, 60 tiles and 120 one-half tiles: cutting the last partial round whatever the rest
-// took 231 us, 180 as decided here, 182 before).  Without one-half tiles a last round of 65 to 128 tiles takes 256 x (64 + 64)
-// halves.  How many tiles are live is known on the device only, so every workgroup decides.  The call above: 165 -> 143 us, the
-// whole call 279 -> 263 us; 2048 x 8192, T = 500 81 -> 71; 4096 x 14336, T = 100 115 -> 97 us.
-// Workgroups past the last item cost nothing that shows.
-// grid.x = 8 * (ids_per_xcd(all tiles) + route_extra_ids(all tiles)): the most workgroups any number of live tiles asks for.
+// A live tile that only one half of its 256 tokens needs (sequences of a few hundred tokens end inside nearly every tile: 140
+// of about 340 at 4096 x 14336, 16 branches, T = 1900, 7 sequences of 4 branches each) is computed like the others, or for that half
+// alone: two quarters of 128 tokens x (64 + 64), which come after the whole tiles, and zeros stored for the other half.  How many
+// tiles are live is known on the device only, so every workgroup decides, from when each way would end on 256 CUs:
+//   like the others, a last round of at most 64 tiles as quarters, of at most 128 as halves of 256 x (64 + 64);
+//   one-half tiles as quarters that start as CUs come free, the other tiles whole;
+//   the same with the tiles of the last round that is not full cut into quarters too.
+// In units of a whole tile's time a half takes 0.55 and a quarter 0.45, fitted to 392 calls (896 x 4864, 2048 x 8192, 3072 x 18000, 4096 x
+// 14336; T = 60 .. 4000; 1 to 16 of 16 branches in 1 to 12 sequences), each timed all three ways.  The first way has to be 4 % longer by
+// the estimate: the others ask for the weights of an N tile twice, far apart.  us a call, first / second way, tiles that both halves and
+// one half need: 4096 x 14336, T = 60, 0 + 98 tiles 111 / 89; T = 550, 224 + 112 283 / 260; T = 1900, 196 + 147 266 / 246; 2048 x 8192, T = 1900,
+// 252 + 104 171 / 156; as long by the estimate: 4096 x 14336, T = 3000, 420 + 77 428 / 454, 3072 x 18000, T = 550, 76 + 170 185 / 206; estimated
+// shorter and not so: 3072 x 18000, T = 1398, 393 + 306 467 / 499.
+// A workgroup past the last item has a CU to itself for as long as it takes to find out: with room for two per tile, 4176 ids for 240
+// live tiles of 3072 x 18000 at T = 3000, the kernel took 90 us, with these ids 85.
+// grid.x = 8 * (ids_per_xcd(all tiles) + kCUs / XCDS): `most` is what it holds whatever the split, ways with more items are not taken.
 struct RoutedSplit {
-    int cut;              // whole tiles that are cut
+    bool merge;           // one-half tiles are computed like the others
+    int cut;              // tiles that are cut
     int pieces;           // into so many: 4 quarters or 2 halves
 };
-// When a round of `wholes` whole tiles (8 units of time each) and `quarters` (3 units) started in that order ends.
-__device__ __forceinline__ int routed_end(int wholes, int quarters)
+constexpr int ROUTED_WHOLE = 100, ROUTED_HALF = 55, ROUTED_QUARTER = 45;
+// When `quarters` end that start as CUs come free: `busy` of them after a whole tile (2.2 quarters), the others at once.
+__device__ __forceinline__ int routed_quarters_end(int busy, int quarters)
 {
-    const int full = wholes / kCUs * 8, r = wholes % kCUs;
-    int m = r > 0 ? 8 : 0;
-    const int least = (3 * quarters + 8 * r) / kCUs;
-    m = m > least ? m : least;
-    while ((kCUs - r) * (m / 3) + (m > 8 ? r * ((m - 8) / 3) : 0) < quarters) ++m;
-    return full + m;
+    const int idle = kCUs - busy;
+    // after a quarters on the idle CUs (the busy ones have done a - 3), or after b on the busy ones (the idle ones b + 2)
+    const int a = quarters <= 3 * idle ? (quarters + idle - 1) / idle : (quarters + 3 * busy + kCUs - 1) / kCUs;
+    const int left = quarters - 2 * idle, b = left > 0 ? (left + kCUs - 1) / kCUs : 0;
+    const int after_idle = a * ROUTED_QUARTER, after_busy = ROUTED_WHOLE + b * ROUTED_QUARTER;
+    if (busy == 0) return after_idle;
+    const int end = after_idle < after_busy ? after_idle : after_busy;
+    return end > ROUTED_WHOLE ? end : ROUTED_WHOLE;
 }
-__device__ __forceinline__ RoutedSplit routed_split(int both, int singles)
+__device__ __forceinline__ RoutedSplit routed_split(int both, int singles, const RouteTiles &rt)
 {
-    const int rest = both % kCUs;
-    if (singles == 0 && rest > kCUs / 4) return RoutedSplit{rest <= kCUs / 2 ? rest : 0, 2};
-    RoutedSplit best{0, 4};
-    int end = routed_end(both, 2 * singles);
-    const int with_rest = routed_end(both - rest, 2 * singles + 4 * rest);
-    if (with_rest < end) {
-        best.cut = rest;
-        end = with_rest;
+    const int live = both + singles, live_rest = live % kCUs, rest = both % kCUs;
+    const int parts = live_rest == 0 || live_rest > kCUs / 2 ? 1 : (live_rest <= kCUs / 4 ? 4 : 2);
+    RoutedSplit best{true, parts == 1 ? 0 : live_rest, parts == 1 ? 4 : parts};
+    if (singles == 0 || rt.words) return best;
+    int end = live / kCUs * ROUTED_WHOLE +
+              (live_rest == 0 ? 0 : (parts == 1 ? ROUTED_WHOLE : (parts == 2 ? ROUTED_HALF : ROUTED_QUARTER)));
+    end = both == 0 ? kOffEnd : end * 24 / 25;
+    const int rounds = both / kCUs * ROUTED_WHOLE;
+    const int cut_end = rounds + routed_quarters_end(0, 2 * singles + 4 * rest), whole_end = rounds + routed_quarters_end(rest, 2 * singles);
+    if (cut_end <= end && both + 3 * rest + 2 * singles <= rt.most) {
+        best = RoutedSplit{false, rest, 4};
+        end = cut_end;
     }
-    if (both <= kCUs && routed_end(0, 2 * singles + 4 * both) < end) best.cut = both;
+    if (whole_end <= end && both + 2 * singles <= rt.most) best = RoutedSplit{false, 0, 4};
     return best;
 }
-// 2 ids per one-half tile and 4 per whole tile that is cut (at most 256, fewer than 128 if in halves), beyond one per tile.
-__host__ __device__ inline int route_extra_ids(long long tiles) { return (int)((tiles + 3LL * kCUs) / XCDS) + 3; }
-
 template <int WM, bool kEdges>
 __global__ void __launch_bounds__(WM * 128)
 gate_up_mfma_routed(const uint16_t *__restrict__ X, const uint16_t *__restrict__ Wg,
@@ -928,8 +942,9 @@ gate_up_mfma_routed(const uint16_t *__restrict__ X, const uint16_t *__restrict__
         live += (int)rt.counts[g];
         both += (int)rt.list[(size_t)g * rt.stride + rt.stride - 1];
     }
+    const RoutedSplit split = routed_split(both, live - both, rt);
+    if (split.merge) both = live;
     const int singles = live - both;
-    const RoutedSplit split = routed_split(both, singles);
     const int wholes = both - split.cut, pieces = 2 * singles + split.pieces * split.cut;
     const int xcd = blockIdx.x % XCDS;
     int k = blockIdx.x / XCDS;
@@ -954,13 +969,13 @@ gate_up_mfma_routed(const uint16_t *__restrict__ X, const uint16_t *__restrict__
     int first = 0;
     for (;; ++g) {
         const int c = (int)rt.counts[g], w = (int)rt.list[(size_t)g * rt.stride + rt.stride - 1];
-        const int n = whole >= 0 ? w : c - w;
+        const int n = whole < 0 ? c - w : (split.merge ? c : w);
         first = whole >= 0 ? 0 : w;
         if (at < n || g == groups - 1) break;
         at -= n;
     }
-    const uint32_t entry = rt.list[(size_t)g * rt.stride + first + at];
-    const int e = (int)(entry % ROUTE_HALF);
+    const uint32_t word = rt.list[(size_t)g * rt.stride + first + at], entry = split.merge ? word % (2 * ROUTE_SECOND) : word >> 16;
+    const int e = (int)(rt.words ? word : entry % (split.merge ? 2 * ROUTE_SECOND : ROUTE_SECOND));
     const int m0 = g * GROUP_M;
     const int gsz = tiles_m - m0 < GROUP_M ? tiles_m - m0 : GROUP_M;
     const int tm = m0 + e % gsz, tn = e / gsz;
@@ -973,12 +988,12 @@ gate_up_mfma_routed(const uint16_t *__restrict__ X, const uint16_t *__restrict__
     n0 += (piece % 2) * 64;
     if (n0 >= n_end) return;                                       // the run ends in the first half of the neurons
     if (n_end - n0 > 64) n_end = n0 + 64;
-    if (single < 0 && split.pieces == 2) {
+    if (split.pieces == 2) {                                       // then one-half tiles are like the others
         gate_up_tile<BM, WM, 2, 2, false, true, kEdges>(X, Wg, Wu, H, T, d_model, ldh, route, bt, lds, tm, n0, n_end);
         return;
     }
-    // token tile of 128; some token needs it, so it exists
-    const int half = single >= 0 ? (int)(entry / ROUTE_HALF) : 1 + piece / 2;
+    const int half = 1 + (single >= 0 ? (int)(entry / ROUTE_SECOND) : piece / 2);
+    if ((2 * tm + half - 1) * HALF >= T) return;                   // the last token tile ends in its first half
     gate_up_tile<HALF, WM, 2, QUARTER_D, false, true, kEdges>(X, Wg, Wu, H, T, d_model, ldh, route, bt, lds, 2 * tm + half - 1,
                                                               n0, n_end);
     if (single < 0) return;
@@ -1144,7 +1159,7 @@ constexpr int ROUTE_MAX_TILES_N = 32768;           // N tiles of the gate+up pro
 template <int BNH>
 __global__ void __launch_bounds__(1024)
 route_tile_list(const uint8_t *__restrict__ route, uint8_t *__restrict__ tile_need, uint32_t *__restrict__ counts,
-                uint32_t *__restrict__ list, int stride, int T, int tiles_m, int tiles_n, BranchTable bt)
+                uint32_t *__restrict__ list, int stride, bool words, int T, int tiles_m, int tiles_n, BranchTable bt)
 {
     constexpr int HALVES = 2 * GROUP_M, HALF = BM / 2;
     __shared__ uint8_t need[HALVES][MLPMOE_MAX_BRANCHES];
@@ -1245,8 +1260,8 @@ route_tile_list(const uint8_t *__restrict__ route, uint8_t *__restrict__ tile_ne
     }
     __syncthreads();
 
-    // compaction in list order (by N tile, then token tile; tiles with both halves live first): every thread takes a contiguous
-    // stretch of N tiles, an exclusive prefix over the threads gives its first positions
+    // compaction into both orders of the list: every thread takes a contiguous stretch of N tiles, an exclusive prefix over the
+    // threads gives its first positions
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int per = (tiles_n + 1023) / 1024;
     const int tn0 = threadIdx.x * per;
@@ -1277,6 +1292,7 @@ route_tile_list(const uint8_t *__restrict__ route, uint8_t *__restrict__ tile_ne
         all_one += wave_one[w];
     }
     uint32_t *out = list + (size_t)g * stride;
+    uint16_t *out16 = reinterpret_cast<uint16_t *>(out);
     if (threadIdx.x == 0) {
         counts[g] = (uint32_t)(all_both + all_one);
         out[stride - 1] = (uint32_t)all_both;
@@ -1284,8 +1300,17 @@ route_tile_list(const uint8_t *__restrict__ route, uint8_t *__restrict__ tile_ne
     for (int tn = tn0; tn < tn1; ++tn)
         for (int j = 0; j < gsz; ++j) {
             const unsigned h = (live[tn] >> (2 * j)) & 3u;
-            if (h == 3) out[pos_both++] = (uint32_t)(tn * gsz + j);
-            else if (h) out[all_both + pos_one++] = (uint32_t)(tn * gsz + j) + h * ROUTE_HALF;
+            const uint32_t tile = (uint32_t)(tn * gsz + j);
+            const int pos = pos_both + pos_one;
+            if (!h) continue;
+            if (words) {
+                out[pos] = tile;
+            } else {
+                out16[2 * pos] = (uint16_t)tile;
+                out16[2 * (h == 3 ? pos_both : all_both + pos_one) + 1] = (uint16_t)(tile + (h == 2 ? ROUTE_SECOND : 0u));
+            }
+            if (h == 3) ++pos_both;
+            else ++pos_one;
         }
 }
 
@@ -1640,7 +1665,7 @@ static hipError_t launch_gate_up_routed(const FwdArgs &a, const BranchTable &bt)
     const int tiles_m = ceil_div(a.T, BM);
     long long tiles_n = 0;
     for (int r = 0; r < bt.n_runs; ++r) tiles_n += ceil_div(bt.run_end[r] - bt.run_start[r], BNH_MAX);
-    const long long grid = (long long)XCDS * (ids_per_xcd(tiles_m * tiles_n) + route_extra_ids(tiles_m * tiles_n));
+    const long long grid = (long long)XCDS * (ids_per_xcd(tiles_m * tiles_n) + kCUs / XCDS);
     if (grid > 0x7fffffffLL) return note_hip_error("gate_up_mfma_routed grid", hipErrorInvalidValue);
     uint8_t *need = a.route_scratch;
     uint32_t *counts = reinterpret_cast<uint32_t *>(a.route_scratch + route_need_bytes(a.T));
@@ -1648,16 +1673,18 @@ static hipError_t launch_gate_up_routed(const FwdArgs &a, const BranchTable &bt)
     const int stride = route_list_stride(a.d_inter);
     if ((long long)GROUP_M * tiles_n > stride - 1 || tiles_n > ROUTE_MAX_TILES_N)
         return note_hip_error("route tile list size", hipErrorInvalidValue);
+    const bool words = GROUP_M * tiles_n > (long long)ROUTE_SECOND;
     {
         ProfileScope ps(MLPMOE_KERNEL_ROUTE_TILES, a.stream);
         route_tile_list<BNH_MAX><<<ceil_div(tiles_m, GROUP_M), 1024, 0, a.stream>>>(
-            a.route, need, counts, list, stride, a.T, tiles_m, (int)tiles_n, bt);
+            a.route, need, counts, list, stride, words, a.T, tiles_m, (int)tiles_n, bt);
     }
     if (launch_status("route_tile_list launch") != hipSuccess) return hipErrorLaunchFailure;
     ProfileScope ps(MLPMOE_KERNEL_GATE_UP_MFMA, a.stream);
     gate_up_mfma_routed<MFMA_WM, kEdges><<<(unsigned)grid, MFMA_WM * 128, 0, a.stream>>>(
         static_cast<const uint16_t *>(a.x), static_cast<const uint16_t *>(a.Wg), static_cast<const uint16_t *>(a.Wu),
-        static_cast<uint16_t *>(a.H), a.T, a.d_model, a.ldh, tiles_m, a.route, RouteTiles{need, counts, list, stride}, bt);
+        static_cast<uint16_t *>(a.H), a.T, a.d_model, a.ldh, tiles_m, a.route,
+        RouteTiles{need, counts, list, stride, words, (int)grid - 2 * XCDS}, bt);
     return launch_status("gate_up_mfma_routed launch");
 }
 

@@ -202,5 +202,15 @@ def decode_odd_boundaries():
             assert ("gate_up_once" if rows else "gate_up_mfma") in name, (T, d_model, active, name)
 
 
+def routed_grid():
+    """The routed gate+up kernel has few more workgroups than there are tiles, and a grid that can be launched at the most tokens."""
+    for T, d_model, widths in ((3000, 3072, [1120] * 16), (1 << 24, 8, [136, 8] * 32)):
+        on = [1, 0] * 32 if len(widths) == 64 else None
+        assert forward(lib.mlpmoe_forward_routed_bf16, T, d_model, widths, on, True) == OK, lib.mlpmoe_last_error_detail()
+        name, grid = next((l[1], int(l[2])) for l in record() if l[0] == "launch" and "gate_up_mfma_routed" in l[1])
+        tiles = -(-T // 256) * (64 if on else 140)
+        assert tiles + 192 <= grid <= tiles + 300 and grid * 512 < 1 << 32, (T, tiles, grid)
+
+
 globals()[sys.argv[1]]()
 print("ok")

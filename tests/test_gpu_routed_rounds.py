@@ -32,6 +32,24 @@ def test_live_tiles(tiles, T):
     assert np.all(np.abs(got - Hd @ W.T) <= C_SUM * U24 * (np.abs(Hd) @ np.abs(W).T) + 1e-30)
 
 
+@pytest.mark.parametrize("tiles_n", [4096, 4097])
+def test_widest_tile_list(tiles_n):
+    """More N tiles than 16-bit list entries hold: 4096 tiles of 128 neurons for each of 8 token tiles."""
+    off = np.array([0, 64, tiles_n * 64 + 32, tiles_n * 128 - 8, tiles_n * 128], np.int32)
+    T, rng = 130, np.random.default_rng(tiles_n)
+    x, Wg, Wu, Wd = synth.random_layer(rng, T, 8, int(off[-1]), dtype="bf16", w_scale=0.1)
+    alpha, on = rng.uniform(0.8, 1.25, size=4).astype(np.float32), np.array([1, 0, 1, 1], np.uint8)
+    route = np.tile(on, (T, 1))
+    route[128:, 3] = 0
+    got, H = run_gpu_with_hidden(x, Wg, Wu, Wd, off, alpha, np.ones(4, np.uint8), route=route)
+    plain_out, plain = run_gpu_with_hidden(x, Wg, Wu, Wd, off, alpha, on)
+    active = np.repeat(on != 0, np.diff(off))
+    assert np.array_equal(H[:128, active], plain[:128, active])
+    assert np.array_equal(H[128:, active][:, :-8], plain[128:, active][:, :-8]) and not H[128:, -8:].any()
+    bound = C_SUM * U24 * (np.abs(plain[:, active]) @ np.abs(widen(Wd)[:, active]).T.astype(np.float64))
+    assert np.all(np.abs(got - plain_out)[:128] <= 2 * bound[:128])
+
+
 @pytest.mark.parametrize("T", [100, 128, 129, 256, 300, 700, 2100])
 @pytest.mark.parametrize("widths", [[128, 256, 64, 192, 128, 320], [4096, 2048, 8192, 4096], [101, 259, 65, 191, 130, 318]],
                          ids=["small", "rounds", "odd"])
