@@ -191,9 +191,9 @@ int forward_table(const BranchTable &bt, bool aligned, const void *x, const void
     a.route_scratch = reinterpret_cast<uint8_t *>(static_cast<char *>(workspace) + need - route_scratch_bytes(T, d_inter));
 
     hipError_t e;
-    // Float storage takes the MFMA kernels where rows are whole 16-byte pieces (256 tokens on 896 x 4864: 67 us
-    // against 1007 us on the generic kernels) and a few tokens the decode kernels' row form; routed calls, other row lengths and more token rows than the generic
-    // kernels' grid holds (an error there) stay where they were.
+    // Float storage takes the float MFMA kernels where rows are whole 16-byte pieces (256 tokens on 896 x 4864: 80 us
+    // against 1007 us on the generic kernels) and a few tokens the decode kernels' row form; routed calls, other row lengths
+    // and more token rows than the generic kernels' grid holds (an error there) stay where they were.
     if (!is_bf16 && !route && d_model % 4 == 0 && d_inter % 4 == 0 && T <= kGenericMaxTokens) {
         e = decode_rows_takes(T, d_model, bt.d_eff, false, false) ? launch_decode_rows_f32(a, bt) : launch_mfma_f32(a, bt);
     } else if (path == MLPMOE_PATH_GENERIC) {

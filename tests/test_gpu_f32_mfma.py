@@ -1,4 +1,4 @@
-"""Float storage on the MFMA kernels (d_model and d_inter multiples of 4): token and feature tails, K tails, runs
+"""Float storage on the float MFMA kernels (d_model and d_inter multiples of 4): token and feature tails, K tails, runs
 that start and end inside a 16-byte chunk, the K split with and without room for its partial sums.  Against float64,
 with the error fp32 sums may have and non-finite weights in every pruned branch."""
 import numpy as np
@@ -50,7 +50,7 @@ def poison_pruned(args):
     return x, Wg, Wu, Wd, off, alpha, mask
 
 
-def check(got, x, Wg, Wu, Wd, off, alpha, mask):
+def check(got, x, Wg, Wu, Wd, off, alpha, mask, floor=1e-30):
     h, g, u, ag, au = oracle.mlpmoe_hidden(x, Wg, Wu, off, alpha, mask, "exact", details=True)
     a = np.repeat(alpha.astype(np.float64) * (mask != 0), np.diff(off))
     sig = 1.0 / (1.0 + np.exp(-g))
@@ -62,7 +62,7 @@ def check(got, x, Wg, Wu, Wd, off, alpha, mask):
     aWd = np.abs(Wd.astype(np.float64))
     allow = dh @ aWd.T + C_SUM * U24 * (np.abs(h) @ aWd.T)
     assert np.all(np.isfinite(got))
-    assert np.all(np.abs(got - h @ Wd.astype(np.float64).T) <= allow + 1e-30)
+    assert np.all(np.abs(got - h @ Wd.astype(np.float64).T) <= allow + floor)
 
 
 @pytest.mark.parametrize("T,d_model", [(1, 68), (17, 4), (64, 96), (65, 132), (300, 64)])
@@ -139,7 +139,7 @@ def test_f32_token_tiles(mm, widths, mask, T):
 @pytest.mark.parametrize("T,d_model,widths", [(5, 64, [64, 64]), (70, 132, [129, 129, 258]), (40, 72, [4864])])
 def test_f32_infinities(mm, T, d_model, widths):
     """Infinities, NaNs and sums that overflow, in x and in every matrix: each result is the infinity or NaN that float
-    arithmetic gives, and everything else what it is without them.  Tiny values (below 2^-100) are held as well."""
+    arithmetic gives, and everything else what it is without them."""
     x, Wg, Wu, Wd, off, alpha, mask = make(widths, [1] * len(widths), T, d_model, seed=3)
     x[4] *= 1e-30
     clean = [a.copy() for a in (x, Wg, Wu, Wd)]
@@ -157,3 +157,34 @@ def test_f32_infinities(mm, T, d_model, widths):
     Wu[20, 9], Wd[4, 11], Wd[6, 13] = clean[2][20, 9], clean[3][4, 11], clean[3][6, 13]
     got = run_gpu(x, Wg, Wu, Wd, off, alpha, mask)[rows]
     check(got[:, cols], clean[0][rows], clean[1], clean[2], clean[3][cols], off, alpha, mask)
+
+
+@pytest.mark.parametrize("T", [70, 256])
+@pytest.mark.parametrize("scale", [1e-30, 1e-36, 1e30])
+def test_f32_magnitudes(mm, T, scale):
+    """Floats of any normal magnitude with all their 24 bits: tiny or huge x against W_gate and W_up the other way round, whose
+    products are of order 1, and tiny or huge W_down under results as tiny or huge."""
+    x, Wg, Wu, Wd, off, alpha, mask = make([64, 100], [1, 1], T, 64, seed=T)
+    up, down = np.float32(scale), np.float32(1 / scale)
+    a = (x * up, Wg * down, Wu * down, Wd, off, alpha, mask)
+    check(run_gpu(*a), *a)
+    a = (x, Wg, Wu, Wd * up, off, alpha, mask)
+    check(run_gpu(*a), *a, floor=1e-44)
+
+
+@pytest.mark.parametrize("n", [4, 8])
+def test_f32_short_sums(mm, n):
+    """Sums of so few products show what a product loses.  Rounding n partial sums, of which the k-th has k / n of the variance
+    of the last, leaves an error of sqrt(n / 6) U24 of a sum (a rounding has 1 / 3 U24^2); g, u and three roundings of h itself
+    sqrt(n / 3 + 1) U24 in the 2-norm, at most 1.92 U24 for n = 8."""
+    import torch
+    T = 256
+    args = make([64], [1], T, n, seed=n)
+    x, Wg, Wu, Wd, off, alpha, mask = [a * 10 if i in (1, 2) else a for i, a in enumerate(args)]
+    ws = mm.new_workspace(T, n, 64, 1, 4)
+    dev = [torch.from_numpy(a).cuda() for a in (x, Wg, Wu, Wd)]
+    mm.mlpmoe_forward_f32_ws(*dev, off, alpha, mask, ws)
+    torch.cuda.synchronize()
+    h = ws[:T * 64 * 4].view(torch.float32).view(T, 64).cpu().numpy().astype(np.float64)
+    want = oracle.mlpmoe_hidden(x, Wg, Wu, off, alpha, mask, "exact")
+    assert np.linalg.norm(h - want) <= 2 * U24 * np.linalg.norm(want)
