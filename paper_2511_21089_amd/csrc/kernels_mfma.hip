@@ -214,12 +214,25 @@ __device__ __forceinline__ KCursor k_seek(const KR &kr, int tile)
 // tile in the last round).  A B part of 64 + 64 rows fills half of its ring slot.
 // Float storage (E = float) differs only in what a 16-byte chunk holds: 4 K elements, fed to four
 // v_mfma_f32_16x16x4_f32 one after the other instead of one 16x16x32.
-template <int BMT, int WM, int NB, int D, bool kStaged, bool kRowsAreB, typename E, typename KR>
+// stops(kt): called with acc0, acc1 the sums over the K tiles before kt, at kt_end and where it said before; gives the next place.
+struct NoStops {
+    static constexpr bool kSome = false;
+    __device__ __forceinline__ int operator()(int) const { return 0; }
+};
+template <typename F>
+struct Stops {
+    static constexpr bool kSome = true;
+    const F &f;
+    int first;
+    __device__ __forceinline__ int operator()(int kt) const { return f(kt); }
+};
+template <int BMT, int WM, int NB, int D, bool kStaged, bool kRowsAreB, typename E, typename KR, typename St = NoStops>
 __device__ __forceinline__ void mainloop(const E *__restrict__ A_tile, int lda, int a_valid,
                                          const E *__restrict__ B0_tile,
                                          const E *__restrict__ B1_tile, int ldb, int b0_valid,
                                          int b1_valid, const KR &kr, int kt_begin, int kt_end, char *lds,
-                                         f32x4 (&acc0)[BMT / 16 / WM][NB], f32x4 (&acc1)[BMT / 16 / WM][NB])
+                                         f32x4 (&acc0)[BMT / 16 / WM][NB], f32x4 (&acc1)[BMT / 16 / WM][NB],
+                                         const St &stops = St{})
 {
     constexpr int BKE = Elem<E>::BK, CHUNK = Elem<E>::CHUNK;
     constexpr unsigned ES = sizeof(E);
@@ -425,17 +438,22 @@ __device__ __forceinline__ void mainloop(const E *__restrict__ A_tile, int lda, 
     for (int g = 0; g < N_PIECES; ++g) read_piece(f0, g, 0, 0);
 
     int rd = 0;                                   // byte offset in the ring of the A part of the tile in use
-    for (int it = 0; it < nk; ++it) {
-        const Part pa = part_of(qa, a_base, wa_dst, a_cl0);
-        k_step(f0, f1, rd, 1, 1, pa);             // + A part of tile it+D
-        advance(qa);
-        // tile it+1 has landed (the newer tiles and the A part just issued may be in flight); tile it's slots are free
-        pipeline_barrier<(D - 2) * (PL + PLB) + PL>();
-        rd = rd + RING_STEP < RING_BYTES ? rd + RING_STEP : rd + RING_STEP - RING_BYTES;
-        const Part pb = part_of(qb, b_base, wb_dst, b_cl0);
-        k_step(f1, f0, rd, 0, 2, pb);             // + B part of tile it+D
-        advance(qb);
-    }
+    int it = 0, until = nk;
+    if constexpr (St::kSome) until = stops.first - kt_begin;
+    do {
+        for (; it < until; ++it) {
+            const Part pa = part_of(qa, a_base, wa_dst, a_cl0);
+            k_step(f0, f1, rd, 1, 1, pa);             // + A part of tile it+D
+            advance(qa);
+            // tile it+1 has landed (the newer tiles and the A part just issued may be in flight); tile it's slots are free
+            pipeline_barrier<(D - 2) * (PL + PLB) + PL>();
+            rd = rd + RING_STEP < RING_BYTES ? rd + RING_STEP : rd + RING_STEP - RING_BYTES;
+            const Part pb = part_of(qb, b_base, wb_dst, b_cl0);
+            k_step(f1, f0, rd, 0, 2, pb);             // + B part of tile it+D
+            advance(qb);
+        }
+        if constexpr (St::kSome) until = stops(kt_begin + it) - kt_begin;
+    } while (it < nk);
     pipeline_barrier<0>();                        // LDS may be reused by the caller
 }
 
@@ -924,12 +942,13 @@ gate_up_mfma_routed(const uint16_t *__restrict__ X, const uint16_t *__restrict__
 // to (tile_need); H is 0 for the tokens of the tile that do not take a branch.
 // kEdges: bt holds the runs rounded inwards (kRouted: the table's own runs; the ranges of a tile are rounded here)
 // and `edges` (static tables) the partial chunks, which the last K split adds.
-// kSerial (no room for partial results): a workgroup goes through all splits of its tile and adds their sums up in the
-// order of reduce_partials, so that the result has the same bits; grid.x = 8 * ids_per_xcd(tilesM * tilesN), dst = out.
-template <int BMT, int WM, int NB, int D, bool kStaged, bool kRouted, bool kEdges, bool kSerial, typename E>
+// kSpans (no room for the partial results of all splits): workgroup z of a tile goes through splits z * span .. and adds their sums
+// up as reduce_partials does, `group` by group, so that the result has the same bits; grid.x = 8 * ids_per_xcd(spans * tilesM * tilesN),
+// dst = out for one span, else partial[span][T][d_model].
+template <int BMT, int WM, int NB, int D, bool kStaged, bool kRouted, bool kEdges, bool kSpans, typename E>
 __global__ void __launch_bounds__(WM * 128)
 down_mfma(const E *__restrict__ H, const E *__restrict__ Wd, float *__restrict__ dst, int T,
-          int d_model, int d_inter, int ldh, int tiles_m, int tiles_n, int splits, int kt_total, int dst_mode,
+          int d_model, int d_inter, int ldh, int tiles_m, int tiles_n, int splits, int kt_total, int dst_mode, int span, int group,
           const uint8_t *__restrict__ tile_need, BranchTable bt, std::conditional_t<kEdges && !kRouted, EdgeList, NoEdges> edges)
 {
     constexpr int BKE = Elem<E>::BK, CHUNK = Elem<E>::CHUNK;
@@ -939,7 +958,7 @@ down_mfma(const E *__restrict__ H, const E *__restrict__ Wd, float *__restrict__
     // eighth of that list: with K split, an XCD then works on few splits, whose slices of H and W_down are
     // what its L2 has to hold (the 0.5B-shaped layer at T = 2048: 4.7 MB per XCD instead of 12.5 MB).
     const int tiles = tiles_m * tiles_n;
-    const long long items = (long long)tiles * (kSerial ? 1 : splits);
+    const long long items = (long long)tiles * (kSpans ? (splits + span - 1) / span : splits);
     const int per_xcd = ids_per_xcd(items);
     const long long item = (long long)(blockIdx.x % XCDS) * per_xcd + blockIdx.x / XCDS;
     if (item >= items) return;
@@ -959,9 +978,8 @@ down_mfma(const E *__restrict__ H, const E *__restrict__ Wd, float *__restrict__
     f32x4 acc0[MI][NB], acc1[MI][NB];
     // the second block of output features may start past d_model: point it at the last row
     const int n1 = n0 + BNH < d_model ? n0 + BNH : d_model - 1;
-    const auto sum_split = [&](int part) {         // acc0, acc1 = the sums over K split `part`
-        const int kt_begin = (int)((long long)kt_total * part / splits);
-        const int kt_end = (int)((long long)kt_total * (part + 1) / splits);
+    const auto first_tile = [&](int part) { return (int)((long long)kt_total * part / splits); };
+    const auto clear = [&]() {
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -969,14 +987,18 @@ down_mfma(const E *__restrict__ H, const E *__restrict__ Wd, float *__restrict__
                 acc0[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
                 acc1[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
             }
+    };
+    // acc0, acc1 = the sums over K splits first .. last - 1, or since a stop last cleared them
+    const auto sum_splits = [&](int first, int last, const auto &stops) {
+        clear();
         if (kRouted)
             mainloop<BMT, WM, NB, D, kStaged, true>(H + (size_t)t0 * ldh, ldh, T - t0, Wd + (size_t)n0 * d_inter,
-                                        Wd + (size_t)n1 * d_inter, d_inter, d_model - n0, d_model - n1, dyn, kt_begin,
-                                        kt_end, lds, acc0, acc1);
+                                        Wd + (size_t)n1 * d_inter, d_inter, d_model - n0, d_model - n1, dyn,
+                                        first_tile(first), first_tile(last), lds, acc0, acc1, stops);
         else
             mainloop<BMT, WM, NB, D, kStaged, true>(H + (size_t)t0 * ldh, ldh, T - t0, Wd + (size_t)n0 * d_inter,
                                         Wd + (size_t)n1 * d_inter, d_inter, d_model - n0, d_model - n1, KRuns{bt},
-                                        kt_begin, kt_end, lds, acc0, acc1);
+                                        first_tile(first), first_tile(last), lds, acc0, acc1, stops);
         if constexpr (kEdges) {
             const auto edge_at = [&](int i, int &col, unsigned &mask) {
                 if constexpr (kRouted) {
@@ -989,31 +1011,49 @@ down_mfma(const E *__restrict__ H, const E *__restrict__ Wd, float *__restrict__
             int n_edges;
             if constexpr (kRouted) n_edges = 2 * raw.n;
             else n_edges = edges.n;
-            if (part == splits - 1)
+            if (last == splits)
                 edge_steps<MI, NB>(n_edges, edge_at, H + (size_t)t0 * ldh, ldh, T - t0, Wd + (size_t)n0 * d_inter,
                                    Wd + (size_t)n1 * d_inter, d_inter, d_model - n0, d_model - n1, acc0, acc1);
         }
     };
-    sum_split(z);
-    if constexpr (kSerial) {
-        f32x4 sum0[MI][NB], sum1[MI][NB];
-        for (int part = 1; part < splits; ++part) {
+    if constexpr (kSpans) {
+        f32x4 sum0[MI][NB], sum1[MI][NB], all0[MI][NB], all1[MI][NB];     // of the group, of the groups before it
+        const int first = z * span, last = first + span < splits ? first + span : splits;
+        int part = first;
+        const auto add_split = [&]() {
+            const int nth = part / group - first / group;                  // group of the split, from the first one on
+            const bool starts = part == first || part % group == 0;
 #pragma unroll
             for (int i = 0; i < MI; ++i)
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
-                    sum0[i][j] = acc0[i][j];
-                    sum1[i][j] = acc1[i][j];
+                    if (starts && nth > 0) {
+                        all0[i][j] = nth == 1 ? sum0[i][j] : all0[i][j] + sum0[i][j];
+                        all1[i][j] = nth == 1 ? sum1[i][j] : all1[i][j] + sum1[i][j];
+                    }
+                    sum0[i][j] = starts ? acc0[i][j] : sum0[i][j] + acc0[i][j];
+                    sum1[i][j] = starts ? acc1[i][j] : sum1[i][j] + acc1[i][j];
                 }
-            sum_split(part);
+        };
+        const auto next_split = [&](int kt) {
+            if (part + 1 == last) return kt;              // the last one: its edges are still to come
+            add_split();
+            clear();
+            ++part;
+            return first_tile(part + 1);
+        };
+        sum_splits(first, last, Stops<decltype(next_split)>{next_split, first_tile(first + 1)});
+        add_split();
+        const bool one_group = (last - 1) / group == first / group;
 #pragma unroll
-            for (int i = 0; i < MI; ++i)
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
-                for (int j = 0; j < NB; ++j) {
-                    acc0[i][j] = sum0[i][j] + acc0[i][j];
-                    acc1[i][j] = sum1[i][j] + acc1[i][j];
-                }
-        }
+            for (int j = 0; j < NB; ++j) {
+                acc0[i][j] = one_group ? sum0[i][j] : all0[i][j] + sum0[i][j];
+                acc1[i][j] = one_group ? sum1[i][j] : all1[i][j] + sum1[i][j];
+            }
+    } else {
+        sum_splits(z, z + 1, NoStops{});
     }
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1217,7 +1257,8 @@ route_tile_list(const uint8_t *__restrict__ route, uint8_t *__restrict__ tile_ne
         }
 }
 
-// out[i] = sum_z partial[z][i], summed in z order: deterministic.  out_bf16: out holds bf16 values.
+// out[i] = sum_z partial[z][i], summed in z order, kGroups: each `group` of them, then the groups: deterministic.  out_bf16: out
+// holds bf16 values.
 // n4 = pieces of four values (T * d_model is a multiple of 4 on this path; partial is 256-byte, out 16-byte
 // aligned).  A thread adds PIECES pieces per trip and has the loads of BATCH partial sums of each in flight.
 // Large results are bound by memory: two pieces far apart, one partial sum after the other (512 x 4096, 8 partial sums:
@@ -1225,14 +1266,14 @@ route_tile_list(const uint8_t *__restrict__ route, uint8_t *__restrict__ tile_ne
 // thread in small workgroups, which spreads them over the chip, and a batch of 8 (128 x 896, 18 partial sums: 9.2 ->
 // 6.2 us, 100 x 4096, 8: 6.7 -> 6.3 us).  The line is where one thread per piece fills the chip.
 constexpr size_t REDUCE_SMALL_N4 = 256 * 1024;
-template <int THREADS, int PIECES, int BATCH>
+template <int THREADS, int PIECES, int BATCH, bool kGroups>
 __global__ void __launch_bounds__(THREADS)
-reduce_partials(const float *__restrict__ partial, float *__restrict__ out, size_t n4, int splits, int out_bf16)
+reduce_partials(const float *__restrict__ partial, float *__restrict__ out, size_t n4, int splits, int group, int out_bf16)
 {
     const f32x4 *p4 = reinterpret_cast<const f32x4 *>(partial);
     const size_t stride = (size_t)gridDim.x * THREADS;
     for (size_t i = blockIdx.x * (size_t)THREADS + threadIdx.x; i < n4; i += PIECES * stride) {
-        f32x4 s[PIECES];
+        f32x4 s[PIECES], all[PIECES];                     // of the group, of the groups before it
 #pragma unroll
         for (int k = 0; k < PIECES; ++k) s[k] = i + k * stride < n4 ? p4[i + k * stride] : f32x4{0.f, 0.f, 0.f, 0.f};
         for (int z = 1; z < splits; z += BATCH) {
@@ -1247,9 +1288,21 @@ reduce_partials(const float *__restrict__ partial, float *__restrict__ out, size
 #pragma unroll
             for (int u = 0; u < BATCH; ++u)
                 if (z + u < splits) {
+                    if (kGroups && (z + u) % group == 0) {
+#pragma unroll
+                        for (int k = 0; k < PIECES; ++k) {
+                            all[k] = z + u == group ? s[k] : all[k] + s[k];
+                            s[k] = v[u][k];
+                        }
+                        continue;
+                    }
 #pragma unroll
                     for (int k = 0; k < PIECES; ++k) s[k] += v[u][k];
                 }
+        }
+        if (kGroups) {
+#pragma unroll
+            for (int k = 0; k < PIECES; ++k) s[k] = all[k] + s[k];
         }
 #pragma unroll
         for (int k = 0; k < PIECES; ++k) {
@@ -1612,41 +1665,44 @@ static hipError_t launch_gate_up_mixed(const FwdArgs &a, const BranchTable &bt)
     return launch_status("gate_up_mfma_mixed launch");
 }
 
-// bt: the K ranges (kEdges without routing: the inner runs, with their edges).  kSerial: all splits in one workgroup.
-template <typename S, bool kRouted = false, bool kEdges = false, bool kSerial = false, typename E = uint16_t>
+// bt: the K ranges (kEdges without routing: the inner runs, with their edges).  kSpans: `span` splits in one workgroup.
+template <typename S, bool kRouted = false, bool kEdges = false, bool kSpans = false, typename E = uint16_t>
 static hipError_t launch_down(const FwdArgs &a, const BranchTable &bt, int splits,
-                              const std::conditional_t<kEdges && !kRouted, EdgeList, NoEdges> &edges)
+                              const std::conditional_t<kEdges && !kRouted, EdgeList, NoEdges> &edges, int span = 1, int group = 1)
 {
     constexpr int BMT = S::BMT, WM = S::WM, NB = S::NB;
     const int tiles_m = ceil_div(a.T, BMT);
     const int tiles_n = ceil_div(a.d_model, 64 * NB);
     const int kt_total = k_tiles(bt, Elem<E>::BK);
-    const long long grid = (long long)XCDS * ids_per_xcd((long long)tiles_m * tiles_n * (kSerial ? 1 : splits));
+    const int sums = kSpans ? ceil_div(splits, span) : splits;      // partial results
+    const long long grid = (long long)XCDS * ids_per_xcd((long long)tiles_m * tiles_n * sums);
     if (grid > 0x7fffffffLL) return note_hip_error("down_mfma grid", hipErrorInvalidValue);
     ProfileScope ps(MLPMOE_KERNEL_DOWN_MFMA, a.stream);
-    down_mfma<BMT, WM, NB, S::D, S::kStaged, kRouted, kEdges, kSerial><<<(unsigned)grid, WM * 128, 0, a.stream>>>(
+    down_mfma<BMT, WM, NB, S::D, S::kStaged, kRouted, kEdges, kSpans><<<(unsigned)grid, WM * 128, 0, a.stream>>>(
         static_cast<const E *>(a.H), static_cast<const E *>(a.Wd),
-        splits > 1 && !kSerial ? a.partial : a.out, a.T, a.d_model, a.d_inter, a.ldh, tiles_m, tiles_n, splits, kt_total,
-        (a.out_bf16 && splits == 1) ? DST_BF16
-                                    : (splits > 1 && !kSerial && (size_t)splits * a.T * a.d_model * sizeof(float) <= THROUGH_BYTES &&
-                                               (size_t)a.d_model * a.d_inter * sizeof(E) <= THROUGH_WEIGHTS
-                                           ? DST_THROUGH
-                                           : DST_F32),
-        a.route_scratch, bt, edges);
+        sums > 1 ? a.partial : a.out, a.T, a.d_model, a.d_inter, a.ldh, tiles_m, tiles_n, splits, kt_total,
+        (a.out_bf16 && sums == 1) ? DST_BF16
+                                  : (sums > 1 && (size_t)sums * a.T * a.d_model * sizeof(float) <= THROUGH_BYTES &&
+                                             (size_t)a.d_model * a.d_inter * sizeof(E) <= THROUGH_WEIGHTS
+                                         ? DST_THROUGH
+                                         : DST_F32),
+        span, group, a.route_scratch, bt, edges);
     return launch_status("down_mfma launch");
 }
 
-// Adds up the partial results of a K split.
-static hipError_t reduce_splits(const FwdArgs &a, int splits)
+// Adds up the partial results of a K split, kGroups: `group` by `group`.
+template <bool kGroups = false>
+static hipError_t reduce_splits(const FwdArgs &a, int splits, int group = 0)
 {
     if (splits < 2) return hipSuccess;
     ProfileScope ps(MLPMOE_KERNEL_SPLITK_REDUCE, a.stream);
     const size_t n4 = (size_t)a.T * a.d_model / 4;
     if (n4 < REDUCE_SMALL_N4) {
-        reduce_partials<128, 1, 8><<<(unsigned)((n4 + 127) / 128), 128, 0, a.stream>>>(a.partial, a.out, n4, splits, a.out_bf16 ? 1 : 0);
+        reduce_partials<128, 1, 8, kGroups>
+            <<<(unsigned)((n4 + 127) / 128), 128, 0, a.stream>>>(a.partial, a.out, n4, splits, group, a.out_bf16 ? 1 : 0);
     } else {
         const size_t blocks = std::min<size_t>((n4 + 511) / 512, 4096);
-        reduce_partials<256, 2, 1><<<(unsigned)blocks, 256, 0, a.stream>>>(a.partial, a.out, n4, splits, a.out_bf16 ? 1 : 0);
+        reduce_partials<256, 2, 1, kGroups><<<(unsigned)blocks, 256, 0, a.stream>>>(a.partial, a.out, n4, splits, group, a.out_bf16 ? 1 : 0);
     }
     return launch_status("reduce_partials launch");
 }
@@ -1690,23 +1746,38 @@ hipError_t launch_mfma_routed_bf16(const FwdArgs &a, const BranchTable &bt, bool
                   : down_and_reduce<true, false>(a, bt, DownPlan{sh, splits}, NoEdges{});
 }
 
-// Float storage.  K split of the down projection: the factor with the shortest estimate.  A K tile of 32 floats takes a
-// workgroup that has its CU to itself 0.7 us (of which 0.43 matrix pipe: nothing hides its waits) and workgroups that
-// share a CU 0.45 us each, the first loads and the stores about 3 us, the separate sum about 4 us plus its traffic.
-// 896 x 4864, whole call, splits of about one workgroup per CU before: T = 256 91 -> 80 us (4 -> 9 splits), T = 500 158 ->
-// 134 us (2 -> 9).
-// Depends on T through whole token tiles only.
-static int f32_down_splits(int T, int d_model, int kt)
+// Float storage.  K split of the down projection in two steps: as many groups as are best where every workgroup has its CU to
+// itself, a K tile of 32 floats taking it 0.43 us of matrix pipe and the first loads and the stores about 2 us; then as many splits
+// per group as are best where the waits of one workgroup are hidden by others on its CU, a K tile taking 0.6 us alone and 0.42 us each
+// of several, and 3 us.  The separate sum takes about 4 us plus its traffic.  A block without room for the partial sums of all splits is
+// enough for those of the groups; a workgroup then goes through the splits of its group, or of all groups, without draining its
+// ring in between.  us a call with room for all, for the groups, for none: 896 x 4864, T = 256, 8 splits in 4 groups 80.3 / 81.5 / 159.5,
+// T = 500 135 / 140 / 190, T = 100 49.7 / 49.5 / 141; 4096 x 14336, T = 256, 2 in 1 784 / - / 889; splitting no further than the groups: 83.8 / - /
+// 161, 144 / - / 192, 53.6 / - / 152 and 885 / - / 885.  Depends on T through whole token tiles only.
+struct F32Split {
+    int groups, per_group;
+    int splits() const { return groups * per_group; }
+};
+static F32Split f32_split(int T, int d_model, int kt)
 {
     const long long tiles_m = ceil_div(T, ShapeF32::BMT), tiles = tiles_m * ceil_div(d_model, 64 * ShapeF32::NB);
-    int best = 1;
+    const int most = std::max(1, kt / 4) < 16 ? std::max(1, kt / 4) : 16;
+    const auto sum_us = [&](int s) { return s > 1 ? 4.0 + (s + 1.0) * (double)(tiles_m * ShapeF32::BMT) * d_model * 4.0 / 5e6 : 0.0; };
+    F32Split best{1, 1};
     double best_us = 1e30;
-    for (int s = 1; s <= 16 && s <= std::max(1, kt / 4); ++s) {
-        const double per_cu = (double)((tiles * s + kCUs - 1) / kCUs);
-        double us = ceil_div(kt, s) * std::max(0.7, 0.45 * per_cu) + 3.0;
-        if (s > 1) us += 4.0 + (s + 1.0) * (double)(tiles_m * ShapeF32::BMT) * d_model * 4.0 / 5e6;
+    for (int s = 1; s <= most; ++s) {
+        const double us = (double)((tiles * s + kCUs - 1) / kCUs) * (ceil_div(kt, s) * 0.43 + 2.0) + sum_us(s);
         if (us < best_us) {
-            best = s;
+            best.groups = s;
+            best_us = us;
+        }
+    }
+    best_us = 1e30;
+    for (int g = 1; g * best.groups <= most; ++g) {
+        const int s = g * best.groups;
+        const double per_cu = (double)((tiles * s + kCUs - 1) / kCUs), us = ceil_div(kt, s) * std::max(0.6, 0.42 * per_cu) + 3.0 + sum_us(s);
+        if (us < best_us) {
+            best.per_group = g;
             best_us = us;
         }
     }
@@ -1725,7 +1796,7 @@ static int pick_f32_tokens(long long tiles_n, int T)
 
 size_t mfma_partial_bytes_f32(int T, int d_model, int d_inter)
 {
-    const int s = f32_down_splits(T, d_model, ceil_div(d_inter, Elem<float>::BK));
+    const int s = f32_split(T, d_model, ceil_div(d_inter, Elem<float>::BK)).splits();
     return s > 1 ? align_up((size_t)s * T * d_model * sizeof(float), 256) : 0;
 }
 
@@ -1742,14 +1813,21 @@ static hipError_t launch_mfma_f32_runs(const FwdArgs &a, const BranchTable &oute
                                        : launch_gate_up<ShapeF32Half, kEdges, float>(a, outer));
     if (e != hipSuccess) return hipErrorLaunchFailure;
     // The order of the sums depends on the sizes and the table alone: at most the splits that the workspace is sized for
-    // (short runs have more K tiles than the width they add up to), and a workspace without room for the partial sums
-    // changes who adds them up, not the result (896 x 4864, T = 256: 161 us in the least block, 86 us in a full one).
-    const int splits = std::min(f32_down_splits(a.T, a.d_model, k_tiles(inner, Elem<float>::BK)),
-                                f32_down_splits(a.T, a.d_model, ceil_div(a.d_inter, Elem<float>::BK)));
-    if (splits > 1 && (size_t)splits * a.T * a.d_model * sizeof(float) > a.partial_bytes)
-        return launch_down<ShapeF32, false, kEdges, true, float>(a, inner, splits, edges);
-    if (launch_down<ShapeF32, false, kEdges, false, float>(a, inner, splits, edges) != hipSuccess) return hipErrorLaunchFailure;
-    return reduce_splits(a, splits);
+    // (short runs have more K tiles than the width they add up to), and a workspace without room for all partial sums
+    // changes who adds them up, not the result.
+    F32Split sp = f32_split(a.T, a.d_model, k_tiles(inner, Elem<float>::BK));
+    const F32Split layer = f32_split(a.T, a.d_model, ceil_div(a.d_inter, Elem<float>::BK));
+    sp.groups = std::min(sp.groups, layer.groups);
+    sp.per_group = std::min(sp.per_group, layer.splits() / sp.groups);
+    const int splits = sp.splits(), group = sp.per_group, groups = sp.groups;
+    const size_t room = a.partial_bytes / ((size_t)a.T * a.d_model * sizeof(float));
+    if (splits == 1 || (size_t)splits <= room) {
+        if (launch_down<ShapeF32, false, kEdges, false, float>(a, inner, splits, edges) != hipSuccess) return hipErrorLaunchFailure;
+        return groups > 1 && group > 1 ? reduce_splits<true>(a, splits, group) : reduce_splits(a, splits);
+    }
+    const int span = (size_t)groups <= room ? group : splits;
+    if (launch_down<ShapeF32, false, kEdges, true, float>(a, inner, splits, edges, span, group) != hipSuccess) return hipErrorLaunchFailure;
+    return reduce_splits(a, ceil_div(splits, span));
 }
 
 // d_model and d_inter are multiples of 4.

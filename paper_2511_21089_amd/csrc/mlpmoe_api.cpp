@@ -182,6 +182,9 @@ int forward_table(const BranchTable &bt, bool aligned, const void *x, const void
     a.H = workspace;
     a.ldh = h_ld(d_inter);
     a.partial_bytes = need - h_bytes(T, d_inter, elem) - route_scratch_bytes(T, d_inter) - 256;
+    // float storage, a block too small for all partial sums: the room there is
+    if (elem == 4 && !route && workspace_bytes < mlpmoe_workspace_bytes(T, d_model, d_inter, bt.B, elem))
+        a.partial_bytes = (workspace_bytes - need) / 256 * 256;
     a.partial = a.partial_bytes
                     ? reinterpret_cast<float *>(static_cast<char *>(workspace) + h_bytes(T, d_inter, elem))
                     : nullptr;

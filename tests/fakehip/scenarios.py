@@ -212,5 +212,23 @@ def routed_grid():
         assert tiles + 192 <= grid <= tiles + 300 and grid * 512 < 1 << 32, (T, tiles, grid)
 
 
+def float_blocks():
+    """Float storage in blocks too small for the partial sums of all splits: several splits per workgroup, and where there is room for
+    four partial sums (all that was ever asked for at this size before K was split further) still a workgroup for each."""
+    T, d_model, widths = 256, 896, [1216] * 4
+    least, full = least_and_full(T, d_model, 4864, 4)
+    part = T * d_model * 4
+    lib.mlpmoe_forward_f32_ws.argtypes = None
+    off, alpha, on, d_inter, B = table(widths)
+    seen = []
+    for n in (full, full - 256, least + 4 * part, least + 2 * part, least):
+        assert lib.mlpmoe_forward_f32_ws(P, P, P, P, off, alpha, on, T, d_model, d_inter, B, P, P, ctypes.c_size_t(n), None) == OK
+        launches = [l for l in record() if l[0] == "launch"][1:]
+        assert "down_mfma" in launches[0][1] and (len(launches) == 1 or "reduce_partials" in launches[1][1]), launches
+        seen.append((int(launches[0][2]) // 56, len(launches)))           # 4 x 14 tiles of 64 x 64
+    splits = (full - least) // part
+    assert splits > 4 and seen == [(splits, 2)] + [(s, 2) for s in (seen[1][0],) * 2] + [(1, 1)] * 2 and 2 < seen[1][0] <= 4, (splits, seen)
+
+
 globals()[sys.argv[1]]()
 print("ok")

@@ -98,6 +98,7 @@ def test_f32_split_k_and_small_workspace(mm, T):
     ([2048, 2048], [1, 1], 3, 64),                       # even runs
     ([1003, 1003, 1003, 1003], [1, 1, 0, 1], 130, 68),   # edge chunks, added by the last split
     ([36, 4] * 32, [1, 0] * 32, 17, 64),                 # short runs: more K tiles than the width adds up to
+    ([1024, 1024], [1, 1], 100, 896), ([1003, 1003, 1002], [1, 0, 1], 250, 512), ([900] * 4, [1] * 4, 200, 1280),   # splits in groups
 ])
 def test_f32_same_bits_in_any_block(mm, widths, mask, T, d_model):
     """Where the partial sums of a K split are kept, or that there is no room for them, does not show in the result."""
@@ -111,7 +112,8 @@ def test_f32_same_bits_in_any_block(mm, widths, mask, T, d_model):
     least = mm.mlpmoe_workspace_bytes(T, 1 << 22, int(off[-1]), len(alpha), 2) - hidden[0] + hidden[1]
     assert least < full                                  # K is split
     results = []
-    for n in (full, full + 4096, full - 1, (least + full) // 2, least):
+    part = T * d_model * 4
+    for n in [full, full + 4096, full - 1, (least + full) // 2] + list(range(least, full, part)):
         ws = torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda")
         out = torch.full((T, d_model), float("nan"), dtype=torch.float32, device="cuda")
         mm.mlpmoe_forward_f32_ws(*dev, off, alpha, mask, ws, out=out)
