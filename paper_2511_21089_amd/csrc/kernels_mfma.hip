@@ -1395,8 +1395,8 @@ using ShapeSlim = ShapeT<BM_SLIM, SLIM_WM, 2, SLIM_D, true>;
 // float MFMA rate (v_mfma_f32_16x16x4_f32, 256 flop per clock and CU, a sixteenth of bf16's), which this small a tile
 // already reaches: it asks the L2 for 16 bytes per clock and CU while the matrix pipe is busy, of about 40 available,
 // and small tiles fill the chip at the sizes float storage is used for (4864 neurons and 256 tokens are 608 tiles; the
-// 128 x (64 + 64) tile would make 152).  The layer at T = 256: 84 us against 1007 us on the general FMA kernels, error
-// against float64 1.0e-6 against 1.5e-6 (rel.).
+// 128 x (64 + 64) tile would make 152).  The layer at T = 256: 80 us against 1007 us on the general FMA kernels, error
+// against float64 0.9e-6 against 1.5e-6 (rel.).
 // Gate+up also with 32 tokens: half the work per tile where 64 leave the last round of workgroups emptier, and with four
 // K tiles requested ahead where there are at most two workgroups per CU to hide each other's latency (see pick_f32_tokens).
 using ShapeF32 = ShapeT<64, 2, 1, 2, false>;
@@ -1785,13 +1785,18 @@ static F32Split f32_split(int T, int d_model, int kt)
 }
 
 // Token rows per gate+up tile.  Rounds of 64-token tiles against half rounds of 32-token ones, of which a CU holds four at a
-// time: a fifth runs alone and hides nothing.  896 x 4864, whole call, 64 / 32 tokens: T = 128 58.7 / 53.7 us, T = 256
-// 91.2 / 96.3 us; 1280 x 3328, T = 200 87.6 / 80.7 us; 512 x 2560, T = 300 39.7 / 41.8 us.
-static int pick_f32_tokens(long long tiles_n, int T)
+// time (the deep form two): a fifth runs alone and hides nothing.  Where both are one round of the chip, the deep form has two
+// workgroups per CU with four K tiles asked for each, which pays from about 24 K tiles on.  us of gate+up, 64 / 32 / 32 deep:
+//   one round either way: 896 x 4864, T = 64 30.6 / 28.4 / 25.6, 1024 x 4096, T = 100 33.9 / 31.9 / 29.2, 1280 x 3328, T = 100 40.8 / 38.2 / 34.6, 2048 x
+//   5504, T = 64 62.7 / 57.5 / 50.3;  512 x 2560, T = 100 16.4 / 16.9 / 17.0, 640 x 1600, T = 200 19.4 / 19.8 / 20.0;
+//   more: 896 x 4864, T = 128 39.4 / 34.7 / 38.6, T = 256 53.6 / 58.7 / 57.9, T = 400 84.2 / 76.9 / 85.9; 1280 x 3328, T = 200 52.5 / 46.0 / 51.2;
+//   512 x 2560, T = 330 25.6 / 27.3 / 30.4.
+constexpr int F32_DEEP_MIN_D = 768;
+static int pick_f32_tokens(long long tiles_n, int T, int d_model)
 {
     const long long whole = tiles_n * ceil_div(T, ShapeF32::BMT), half = tiles_n * ceil_div(T, ShapeF32Half::BMT);
     const long long cost64 = 2 * ((whole + kCUs - 1) / kCUs), cost32 = (half + kCUs - 1) / kCUs + (half > 4 * kCUs ? 1 : 0);
-    return cost32 < cost64 ? 32 : 64;
+    return cost32 < cost64 || (cost32 == cost64 && half <= 2 * kCUs && d_model >= F32_DEEP_MIN_D) ? 32 : 64;
 }
 
 size_t mfma_partial_bytes_f32(int T, int d_model, int d_inter)
@@ -1805,8 +1810,8 @@ static hipError_t launch_mfma_f32_runs(const FwdArgs &a, const BranchTable &oute
 {
     long long tiles_n = 0;
     for (int r = 0; r < outer.n_runs; ++r) tiles_n += ceil_div(outer.run_end[r] - outer.run_start[r], 32 * ShapeF32::NB);
-    const bool half = pick_f32_tokens(tiles_n, a.T) == 32;
-    // T = 60 42.9 us, with four K tiles ahead 38.9 us; T = 20 41.2 and 30.5 us; T = 128 (608 tiles) 53.7 and 56.0 us
+    const bool half = pick_f32_tokens(tiles_n, a.T, a.d_model) == 32;
+    // us of gate+up with two and with four K tiles ahead, 896 x 4864: T = 20 (152 tiles) 27.2 / 18.0, T = 96 (456) 29.6 / 26.2, T = 128 (608) 34.7 / 38.6
     const bool deep = tiles_n * ceil_div(a.T, ShapeF32Half::BMT) <= 2 * kCUs;
     const hipError_t e = !half ? launch_gate_up<ShapeF32, kEdges, float>(a, outer)
                                : (deep ? launch_gate_up<ShapeF32HalfDeep, kEdges, float>(a, outer)

@@ -230,5 +230,16 @@ def float_blocks():
     assert splits > 4 and seen == [(splits, 2)] + [(s, 2) for s in (seen[1][0],) * 2] + [(1, 1)] * 2 and 2 < seen[1][0] <= 4, (splits, seen)
 
 
+def float_token_tiles():
+    """Float storage, gate+up: 32-token tiles where they take fewer rounds, and with a deep ring where one round of the chip is enough
+    for either and K is long."""
+    tile64, tile32, deep = "gate_up_mfmaILi64ELi2ELi1ELi2E", "gate_up_mfmaILi32ELi2ELi1ELi2E", "gate_up_mfmaILi32ELi2ELi1ELi4E"
+    for T, d_model, d_inter, kernel in ((20, 896, 4864, deep), (64, 896, 4864, deep), (100, 512, 2560, tile64), (100, 768, 2560, deep),
+                                        (100, 764, 2560, tile64), (128, 896, 4864, tile32), (256, 896, 4864, tile64),
+                                        (400, 896, 4864, tile32), (330, 512, 2560, tile64)):
+        assert forward(lib.mlpmoe_forward_f32, T, d_model, [d_inter]) == OK
+        assert kernel in kernels(record())[0], (T, d_model, d_inter)
+
+
 globals()[sys.argv[1]]()
 print("ok")

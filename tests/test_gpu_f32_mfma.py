@@ -133,7 +133,7 @@ def test_f32_same_bits_in_any_block(mm, widths, mask, T, d_model):
 @pytest.mark.parametrize("T", [31, 32, 97, 128, 129, 250])
 @pytest.mark.parametrize("widths,mask", [([4864], [1]), ([1621, 1621, 1622], [1, 0, 1])])
 def test_f32_token_tiles(mm, widths, mask, T):
-    """Gate+up tiles of 32 tokens (one workgroup per CU with four K tiles ahead: T = 31, 32; three: T = 97, 128) and of 64."""
+    """Gate+up tiles of 32 tokens (with two and with four K tiles ahead) and of 64, full and partly filled."""
     args = make(widths, mask, T, 72, seed=T)
     check(run_gpu(*poison_pruned(args)), *args)
 
