@@ -986,27 +986,36 @@ constexpr size_t kStreamLdsMax = 160 * 1024;
 
 }  // namespace
 
-template <int NW, int XB, bool kRouted, bool kEdges, typename E>
+// kFew: sizes that are only taken with at most 8 tokens.
+template <int NW, int XB, bool kRouted, bool kEdges, typename E, bool kFew = false>
 static void launch_gate_up_once_xb(const FwdArgs &a, const BranchTable &bt, int tiles, float *clear, int clear_n)
 {
-    const auto kernel = a.T <= 8 ? decode_gate_up_once<NW, XB, 2, kRouted, kEdges, E> : decode_gate_up_once<NW, XB, 1, kRouted, kEdges, E>;
+    auto kernel = decode_gate_up_once<NW, XB, 2, kRouted, kEdges, E>;
+    if constexpr (!kFew) kernel = a.T <= 8 ? kernel : decode_gate_up_once<NW, XB, 1, kRouted, kEdges, E>;
     kernel<<<tiles, NW * 64, 0, a.stream>>>(
         static_cast<const E *>(a.x), a.T, static_cast<const E *>(a.Wg), static_cast<const E *>(a.Wu),
         a.d_model, static_cast<E *>(a.H), a.ldh, a.route, clear, clear_n, tiles, bt);
 }
-// d_model is at most ONCE_MAX_D (bf16) or ROWS_MAX_D.
+// Whole tables in bf16: d_model is at most ONCE_MAX_D, with more than 8 tokens ONCE_MAX_D_16.  Odd boundaries and float storage: at most
+// ROWS_MAX_D, floats with more than 8 tokens 910 (decode_rows_takes).
 template <bool kRouted, bool kEdges = false, typename E = uint16_t>
 static void launch_gate_up_once(const FwdArgs &a, const BranchTable &bt, int tiles, float *clear, int clear_n)
 {
-    static_assert(ONCE_MAX_D <= 6 * ONCE_NW * RowElem<uint16_t>::KBLK && ROWS_MAX_D <= 8 * 8 * RowElem<float>::KBLK, "K blocks per wave");
-    const int xb = ceil_div(ceil_div(a.d_model, RowElem<E>::KBLK), ONCE_NW);
+    constexpr int KBLK = RowElem<E>::KBLK;
+    constexpr bool kWhole = !kEdges && sizeof(E) == 2;
+    static_assert(ONCE_MAX_D <= 6 * ONCE_NW * KBLK || !kWhole, "K blocks per wave");
+    static_assert(ONCE_MAX_D_16 <= 4 * ONCE_NW * KBLK || !kWhole, "more than 8 tokens: at most 4 K blocks per wave");
+    static_assert(ROWS_MAX_D <= (sizeof(E) == 2 ? 8 * ONCE_NW : 8 * 8) * KBLK && 910 <= 8 * ONCE_NW * KBLK, "K blocks per wave");
+    const int xb = ceil_div(ceil_div(a.d_model, KBLK), ONCE_NW);
     if (xb <= 2) launch_gate_up_once_xb<ONCE_NW, 2, kRouted, kEdges, E>(a, bt, tiles, clear, clear_n);
     else if (xb <= 4) launch_gate_up_once_xb<ONCE_NW, 4, kRouted, kEdges, E>(a, bt, tiles, clear, clear_n);
-    else if (xb <= 6) launch_gate_up_once_xb<ONCE_NW, 6, kRouted, kEdges, E>(a, bt, tiles, clear, clear_n);
-    if constexpr (kEdges || sizeof(E) == 4) {
+    else if (xb <= 6) launch_gate_up_once_xb<ONCE_NW, 6, kRouted, kEdges, E, kWhole>(a, bt, tiles, clear, clear_n);
+    if constexpr (!kWhole) {
         if (xb > 6 && xb <= 8) launch_gate_up_once_xb<ONCE_NW, 8, kRouted, kEdges, E>(a, bt, tiles, clear, clear_n);
-        else if (xb > 8 && xb <= 12) launch_gate_up_once_xb<8, 6, kRouted, kEdges, E>(a, bt, tiles, clear, clear_n);
-        else if (xb > 12) launch_gate_up_once_xb<8, 8, kRouted, kEdges, E>(a, bt, tiles, clear, clear_n);
+    }
+    if constexpr (sizeof(E) == 4) {
+        if (xb > 8 && xb <= 12) launch_gate_up_once_xb<8, 6, kRouted, kEdges, E, true>(a, bt, tiles, clear, clear_n);
+        else if (xb > 12) launch_gate_up_once_xb<8, 8, kRouted, kEdges, E, true>(a, bt, tiles, clear, clear_n);
     }
 }
 
@@ -1041,9 +1050,10 @@ static hipError_t launch_decode_rows_impl(const FwdArgs &a, const BranchTable &b
         return hipErrorLaunchFailure;
     ProfileScope ps(MLPMOE_KERNEL_DECODE_DOWN, a.stream);
     const int rows = down_shape(a.T, a.d_model, a.out_bf16);
-    if (!a.out_bf16) {
-        if (rows == 16) launch_down_rows<16, 1, 2, false, kEdges, E>(a, bt);
-        else a.T <= 8 ? launch_down_rows<8, 2, 2, false, kEdges, E>(a, bt) : launch_down_rows<8, 1, 2, false, kEdges, E>(a, bt);
+    if (!a.out_bf16 && rows == 8)                        // floats: always, 16 rows need more than 8 tokens of more than 1024 features
+        a.T <= 8 ? launch_down_rows<8, 2, 2, false, kEdges, E>(a, bt) : launch_down_rows<8, 1, 2, false, kEdges, E>(a, bt);
+    if constexpr (sizeof(E) == 2) {
+        if (!a.out_bf16 && rows == 16) launch_down_rows<16, 1, 2, false, kEdges, E>(a, bt);
     }
     if constexpr (sizeof(E) == 2) {
         if (a.out_bf16 && rows == 8)
@@ -1150,8 +1160,8 @@ static hipError_t launch_decode_impl(const FwdArgs &a, const BranchTable &bt)
         decode_kernel<DEC_NW2, DEC_U2, false, kRouted><<<tiles2, DEC_NW2 * 64, 0, a.stream>>>(
             H, a.ldh, a.T, static_cast<const uint16_t *>(a.Wd), nullptr, a.d_inter, a.d_model, nullptr,
             a.ldh, a.out, a.out_bf16 ? 1 : 0, a.route, bt);
-    else
-        decode_kernel<16, 4, false, kRouted><<<tiles2, 1024, 0, a.stream>>>(
+    else if constexpr (!kRouted)                         // a bf16 result of 2560 to 3064 features
+        decode_kernel<16, 4, false><<<tiles2, 1024, 0, a.stream>>>(
             H, a.ldh, a.T, static_cast<const uint16_t *>(a.Wd), nullptr, a.d_inter, a.d_model, nullptr,
             a.ldh, a.out, a.out_bf16 ? 1 : 0, a.route, bt);
     return launch_status("decode_down launch");
