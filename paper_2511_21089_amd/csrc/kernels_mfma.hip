@@ -62,10 +62,11 @@ constexpr int BM_SLIM = 64;                          // tokens per tile of the s
 constexpr int SLIM_WM = 2;
 
 // How down_mfma writes its result.  DST_THROUGH: partial sums of at most THROUGH_BYTES, stored past the L2 (sc1), so that the end
-// of the kernel has no dirty lines to write back before the sum may start.  896 x 4864: T = 64 20.9 -> 20.3 us a call, T = 500 34.5 ->
-// 33.1, T = 333 in 12 branches, 9 kept 26.4 -> 25.7; 2048 x 5504, T = 100 34.7 -> 34.1.  Not for more bytes (4096 x 14336, T = 512, 67 MB:
-// 163.5 -> 168.3 with H stored so as well) nor where W_down itself streams from HBM (4096 x 14336: T = 100 85.2 -> 84.5, but T = 64 79.4 ->
-// 80.5).
+// of the kernel has no dirty lines to write back before the sum may start.  us a call, plain / through: 896 x 4864, T = 64 20.9 / 20.3,
+// T = 500 34.5 / 33.1, T = 333 in 12 branches, 9 kept 26.4 / 25.7; 2048 x 5504, T = 100 34.7 / 34.1, T = 250 45.5 / 44.0; 3072 x 8192, T = 100 52.7 / 51.6.
+// Not for more bytes (4096 x 14336, T = 512, 67 MB: 163.5 / 168.3 with H stored so as well).  Layers whose W_down is larger than
+// THROUGH_WEIGHTS and streams from HBM gain less or lose: 4096 x 8192, T = 64 58.3 / 57.8, 5120 x 13824 97.9 / 96.7, 3584 x 18944 104.8 / 103.6, but
+// 4096 x 11008 70.9 / 71.8, 4096 x 14336 86.0 / 87.0 and T = 100 92.7 / 93.3.
 enum { DST_F32 = 0, DST_BF16 = 1, DST_THROUGH = 2 };
 constexpr size_t THROUGH_BYTES = 16u << 20, THROUGH_WEIGHTS = 64u << 20;      // partial sums, W_down
 constexpr int STORE_SC1 = 16;           // cache policy of a buffer store: sc1

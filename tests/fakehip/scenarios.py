@@ -241,5 +241,15 @@ def float_token_tiles():
         assert kernel in kernels(record())[0], (T, d_model, d_inter)
 
 
+def partial_sums_at_the_limit():
+    """The splits of the calls that test_gpu_split_sum.py has around 16 MiB of partial sums."""
+    for T, d_model, d_inter, tile_rows, splits in ((2048, 512, 2048, 128, 4), (1021, 1016, 2048, 128, 4), (1028, 1048, 4096, 256, 5)):
+        assert forward(lib.mlpmoe_forward_bf16, T, d_model, [d_inter]) == OK
+        _, down, total = [l for l in record() if l[0] == "launch"]
+        tiles = -(-T // tile_rows) * -(-d_model // 128)
+        assert "down_mfmaILi%dE" % tile_rows in down[1] and "reduce_partials" in total[1], down
+        assert int(down[2]) == (tiles * splits + 7) // 8 * 8, (T, down)
+
+
 globals()[sys.argv[1]]()
 print("ok")

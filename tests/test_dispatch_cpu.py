@@ -22,7 +22,8 @@ def fake(tmp_path_factory):
 
 @pytest.mark.parametrize("scenario", ["graph_block_stays", "short_of_memory", "most_tokens", "widest_routed", "smallest_routed",
                                       "unsplit_narrow", "in_place", "decode_gate_up", "decode_down", "decode_few_tokens",
-                                      "decode_odd_boundaries", "routed_grid", "float_blocks", "float_token_tiles"])
+                                      "decode_odd_boundaries", "routed_grid", "float_blocks", "float_token_tiles",
+                                      "partial_sums_at_the_limit"])
 def test_scenario(fake, scenario):
     from paper_2511_21089_amd import binding as mm
     res = subprocess.run([sys.executable, os.path.join(FAKE, "scenarios.py"), scenario, fake, mm.lib._name],

@@ -39,10 +39,10 @@ def test_split_sum(mm, T, d_model, d_inter):
     assert np.all(np.abs(low - got) <= 2.0 ** -8 * np.abs(got) + 1e-30)
 
 
-# Partial sums of at most 16 MiB under a W_down of at most 64 MiB are stored past the L2: around both limits (four splits
-# of 1170 x 896 floats end 4 KiB below 16 MiB; 4096 x 8192 is 64 MiB in bf16), and with tiles that end inside T and d_model.
+# Partial sums of at most 16 MiB under a W_down of at most 64 MiB are stored past the L2, through a descriptor of 16 MiB: four
+# splits of 2048 x 512 floats end where it ends, four of 1021 x 1016 just below and with tiles that end inside both, five of 1028 x 1048
+# are above (tests/test_dispatch_cpu.py checks that the splits are these); 4096 x 8192 is 64 MiB in bf16.
 @pytest.mark.parametrize("T,d_model,d_inter", [
-    (65, 904, 4864), (129, 1032, 4096), (1170, 896, 4864), (1171, 896, 4864), (2048, 896, 4864), (65, 4096, 8192),
-    (65, 4096, 8200)])
+    (65, 904, 4864), (129, 1032, 4096), (2048, 512, 2048), (1021, 1016, 2048), (1028, 1048, 4096), (65, 4096, 8192), (65, 4096, 8200)])
 def test_partial_sums_around_the_store_limits(mm, T, d_model, d_inter):
     test_split_sum(mm, T, d_model, d_inter)
