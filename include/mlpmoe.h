@@ -64,10 +64,11 @@ enum {
 /* Kernel path selection for the *_ws entry points. */
 enum {
     MLPMOE_PATH_AUTO = 0,    /* library picks.  bf16: decode for T <= 16, MFMA otherwise; with branch boundaries
-                              * off a multiple of 8 decode for small T * d_model (not routed), else MFMA; generic if
+                              * off a multiple of 8 decode for d_model <= 2048, T * d_model <= 25600 and at most 8192
+                              * active neurons (T <= 8: 32768, T <= 4: any; not routed), else MFMA; generic if
                               * d_model or d_inter is not a multiple of 8.  Float storage (always AUTO): decode for
-                              * T <= 8 (narrow layers: 16), else MFMA, generic if d_model or d_inter is not a
-                              * multiple of 4 and for routed calls                                         */
+                              * d_model <= 2048 and T <= 8 (T * d_model <= 8192: 16), else float MFMA; generic if d_model
+                              * or d_inter is not a multiple of 4 and for routed calls                     */
     MLPMOE_PATH_GENERIC = 1, /* LDS-tiled FMA kernels: any shape and alignment                        */
     MLPMOE_PATH_MFMA = 2,    /* bf16 MFMA prefill kernels (needs d_model%8==0 and offsets%8==0)       */
     MLPMOE_PATH_DECODE = 3,  /* weight-streaming kernels, T <= 16 (same alignment needs as MFMA)      */
@@ -182,7 +183,7 @@ MLPMOE_API size_t mlpmoe_workspace_bytes(int T, int d_model, int d_inter, int B,
  * accumulates those bf16 values against W_down in fp32 across all branches.
  * Results are bitwise reproducible from run to run, and do not depend on the workspace: sums are formed
  * in an order that follows from the sizes (T among them), the table and the path; the one place
- * that uses floating-point atomics (the decode down projection of wide layers) adds exactly two
+ * that uses floating-point atomics (the decode down projection with a float result) adds exactly two
  * partial sums into a zero, which gives the same number in either order.
  *
  * Workspace: the block given to mlpmoe_set_workspace() for the current device if there is
