@@ -366,11 +366,22 @@ __device__ __forceinline__ void mainloop(const E *__restrict__ A_tile, int lda, 
     // operand.  In the 16x16 result lane l then holds column l & 15 = one token and rows
     // 4 * (l >> 4) + 0..3 = four consecutive B rows, which the epilogues store as one 8- or 16-byte
     // piece of the token's output row.  Otherwise tokens are the rows.
-    auto mfma_n = [&](const Frags &f, int m, int e) {
+    // Floats: the second K step of every tile has sums of its own.  Chains of half the length leave less of an error: 896 x 4864, T = 256
+    // against float64 9.2e-7 -> 6.4e-7, T = 500 1.1e-6 -> 6.8e-7, in the same time.
+    constexpr bool kTwoSums = sizeof(E) == 4;
+    f32x4 second0[kTwoSums ? MI : 1][NB], second1[kTwoSums ? MI : 1][NB];
+    auto clear_second = [&]() {
+#pragma unroll
+        for (int i = 0; i < (kTwoSums ? MI : 1); ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) second0[i][j] = second1[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    auto mfma_n = [&](const Frags &f, int m, int e, bool second_step) {
         const int i = m / (2 * NB), b = m % (2 * NB);
         const Frag<E> r = kRowsAreB ? f.v[b] : f.v[2 * NB + i], c = kRowsAreB ? f.v[2 * NB + i] : f.v[b];
-        if (b < NB) acc0[i][b] = mfma_step(r, c, acc0[i][b], e);
-        else acc1[i][b - NB] = mfma_step(r, c, acc1[i][b - NB], e);
+        f32x4 &acc = kTwoSums && second_step ? (b < NB ? second0[kTwoSums ? i : 0][b % NB] : second1[kTwoSums ? i : 0][b % NB])
+                                             : (b < NB ? acc0[i][b % NB] : acc1[i][b % NB]);
+        acc = mfma_step(r, c, acc, e);
     };
     // One K step, written in the instruction order wanted: slots of {4 MFMAs, then LDS reads of
     // the next step's fragments, then (in evenly spaced slots) one direct load}; nothing may be
@@ -386,14 +397,14 @@ __device__ __forceinline__ void mainloop(const E *__restrict__ A_tile, int lda, 
             // asking at 1, cannot cut in, which the older wave otherwise always does) and drops
             // to 0 for its loads and address arithmetic, which then run under the other's turn.
             __builtin_amdgcn_s_setprio(1);
-            mfma_n(cur_f, SLOT * g, 0);
+            mfma_n(cur_f, SLOT * g, 0, rd_ks == 0);
             __builtin_amdgcn_s_setprio(3);
 #pragma unroll
-            for (int q = 1; q < SLOT; ++q) mfma_n(cur_f, SLOT * g + q, 0);
+            for (int q = 1; q < SLOT; ++q) mfma_n(cur_f, SLOT * g + q, 0, rd_ks == 0);
 #pragma unroll
             for (int e = 1; e < MFMAS_PER_CHUNK<E>; ++e)
 #pragma unroll
-                for (int q = 0; q < SLOT; ++q) mfma_n(cur_f, SLOT * g + q, e);
+                for (int q = 0; q < SLOT; ++q) mfma_n(cur_f, SLOT * g + q, e, rd_ks == 0);
             __builtin_amdgcn_s_setprio(0);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -439,6 +450,7 @@ __device__ __forceinline__ void mainloop(const E *__restrict__ A_tile, int lda, 
     for (int g = 0; g < N_PIECES; ++g) read_piece(f0, g, 0, 0);
 
     int rd = 0;                                   // byte offset in the ring of the A part of the tile in use
+    clear_second();
     int it = 0, until = nk;
     if constexpr (St::kSome) until = stops.first - kt_begin;
     do {
@@ -452,6 +464,16 @@ __device__ __forceinline__ void mainloop(const E *__restrict__ A_tile, int lda, 
             const Part pb = part_of(qb, b_base, wb_dst, b_cl0);
             k_step(f1, f0, rd, 0, 2, pb);             // + B part of tile it+D
             advance(qb);
+        }
+        if constexpr (kTwoSums) {
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    acc0[i][j] += second0[i][j];
+                    acc1[i][j] += second1[i][j];
+                }
+            clear_second();
         }
         if constexpr (St::kSome) until = stops(kt_begin + it) - kt_begin;
     } while (it < nk);
@@ -1397,7 +1419,7 @@ using ShapeSlim = ShapeT<BM_SLIM, SLIM_WM, 2, SLIM_D, true>;
 // already reaches: it asks the L2 for 16 bytes per clock and CU while the matrix pipe is busy, of about 40 available,
 // and small tiles fill the chip at the sizes float storage is used for (4864 neurons and 256 tokens are 608 tiles; the
 // 128 x (64 + 64) tile would make 152).  The layer at T = 256: 80 us against 1007 us on the general FMA kernels, error
-// against float64 0.9e-6 against 1.5e-6 (rel.).
+// against float64 0.64e-6 against 1.5e-6 (rel.).
 // Gate+up also with 32 tokens: half the work per tile where 64 leave the last round of workgroups emptier, and with four
 // K tiles requested ahead where there are at most two workgroups per CU to hide each other's latency (see pick_f32_tokens).
 using ShapeF32 = ShapeT<64, 2, 1, 2, false>;
