@@ -935,6 +935,7 @@ decode_down_rows(const E *__restrict__ Hin, int ldx, int T, const E *__restrict_
 //     1152 x 6208 T = 10 18.9 / 19.9, 1280 x 6912 T = 10 20.4 / 21.3, 1408 x 7552 T = 10 21.6 / 22.8.
 constexpr int ONCE_MAX_D = 1536, ONCE_MAX_D_16 = 1024, ONCE_NW = 4;
 constexpr long long ONCE_X_BYTES_4 = 64 << 20, ONCE_X_BYTES_8 = 32 << 20, ONCE_X_BYTES_16 = 24 << 20;
+constexpr int ONCE_ROUTED_X = 14336;                     // elements of x
 constexpr int ROWS_MAX_D = 2048;                         // float storage and odd boundaries: what 8 waves hold of x
 bool gate_up_once(int T, int d_model, long long tiles)
 {
@@ -996,13 +997,13 @@ static void launch_gate_up_once_xb(const FwdArgs &a, const BranchTable &bt, int 
         static_cast<const E *>(a.x), a.T, static_cast<const E *>(a.Wg), static_cast<const E *>(a.Wu),
         a.d_model, static_cast<E *>(a.H), a.ldh, a.route, clear, clear_n, tiles, bt);
 }
-// Whole tables in bf16: d_model is at most ONCE_MAX_D, with more than 8 tokens ONCE_MAX_D_16.  Odd boundaries and float storage: at most
+// Whole tables in bf16: d_model is at most ONCE_MAX_D, with more than 8 tokens ONCE_MAX_D_16 (not routed).  Odd boundaries and float storage: at most
 // ROWS_MAX_D, floats with more than 8 tokens 910 (decode_rows_takes).
 template <bool kRouted, bool kEdges = false, typename E = uint16_t>
 static void launch_gate_up_once(const FwdArgs &a, const BranchTable &bt, int tiles, float *clear, int clear_n)
 {
     constexpr int KBLK = RowElem<E>::KBLK;
-    constexpr bool kWhole = !kEdges && sizeof(E) == 2;
+    constexpr bool kWhole = !kEdges && !kRouted && sizeof(E) == 2;
     static_assert(ONCE_MAX_D <= 6 * ONCE_NW * KBLK || !kWhole, "K blocks per wave");
     static_assert(ONCE_MAX_D_16 <= 4 * ONCE_NW * KBLK || !kWhole, "more than 8 tokens: at most 4 K blocks per wave");
     static_assert(ROWS_MAX_D <= (sizeof(E) == 2 ? 8 * ONCE_NW : 8 * 8) * KBLK && 910 <= 8 * ONCE_NW * KBLK, "K blocks per wave");
@@ -1010,7 +1011,7 @@ static void launch_gate_up_once(const FwdArgs &a, const BranchTable &bt, int til
     if (xb <= 2) launch_gate_up_once_xb<ONCE_NW, 2, kRouted, kEdges, E>(a, bt, tiles, clear, clear_n);
     else if (xb <= 4) launch_gate_up_once_xb<ONCE_NW, 4, kRouted, kEdges, E>(a, bt, tiles, clear, clear_n);
     else if (xb <= 6) launch_gate_up_once_xb<ONCE_NW, 6, kRouted, kEdges, E, kWhole>(a, bt, tiles, clear, clear_n);
-    if constexpr (!kWhole) {
+    if constexpr (kEdges || sizeof(E) == 4) {
         if (xb > 6 && xb <= 8) launch_gate_up_once_xb<ONCE_NW, 8, kRouted, kEdges, E>(a, bt, tiles, clear, clear_n);
     }
     if constexpr (sizeof(E) == 4) {
@@ -1086,7 +1087,9 @@ static hipError_t launch_decode_impl(const FwdArgs &a, const BranchTable &bt)
     float *clear = cleared_by_gate_up(a, split_down);
     const int clear_n = a.T * a.d_model;
     const uint16_t *Wg = static_cast<const uint16_t *>(a.Wg), *Wu = static_cast<const uint16_t *>(a.Wu);
-    if (gate_up_once(a.T, a.d_model, tiles1)) {
+    // How many tiles of a routed call are live is known on the device only.  Few are, as a rule, and the one-tile workgroups end sooner:
+    // 1152 x 6208, T = 12, 1 / 4 / 8 of 16 branches 12.7 / 13.7 / 16.4 us, with the ring kernel 14.2 / 15.2 / 17.7.
+    if (kRouted ? a.d_model <= ONCE_MAX_D && a.T * a.d_model <= ONCE_ROUTED_X : gate_up_once(a.T, a.d_model, tiles1)) {
         ProfileScope ps(MLPMOE_KERNEL_DECODE_GATE_UP, a.stream);
         launch_gate_up_once<kRouted>(a, bt, (int)tiles1, clear, clear_n);
         if (launch_status("decode gate+up (one tile per workgroup) launch") != hipSuccess) return hipErrorLaunchFailure;
@@ -1140,9 +1143,14 @@ static hipError_t launch_decode_impl(const FwdArgs &a, const BranchTable &bt)
     }
     if (clear_in_place(a, split_down) != hipSuccess) return hipErrorLaunchFailure;
     ProfileScope ps(MLPMOE_KERNEL_DECODE_DOWN, a.stream);
-    const int rows = persistent ? down_shape(a.T, a.d_model, a.out_bf16) : 0;
-    if (split_down && down_long_k(a.T, a.d_model, bt.d_eff))
-        decode_down_split<16, 4, 1, kRouted><<<dim3(tiles2, 2), 16 * 64, 0, a.stream>>>(
+    // Routed calls: how many neurons some token takes is known on the device only, and walking a stretch per branch costs the many
+    // workgroups of a few rows more.  They keep the kernels that are right for a short K: 4096 x 14336, T = 2, 1 / 2 / 4 of 16 branches with
+    // 8 rows 17.7 / 18.8 / 23.9 us, with the wide kernel 15.1 / 17.0 / 23.2; 1536 x 16384, T = 16, 1 / 4 branches with 16 waves 18.2 / 22.8, with
+    // rows 16.4 / 20.7.
+    const bool wide_routed = kRouted && tiles2 >= WIDE_TILES && a.T * (long long)a.d_model > 4096;
+    const int rows = !persistent || wide_routed ? 0 : down_shape(a.T, a.d_model, a.out_bf16);
+    if (!kRouted && split_down && down_long_k(a.T, a.d_model, bt.d_eff))
+        decode_down_split<16, 4, 1><<<dim3(tiles2, 2), 16 * 64, 0, a.stream>>>(
             H, a.ldh, a.T, static_cast<const uint16_t *>(a.Wd), a.d_inter, a.d_model, a.out, a.route, bt);
     else if (split_down && rows == 16)
         launch_down_rows<16, 1, 2, kRouted>(a, bt);

@@ -165,6 +165,9 @@ def decode_gate_up():
         assert forward(lib.mlpmoe_forward_bf16, T, d_model, [d_inter]) == OK, lib.mlpmoe_last_error_detail()
         name = kernels(record())[0]
         assert ("gate_up_once" if once else "gate_up_xreg") in name, (T, d_model, d_inter, name)
+    for T, d_model, once in ((12, 1152, 1), (8, 1536, 1), (16, 896, 1), (16, 904, 0), (1, 1544, 0)):     # routed: by x alone
+        assert forward(lib.mlpmoe_forward_routed_bf16, T, d_model, [16384], None, True) == OK
+        assert ("gate_up_once" if once else "gate_up_xreg") in kernels(record())[0], (T, d_model)
 
 
 def decode_few_tokens():
@@ -177,6 +180,9 @@ def decode_few_tokens():
         assert forward(f, T, d_model, [1024]) == OK, lib.mlpmoe_last_error_detail()
         name = kernels(record())[-1]
         assert kernel in name, (T, d_model, name)
+    for T, d_model, kernel in ((2, 4096, "down_splitILi4"), (1, 8192, "down_splitILi4"), (1, 4096, rows8), (2, 3056, rows8)):
+        assert forward(lib.mlpmoe_forward_routed_bf16, T, d_model, [1024], None, True) == OK
+        assert kernel in kernels(record())[-1], (T, d_model)
 
 
 def decode_down():
@@ -190,6 +196,8 @@ def decode_down():
         assert kernel in name, (T, d_model, d_inter, name)
         assert forward(lib.mlpmoe_forward_bf16_out_bf16, T, d_model, [d_inter]) == OK
         assert "down_split" not in kernels(record())[-1]
+    assert forward(lib.mlpmoe_forward_routed_bf16, 8, 1280, [16384], None, True) == OK       # how long K is depends on the routes
+    assert "down_rows" in kernels(record())[-1]
 
 
 def decode_odd_boundaries():
