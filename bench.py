@@ -37,10 +37,10 @@ TRAFFIC = {
     # (workload, kernel): (sha256 of the kernel's source file, bytes per launch = read + written, summary file)
     # gate_up_mfma at T=4096: 1409.5 MB read (x is re-read once per group of 4 neuron tiles and the
     # weights once per XCD that needs them: 5.3x the 268 MB the kernel has to read) + 117.5 MB written
-    ("llama8b_T4096", "gate_up_mfma"): ("eef7c5449bc106c017219800a96630a90758b281d87b27f5b339d46cae040c76", 1527.0e6,
+    ("llama8b_T4096", "gate_up_mfma"): ("d4594d1c179225b761b13aca1960971cdc6b411c7f122b005bf38bf67df1130e", 1526.9e6,
                                         "profiles/bench_llama8b_T4096_hbm_counters.md"),
-    # decode gate+up at T=1: 236.8 MB read (the weights, once) + 0.1 MB written
-    ("llama8b_T1", "decode_gate_up"): ("52d359e791ce157a0d3ba4b8b6b389e07fd36d0d830f56c3296f858d417c5f57", 236.9e6,
+    # decode gate+up at T=1: 236.3 MB read (the weights, once) + 0.1 MB written
+    ("llama8b_T1", "decode_gate_up"): ("05d3b53a9b77de2bf2eed916af8e9cd2e0c45006dec4ffe71711e494ebd04c8e", 236.4e6,
                                        "profiles/bench_llama8b_T1_hbm_counters.md"),
 }
 PREWARM_S = 0.1          # untimed repetitions of the step before the warm-up steps (see time_steps)
